@@ -760,7 +760,16 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
 // Pass 2, with each tile's first run and piece known: the slice's runs
 // (lattice point per run, run slot per entry in point order), the splat's
 // entries in run order (point within the tile, weight) and its pieces
-// (first entry relative to the tile, lattice point).
+// (first entry relative to the tile and length; lattice point). Pieces are
+// stored longest first (a stable counting sort by length: the pieces of one
+// lattice point keep their order, as only the last is short), so that the
+// splat's waves take pieces of about equal length.
+// Counters of that sort: (K - length, round, wave).
+constexpr int kPieceCounters = kPiece * kTileSpan * (kTileThreads / 64);
+static_assert(kPieceCounters == 2 * kTileThreads && kPiece < 64, "two piece counters per thread");
+__device__ __forceinline__ int piece_counter(int digit, int round) {
+  return (digit * kTileSpan + round) * (kTileThreads / 64) + (int)(threadIdx.x >> 6);
+}
 __global__ __launch_bounds__(kTileThreads) void k_tile_fill(const sgp_entry* __restrict__ pm,
                                                             const uint16_t* __restrict__ ord, int64_t n,
                                                             int D, int P, int K,
@@ -771,9 +780,10 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_fill(const sgp_entry* __r
                                                             float* __restrict__ ws,
                                                             uint8_t* __restrict__ ent_lp,
                                                             float* __restrict__ ent_w,
-                                                            uint16_t* __restrict__ run_rel,
+                                                            uint32_t* __restrict__ piece,
                                                             int32_t* __restrict__ piece_vert) {
   __shared__ TileSort T;
+  __shared__ int32_t cnt[kPieceCounters];
   const int64_t t = blockIdx.x;
   const int64_t p0 = t * P;
   const int ne = (int)((n - p0 < P ? n - p0 : P) * D);
@@ -802,10 +812,49 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_fill(const sgp_entry* __r
     ent_w[base + i] = pm[base + le].w;
     loc[base + le] = (uint16_t)r.q[u];
     if (r.rs[u]) tile_verts[q0 + r.q[u]] = j;
-    if (r.qp[u] >= 0) {
-      run_rel[qp0 + r.qp[u]] = (uint16_t)i;
-      piece_vert[qp0 + r.qp[u]] = j;
+  }
+  // pieces, longest first
+  for (int c = threadIdx.x; c < kPieceCounters; c += kTileThreads) cnt[c] = 0;
+#pragma unroll
+  for (int u = 0; u < kTileSpan; ++u)
+    if (r.qp[u] >= 0) T.rstart[r.qp[u]] = i0 + u;  // the run starts are no longer read
+  __syncthreads();
+  int start[kTileSpan], len[kTileSpan], rk[kTileSpan];
+#pragma unroll
+  for (int u = 0; u < kTileSpan; ++u) {
+    const int p = threadIdx.x + u * kTileThreads;
+    rk[u] = 0;
+    len[u] = 0;
+    if (u * kTileThreads >= r.pieces) continue;  // uniform
+    if (p < r.pieces) {
+      start[u] = T.rstart[p];
+      len[u] = (p + 1 < r.pieces ? T.rstart[p + 1] : ne) - start[u];
     }
+    unsigned long long peers = __ballot(len[u] > 0);  // lanes whose piece is as long as this lane's
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+      const bool set = (len[u] >> k) & 1;
+      const unsigned long long bal = __ballot(set);
+      peers &= set ? bal : ~bal;
+    }
+    if (len[u] > 0) {
+      rk[u] = (int)__popcll(peers & ((1ull << (threadIdx.x & 63)) - 1));
+      if (rk[u] == 0) cnt[piece_counter(K - len[u], u)] = (int)__popcll(peers);
+    }
+  }
+  __syncthreads();
+  int tot;
+  const int c0 = threadIdx.x * 2, a0 = cnt[c0], a1 = cnt[c0 + 1];
+  const int pre = tile_scan(a0 + a1, T.wsum, &tot);  // every thread has read its counters
+  cnt[c0] = pre;
+  cnt[c0 + 1] = pre + a0;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kTileSpan; ++u) {
+    if (len[u] == 0) continue;
+    const int64_t o = qp0 + cnt[piece_counter(K - len[u], u)] + rk[u];
+    piece[o] = (uint32_t)start[u] | (uint32_t)len[u] << 16;
+    piece_vert[o] = (int32_t)(T.key[tile_at(start[u])] >> 12);
   }
 }
 
@@ -1168,7 +1217,7 @@ int build_attempt(sgp_lattice* L, const float* X, const double* f, double load_f
   uint32_t* va = (uint32_t*)tr.ptr[T_VA];
   uint32_t* vb = (uint32_t*)tr.ptr[T_VB];
   uint32_t* sort_tmp = (uint32_t*)tr.ptr[T_SORTTMP];
-  for (sgp::DevBuf* b : {&L->perm, &L->loc, &L->ws, &L->tile_off, &L->tile_verts, &L->run_rel,
+  for (sgp::DevBuf* b : {&L->perm, &L->loc, &L->ws, &L->tile_off, &L->tile_verts, &L->piece,
                          &L->ent_lp, &L->ent_w, &L->occ_ptr, &L->run_dst, &L->row_vert, &L->stile_off, &L->nbr, &L->int2can})
     dev_free(*b);
   if ((rc = dev_alloc(L->perm, sizeof(uint32_t) * n, st))) return rc;
@@ -1367,7 +1416,7 @@ int build_attempt(sgp_lattice* L, const float* X, const double* f, double load_f
     // four spare bytes: the splat reads entry points four at a time
     if ((rc = dev_alloc(L->ent_lp, sizeof(uint8_t) * (Lel + 4), st))) return rc;
     if ((rc = dev_alloc(L->ent_w, sizeof(float) * Lel, st))) return rc;
-    if ((rc = dev_alloc(L->run_rel, sizeof(uint16_t) * Qs, st))) return rc;
+    if ((rc = dev_alloc(L->piece, sizeof(uint32_t) * Qs, st))) return rc;
     if ((rc = dev_alloc(L->occ_ptr, sizeof(int32_t) * (m + 1), st))) return rc;
     if ((rc = dev_alloc(L->run_dst, sizeof(int32_t) * Qs, st))) return rc;
     if ((rc = dev_alloc(L->row_vert, sizeof(int32_t) * Qs, st))) return rc;
@@ -1379,7 +1428,7 @@ int build_attempt(sgp_lattice* L, const float* X, const double* f, double load_f
                          (const sgp_entry*)tr.ptr[T_PM], (const uint16_t*)ord, n, D, P, kPiece,
                          (const int32_t*)tile_off, (const int32_t*)stile_off, (int32_t*)L->tile_verts.ptr,
                          (uint16_t*)L->loc.ptr, (float*)L->ws.ptr, (uint8_t*)L->ent_lp.ptr,
-                         (float*)L->ent_w.ptr, (uint16_t*)L->run_rel.ptr, (int32_t*)sub);
+                         (float*)L->ent_w.ptr, (uint32_t*)L->piece.ptr, (int32_t*)sub);
       SGP_LAUNCH_CHECK("k_tile_fill");
     }
     // pieces grouped by lattice point (32-bit keys; reuses the sort buffers)

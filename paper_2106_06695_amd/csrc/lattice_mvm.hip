@@ -35,184 +35,10 @@
 
 #include "cg_step.h"
 #include "sgp_internal.h"
+#include "tile.h"
 
 namespace sgp {
 namespace {
-
-constexpr int kXcds = 8;
-
-// Logical block for dispatch slot b when blocks are dealt round-robin over
-// the XCDs: XCD x runs logical blocks [x*q + min(x, r), ...) contiguously.
-__device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t nb) {
-  const int64_t x = b % kXcds, t = b / kXcds;
-  const int64_t q = nb / kXcds, r = nb % kXcds;
-  return x * q + (x < r ? x : r) + t;
-}
-
-__device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
-
-// 16-byte vectors for LDS and global accesses of lattice and point rows.
-typedef double dvec2 __attribute__((ext_vector_type(2)));
-typedef float fvec4 __attribute__((ext_vector_type(4)));
-template <typename T>
-struct Vec16;
-template <>
-struct Vec16<double> {
-  typedef dvec2 T;
-  static constexpr int N = 2;
-};
-template <>
-struct Vec16<float> {
-  typedef fvec4 T;
-  static constexpr int N = 4;
-};
-
-// Read (or write) W consecutive elements at p, as 16-byte vectors when W
-// elements span whole vectors (p is then 16-byte aligned by construction).
-template <typename T, int W>
-__device__ __forceinline__ void read_row(const T* p, T (&o)[W]) {
-  constexpr int N = Vec16<T>::N;
-  if constexpr (W % N == 0) {
-#pragma unroll
-    for (int i = 0; i < W / N; ++i) {
-      const typename Vec16<T>::T x = *(const typename Vec16<T>::T*)(p + i * N);
-#pragma unroll
-      for (int j = 0; j < N; ++j) o[i * N + j] = x[j];
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < W; ++i) o[i] = p[i];
-  }
-}
-template <typename T, int W>
-__device__ __forceinline__ void write_row(T* p, const T (&v)[W]) {
-  constexpr int N = Vec16<T>::N;
-  if constexpr (W % N == 0) {
-#pragma unroll
-    for (int i = 0; i < W / N; ++i) {
-      typename Vec16<T>::T x;
-#pragma unroll
-      for (int j = 0; j < N; ++j) x[j] = v[i * N + j];
-      *(typename Vec16<T>::T*)(p + i * N) = x;
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < W; ++i) p[i] = v[i];
-  }
-}
-
-// read_row with non-temporal loads
-template <typename T, int W>
-__device__ __forceinline__ void read_row_nt(const T* p, T (&o)[W]) {
-  constexpr int N = Vec16<T>::N;
-  if constexpr (W % N == 0) {
-#pragma unroll
-    for (int i = 0; i < W / N; ++i) {
-      const typename Vec16<T>::T x = __builtin_nontemporal_load((const typename Vec16<T>::T*)(p + i * N));
-#pragma unroll
-      for (int j = 0; j < N; ++j) o[i * N + j] = x[j];
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < W; ++i) o[i] = __builtin_nontemporal_load(p + i);
-  }
-}
-
-// write_row with non-temporal stores (streamed past the caches)
-template <typename TU, int W>
-__device__ __forceinline__ void write_row_nt(TU* p, const TU (&v)[W]) {
-  constexpr int N = Vec16<TU>::N;
-  if constexpr (W % N == 0) {
-#pragma unroll
-    for (int i = 0; i < W / N; ++i) {
-      typename Vec16<TU>::T x;
-#pragma unroll
-      for (int j = 0; j < N; ++j) x[j] = v[i * N + j];
-      __builtin_nontemporal_store(x, (typename Vec16<TU>::T*)(p + i * N));
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < W; ++i) __builtin_nontemporal_store(v[i], p + i);
-  }
-}
-
-// Persistent tile kernels: block b runs on XCD b % 8 and takes work items
-// from a contiguous range owned by its XCD, striding over it with the other
-// blocks of that XCD.
-__device__ __forceinline__ void xcd_items(int64_t items, int64_t* first, int64_t* end, int64_t* step) {
-  const int64_t nb = gridDim.x, b = blockIdx.x;
-  const int64_t x = b % kXcds, k = b / kXcds;
-  const int64_t per = nb / kXcds, rem = nb % kXcds;
-  const int64_t before = x * per + (x < rem ? x : rem);
-  const int64_t mine = per + (x < rem ? 1 : 0);
-  const int64_t lo = items * before / nb;
-  const int64_t hi = items * (before + mine) / nb;
-  *first = lo + k;
-  *end = hi;
-  *step = mine;
-}
-
-// Per-thread register shapes of the tile kernels (NT threads per block, at
-// most 256 points and kMaxTileEntries entries and runs per tile).
-constexpr int kMaxTileEntries = 4096;
-constexpr int kSplatBlock = 512;   // two blocks per CU
-// The slice adds a point's entries by blocks of this many runs of its tile's
-// run list; every staged chunk (at most 16 channels) holds a whole number of
-// such blocks (RC = 8 NT / G >= 512).
-constexpr int kSliceOrderRows = 512;
-// Threads per block of k_slice_tile: 1024 (one block per CU), or for narrow
-// channel chunks just the lane groups for the 256 points of a tile (LPR =
-// G / VW lanes each), so that the lanes are not left idle. The narrow block
-// also stages fewer lattice rows per pass (RC = 8 NT / G), so it is taken
-// only where a tile's runs mostly fit in one pass.
-template <int G>
-constexpr int slice_threads_narrow() { return G >= 16 ? 1024 : G == 8 ? 512 : 256; }
-template <typename TU, int G, int NT_>
-struct TileShape {
-  static constexpr int NT = NT_;
-  static constexpr int kPts = 256;
-  static constexpr int EPT = kMaxTileEntries / NT;  // entries per thread
-  static constexpr int RPT = 2;                      // runs prefetched per thread (splat)
-  static constexpr int VPT = (kPts * G) / NT > 0 ? (kPts * G) / NT : 1;  // point values
-  static constexpr int VW = G < 4 ? G : 4;  // channels per lane
-  static constexpr int LPR = G / VW;        // lanes per run (splat) or point (slice)
-  static constexpr int NG = NT / LPR;
-  static constexpr int UPT = 8;             // lattice rows staged per thread in the slice
-  static constexpr int RC = UPT * NT / G;   // lattice rows per slice chunk
-  static constexpr int PPG = (kPts + NG - 1) / NG;  // points per lane group in the slice
-  // LDS row stride in elements: rows of 64 bytes or more get 16 bytes of
-  // padding, so lane groups reading different rows spread over the banks
-  static constexpr int RS = G * (int)sizeof(TU) >= 64 ? G + 16 / (int)sizeof(TU) : G;
-  // point values can be staged as whole 16-byte vectors per thread
-  static constexpr bool VEC = VPT >= Vec16<TU>::N && VPT % Vec16<TU>::N == 0;
-};
-
-// LDS layout of k_splat_tile: values [P+1][G] (TU; row P stays zero) | weights [P*D] (fp32) |
-// partial rows [maxq] (int32) | run starts [maxq+1] (uint16) | entry points
-// [P*D] (uint8) | next unclaimed run (int32).
-struct SplatLds {
-  size_t w, dst, rel, lp, next, total;
-};
-template <typename TU>
-__host__ __device__ inline SplatLds splat_lds(int P, int D, int maxq, int G) {
-  SplatLds o;
-  const int rs = G * (int)sizeof(TU) >= 64 ? G + 16 / (int)sizeof(TU) : G;
-  size_t b = sizeof(TU) * (size_t)(P + 1) * rs;
-  o.w = b;
-  b += sizeof(float) * (size_t)P * D;
-  o.dst = b;
-  b += sizeof(int32_t) * (size_t)maxq;
-  o.rel = b;
-  b += sizeof(uint16_t) * (size_t)(maxq + 1);
-  b = (b + 3) & ~(size_t)3;
-  o.lp = b;
-  b += ((size_t)P * D + 3) & ~(size_t)3;
-  o.next = b;
-  b += sizeof(int);
-  o.total = (b + 15) & ~(size_t)15;
-  return o;
-}
 
 // Scalars of k_splat_tile; its arrays are separate non-aliasing kernel
 // arguments, so uniform loads (tile offsets) go through the scalar cache
@@ -230,12 +56,9 @@ struct SplatArgs {
 };
 
 // W^T restricted to one tile (Section 3.2, Splat). The block stages the
-// tile's values, entries and run lists in LDS from registers that were
-// loaded while the previous tile was being reduced. Each run (one lattice
-// point of the tile) is summed by LPR lanes of VW channels, entries in
-// order; a lane group that finishes a run claims the next unclaimed one, so
-// runs of different lengths balance over the groups. The sum lands in the
-// lattice point's block of partial rows (run_dst).
+// tile's values, entries and pieces in LDS from registers that were loaded
+// while the previous tile was being reduced, and splat_pieces sums every
+// piece into its partial row (run_dst).
 //
 // Inside CG (up.p set, fp64) the values are the direction p in internal
 // order, and the block applies the previous iteration's direction update to
@@ -250,7 +73,7 @@ struct SplatArgs {
 // from the staged values.
 template <typename TU, int G, bool DIR>
 __global__ __launch_bounds__(kSplatBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_splat_tile(
-    const int32_t* __restrict__ tile_off, const uint16_t* __restrict__ run_rel,
+    const int32_t* __restrict__ tile_off, const uint32_t* __restrict__ piece,
     const int32_t* __restrict__ run_dst, const uint8_t* __restrict__ ent_lp,
     const float* __restrict__ ent_w, const TU* __restrict__ V, const uint32_t* __restrict__ perm,
     TU* __restrict__ part, double* __restrict__ pp, SplatArgs<TU> a, CgDirUpdate up) {
@@ -263,7 +86,7 @@ __global__ __launch_bounds__(kSplatBlock) __attribute__((amdgpu_waves_per_eu(4))
   TU* lv = (TU*)smem;
   float* lw = (float*)(smem + a.lds.w);
   int32_t* ldst = (int32_t*)(smem + a.lds.dst);
-  uint16_t* lrel = (uint16_t*)(smem + a.lds.rel);
+  uint32_t* lpc = (uint32_t*)(smem + a.lds.pc);
   uint8_t* llp = smem + a.lds.lp;
   int* lnext = (int*)(smem + a.lds.next);
   const int tid = threadIdx.x;
@@ -272,7 +95,7 @@ __global__ __launch_bounds__(kSplatBlock) __attribute__((amdgpu_waves_per_eu(4))
   TU v[S::VPT];
   float w[S::EPT];
   uint32_t lp4[S::EPT / 4];  // entry points, four per register
-  uint16_t rel[S::RPT];
+  uint32_t pc[S::RPT];
   int32_t dst[S::RPT];
   int nq = 0, ne = 0, q0 = 0;
   // Every load below is unconditional (indices clamped into the tile), so
@@ -339,11 +162,21 @@ __global__ __launch_bounds__(kSplatBlock) __attribute__((amdgpu_waves_per_eu(4))
 #pragma unroll
     for (int u = 0; u < S::RPT; ++u) {
       const int q = tid + u * kSplatBlock;
-      rel[u] = run_rel[q0 + (q < nq ? q : nq - 1)];
+      pc[u] = piece[q0 + (q < nq ? q : nq - 1)];
       dst[u] = run_dst[q0 + (q < nq ? q : nq - 1)];
     }
   };
 
+  __shared__ double sh_pp[sizeof(TU) == 8 ? 16 * G : 1];
+  int64_t pp_item = -1;  // the item whose block sums sh_pp holds
+  auto finish_pp = [&]() {
+    if (pp_item < 0 || tid >= G) return;
+    const int c = (int)(pp_item % a.chunks) * G + tid;
+    double tot = 0.0;
+#pragma unroll
+    for (int b = 0; b < 16; ++b) tot += sh_pp[b * G + tid];
+    if (c < a.C) pp[pp_item / a.chunks * a.C + c] = a.pp_scale * tot;
+  };
   int64_t item, end, step;
   xcd_items(a.items, &item, &end, &step);
   for (int i = tid; i < S::RS; i += kSplatBlock) lv[a.P * S::RS + i] = (TU)0;  // the zero row
@@ -357,7 +190,10 @@ __global__ __launch_bounds__(kSplatBlock) __attribute__((amdgpu_waves_per_eu(4))
   if (item < end) fetch(item);
   for (; item < end; item += step) {
     const int cur_nq = nq, cur_ne = ne, cur_q0 = q0;
-    __syncthreads();  // the previous tile's runs are done with the LDS
+    __syncthreads();  // the previous tile's pieces are done with the LDS
+    if constexpr (sizeof(TU) == 8) {
+      if (pp) finish_pp();
+    }
     if (S::VEC && (DIR || a.vec_v || a.vec_perm)) {
       const int64_t p0 = (item / a.chunks) * a.P;
 #pragma unroll
@@ -431,106 +267,38 @@ __global__ __launch_bounds__(kSplatBlock) __attribute__((amdgpu_waves_per_eu(4))
     for (int u = 0; u < S::RPT; ++u) {
       const int q = tid + u * kSplatBlock;
       if (q < cur_nq) {
-        lrel[q] = rel[u];
+        lpc[q] = pc[u];
         ldst[q] = dst[u];
       }
     }
-    // runs past the prefetched ones (tiles with very many distinct points)
+    // pieces past the prefetched ones (tiles with very many distinct points)
     for (int q = S::RPT * kSplatBlock + tid; q < cur_nq; q += kSplatBlock) {
-      lrel[q] = run_rel[cur_q0 + q];
+      lpc[q] = piece[cur_q0 + q];
       ldst[q] = run_dst[cur_q0 + q];
     }
-    if (tid == 0) {
-      lrel[cur_nq] = (uint16_t)cur_ne;
-      *lnext = S::NG;  // runs 0 .. NG-1 start on their own group
-    }
+    if (tid == 0) *lnext = S::NG;  // pieces 0 .. NG-1 start on their own group
     __syncthreads();
     if (item + step < end) fetch(item + step);  // in flight while this tile is reduced
 
     if constexpr (sizeof(TU) == 8) {
       if (pp) {
         // CG: the tile's p . p per column from the staged values, its points
-        // in 16 blocks of 16, each block and then the blocks added in index
-        // order, so that the sum does not depend on the channel chunk; the
-        // 16 lanes of a column are consecutive (one wave)
-        const int64_t tt = item / a.chunks;
-        const int cc0 = (int)(item % a.chunks) * G;
+        // in 16 blocks of 16 added in index order, so that the sum does not
+        // depend on the channel chunk. Consecutive lanes take consecutive
+        // columns of one block (a column's blocks are 16 padded rows apart,
+        // the same LDS bank); finish_pp adds the blocks after the next barrier.
         const int np = cur_ne / a.D;
-        for (int pr = tid; pr < 16 * G; pr += kSplatBlock) {
-          const int c = pr / 16, blk = pr % 16;
-          double v = 0.0;
-#pragma unroll
-          for (int u = 0; u < 16; ++u) {
-            const int q = blk * 16 + u;
-            const double x = q < np ? (double)lv[q * S::RS + c] : 0.0;
-            v = __builtin_fma(x, x, v);
-          }
-          double tot = 0.0;
-          const int l0 = (tid & 63) & ~15;
-#pragma unroll
-          for (int b = 0; b < 16; ++b) tot += __shfl(v, l0 + b);
-          if (blk == 0 && cc0 + c < a.C) pp[tt * a.C + cc0 + c] = a.pp_scale * tot;
-        }
+        if (tid < 16 * G) sh_pp[tid] = block_sumsq<S::RS>(lv, tid / G, tid % G, np);
+        pp_item = item;
       }
     }
 
-    const int ch = (int)(item % a.chunks);
-    const int grp = tid / S::LPR;
-    const int cg = ch * G + (tid % S::LPR) * S::VW;
-    const bool full = cg + S::VW <= a.C;
-    int q = grp;
-    if (q < cur_nq && cg < a.C) {
-      int e = lrel[q], e1 = lrel[q + 1];
-      int dq = ldst[q];
-      TU acc[S::VW];
-#pragma unroll
-      for (int i = 0; i < S::VW; ++i) acc[i] = 0;
-      for (;;) {
-        // up to four entries of the run per pass, added in entry order
-        // (a pass with fewer than four left reads the zero row with weight
-        // 0 for the rest: fma(0, 0, acc) is acc exactly, as acc is never -0)
-        const int cnt = e1 - e < 4 ? e1 - e : 4;
-        int lpu[4];
-        TU wu[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int eu = e + (u < cnt ? u : cnt - 1);
-          const int lpv = (int)llp[eu];
-          const float wv = lw[eu];
-          lpu[u] = u < cnt ? lpv : a.P;
-          wu[u] = (TU)(u < cnt ? wv : 0.f);
-        }
-        TU x[4][S::VW];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) read_row<TU, S::VW>(lv + lpu[u] * S::RS + (cg - ch * G), x[u]);
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-          for (int i = 0; i < S::VW; ++i) acc[i] = fma_t(wu[u], x[u][i], acc[i]);
-        e += cnt - 1;
-        if (++e == e1) {
-          TU* o = part + (int64_t)dq * a.C + cg;
-          if (full && a.cvec) {
-            write_row<TU, S::VW>(o, acc);
-          } else {
-#pragma unroll
-            for (int i = 0; i < S::VW; ++i)
-              if (cg + i < a.C) o[i] = acc[i];
-          }
-          // next run: whichever is unclaimed (one group's lanes share it);
-          // a run's sum does not depend on which group takes it
-          int nx = 0;
-          if (tid % S::LPR == 0) nx = atomicAdd(lnext, 1);
-          q = __shfl(nx, tid - tid % S::LPR);
-          if (q >= cur_nq) break;
-          e = lrel[q];
-          e1 = lrel[q + 1];
-          dq = ldst[q];
-#pragma unroll
-          for (int i = 0; i < S::VW; ++i) acc[i] = 0;
-        }
-      }
-    }
+    splat_pieces<TU, S>(lv, a.P, lw, llp, lpc, ldst, lnext, cur_nq, part, a.C,
+                        (int)(item % a.chunks) * G, a.cvec != 0);
+  }
+  if constexpr (sizeof(TU) == 8) {
+    __syncthreads();
+    if (pp) finish_pp();
   }
 }
 
@@ -1410,12 +1178,12 @@ int mvm_g(const sgp_lattice* L, const TU* V, const uint32_t* perm, int C, TU* ou
     const unsigned grid = persistent_grid(kern, kSplatBlock, sa.lds.total, sa.items, lc.splat_bpc);
     if (dir_fused)
       hipLaunchKernelGGL((k_splat_tile<TU, G, true>), dim3(grid), dim3(kSplatBlock), sa.lds.total, s,
-                         (const int32_t*)L->stile_off.ptr, (const uint16_t*)L->run_rel.ptr,
+                         (const int32_t*)L->stile_off.ptr, (const uint32_t*)L->piece.ptr,
                          (const int32_t*)L->run_dst.ptr, (const uint8_t*)L->ent_lp.ptr,
                          (const float*)L->ent_w.ptr, V, perm, part, pp, sa, *up);
     else
       hipLaunchKernelGGL((k_splat_tile<TU, G, false>), dim3(grid), dim3(kSplatBlock), sa.lds.total, s,
-                         (const int32_t*)L->stile_off.ptr, (const uint16_t*)L->run_rel.ptr,
+                         (const int32_t*)L->stile_off.ptr, (const uint32_t*)L->piece.ptr,
                          (const int32_t*)L->run_dst.ptr, (const uint8_t*)L->ent_lp.ptr,
                          (const float*)L->ent_w.ptr, V, perm, part, pp, sa, CgDirUpdate{});
     SGP_LAUNCH_CHECK("k_splat_tile");

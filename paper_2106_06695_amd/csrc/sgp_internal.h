@@ -170,7 +170,8 @@ struct sgp_lattice {
   sgp::DevBuf tile_off;   // ntiles+1 int32: first run of each tile
   sgp::DevBuf tile_verts; // nrun int32: internal lattice point of each run (ascending per tile)
   sgp::DevBuf stile_off;  // ntiles+1 int32: first piece of each tile
-  sgp::DevBuf run_rel;    // npiece uint16: first entry of each piece, relative to its tile's entries
+  sgp::DevBuf piece;      // npiece uint32: first entry of each piece, relative to its tile's entries,
+                          //   and its length << 16; a tile's pieces are stored longest first
   sgp::DevBuf ent_lp;     // n(d+1) uint8: point within its tile, entries grouped by run
   sgp::DevBuf ent_w;      // n(d+1) fp32: weight of each entry, grouped by run
   sgp::DevBuf occ_ptr;    // m+1 int32: first partial row of each lattice point
