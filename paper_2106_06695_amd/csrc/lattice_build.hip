@@ -624,8 +624,9 @@ __device__ inline void tile_radix(unsigned long long* key, int32_t* hist, int32_
 // their ranks within the tile. key[] holds the tile's sorted keys.
 struct TileRanks {
   int q[kTileSpan];   // run of each position
-  int qp[kTileSpan];  // piece of each position, where it starts one (else -1)
-  bool rs[kTileSpan];
+  int qp[kTileSpan];  // piece of each position
+  bool rs[kTileSpan];  // the position starts a run
+  bool ps[kTileSpan];  // the position starts a piece
   int runs, pieces;
 };
 __device__ inline void tile_ranks(TileSort& T, int ne, int K, TileRanks& r) {
@@ -645,19 +646,18 @@ __device__ inline void tile_ranks(TileSort& T, int ne, int K, TileRanks& r) {
     if (r.rs[u]) T.rstart[q] = i0 + u;
   }
   __syncthreads();
-  bool ps[kTileSpan];
   c = 0;
 #pragma unroll
   for (int u = 0; u < kTileSpan; ++u) {
     const int i = i0 + u;
-    ps[u] = i < ne && (i - T.rstart[r.q[u]]) % K == 0;
-    c += ps[u] ? 1 : 0;
+    r.ps[u] = i < ne && (i - T.rstart[r.q[u]]) % K == 0;
+    c += r.ps[u] ? 1 : 0;
   }
-  int qp = tile_scan(c, T.wsum, &r.pieces);
+  int qp = tile_scan(c, T.wsum, &r.pieces) - 1;
 #pragma unroll
   for (int u = 0; u < kTileSpan; ++u) {
-    r.qp[u] = ps[u] ? qp : -1;
-    qp += ps[u] ? 1 : 0;
+    qp += r.ps[u] ? 1 : 0;
+    r.qp[u] = qp;
   }
 }
 
@@ -758,21 +758,29 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
 }
 
 // Pass 2, with each tile's first run and piece known: the slice's runs
-// (lattice point per run, run slot per entry in point order), the splat's
-// entries in run order (point within the tile, weight) and its pieces
-// (first entry relative to the tile and length; lattice point). Pieces are
-// stored longest first (a stable counting sort by length: the pieces of one
-// lattice point keep their order, as only the last is short), so that the
-// splat's waves take pieces of about equal length.
-// Counters of that sort: (K - length, round, wave).
+// (lattice point per run, run slot per entry in point order) and the splat's
+// pieces (lattice point) and entries (point within the tile, weight).
+// Pieces are stored longest first (a stable counting sort by length: the
+// pieces of one lattice point keep their order, as only the last is short)
+// and cut into slices of kSlicePieces. A slice's entries are interleaved,
+// entry k of its pieces side by side, padded to its longest piece (to a
+// multiple of 4 for pieces of more than kShortPiece entries) with entries
+// whose weight is the bit pattern kPadWeight: a wave of the splat reads a
+// slice with one address and no per-entry tests. Sorted pieces leave few
+// pads: at most 16 * 32 a tile, and 3 * 16 a long slice.
+// Counters of the sort: (K - length, round, wave).
 constexpr int kPieceCounters = kPiece * kTileSpan * (kTileThreads / 64);
 static_assert(kPieceCounters == 2 * kTileThreads && kPiece < 64, "two piece counters per thread");
 __device__ __forceinline__ int piece_counter(int digit, int round) {
   return (digit * kTileSpan + round) * (kTileThreads / 64) + (int)(threadIdx.x >> 6);
 }
-__global__ __launch_bounds__(kTileThreads) void k_tile_fill(const sgp_entry* __restrict__ pm,
+constexpr int kMaxSlices = kTileSlots / kSlicePieces;
+static_assert(kMaxSlices <= kTileThreads, "a slice per thread");
+static_assert(tile_ent_stride(kTileSlots) * 5 <= kTileSlots * 8, "a tile's padded entries fit the key array");
+
+__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8))) void k_tile_fill(const sgp_entry* __restrict__ pm,
                                                             const uint16_t* __restrict__ ord, int64_t n,
-                                                            int D, int P, int K,
+                                                            int D, int P, int K, int estride,
                                                             const int32_t* __restrict__ tile_off,
                                                             const int32_t* __restrict__ stile_off,
                                                             int32_t* __restrict__ tile_verts,
@@ -780,10 +788,14 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_fill(const sgp_entry* __r
                                                             float* __restrict__ ws,
                                                             uint8_t* __restrict__ ent_lp,
                                                             float* __restrict__ ent_w,
-                                                            uint32_t* __restrict__ piece,
-                                                            int32_t* __restrict__ piece_vert) {
+                                                            uint32_t* __restrict__ slice,
+                                                            int32_t* __restrict__ tile_ent,
+                                                            int32_t* __restrict__ piece_vert,
+                                                            uint32_t* __restrict__ max_ent) {
   __shared__ TileSort T;
   __shared__ int32_t cnt[kPieceCounters];
+  __shared__ uint16_t prank[kTileSlots];
+  __shared__ int32_t soff[kMaxSlices];
   const int64_t t = blockIdx.x;
   const int64_t p0 = t * P;
   const int ne = (int)((n - p0 < P ? n - p0 : P) * D);
@@ -801,23 +813,24 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_fill(const sgp_entry* __r
   tile_ranks(T, ne, K, r);
   const int64_t q0 = tile_off[t], qp0 = stile_off[t];
   const int i0 = threadIdx.x * kTileSpan;
+  float w[kTileSpan];
+  uint8_t lp[kTileSpan];
 #pragma unroll
   for (int u = 0; u < kTileSpan; ++u) {
     const int i = i0 + u;
     if (i >= ne) break;
     const unsigned long long k = T.key[tile_at(i)];
-    const int32_t j = (int32_t)(k >> 12);
     const unsigned le = (unsigned)(k & 4095u);
-    ent_lp[base + i] = (uint8_t)(le / (unsigned)D);
-    ent_w[base + i] = pm[base + le].w;
+    lp[u] = (uint8_t)(le / (unsigned)D);
+    w[u] = pm[base + le].w;
     loc[base + le] = (uint16_t)r.q[u];
-    if (r.rs[u]) tile_verts[q0 + r.q[u]] = j;
+    if (r.rs[u]) tile_verts[q0 + r.q[u]] = (int32_t)(k >> 12);
   }
   // pieces, longest first
   for (int c = threadIdx.x; c < kPieceCounters; c += kTileThreads) cnt[c] = 0;
 #pragma unroll
   for (int u = 0; u < kTileSpan; ++u)
-    if (r.qp[u] >= 0) T.rstart[r.qp[u]] = i0 + u;  // the run starts are no longer read
+    if (r.ps[u]) T.rstart[r.qp[u]] = i0 + u;  // the run starts are no longer read
   __syncthreads();
   int start[kTileSpan], len[kTileSpan], rk[kTileSpan];
 #pragma unroll
@@ -852,10 +865,46 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_fill(const sgp_entry* __r
 #pragma unroll
   for (int u = 0; u < kTileSpan; ++u) {
     if (len[u] == 0) continue;
-    const int64_t o = qp0 + cnt[piece_counter(K - len[u], u)] + rk[u];
-    piece[o] = (uint32_t)start[u] | (uint32_t)len[u] << 16;
-    piece_vert[o] = (int32_t)(T.key[tile_at(start[u])] >> 12);
+    const int o = cnt[piece_counter(K - len[u], u)] + rk[u];
+    prank[threadIdx.x + u * kTileThreads] = (uint16_t)o;
+    piece_vert[qp0 + o] = (int32_t)(T.key[tile_at(start[u])] >> 12);
+    if (o % kSlicePieces == 0) soff[o / kSlicePieces] = len[u] > kShortPiece ? (len[u] + 3) & ~3 : len[u];
   }
+  __syncthreads();
+  // slices: depth, first entry
+  const int nsl = (r.pieces + kSlicePieces - 1) / kSlicePieces;
+  const int depth = (int)threadIdx.x < nsl ? soff[threadIdx.x] : 0;
+  int total;
+  const int off = tile_scan(depth * kSlicePieces, T.wsum, &total);  // every depth has been read
+  if ((int)threadIdx.x < nsl) {
+    soff[threadIdx.x] = off;
+    slice[tile_slice0(qp0, t) + threadIdx.x] = (uint32_t)off | (uint32_t)depth << 16;
+  }
+  if (threadIdx.x == 0) {
+    tile_ent[t] = total;
+    atomicMax(max_ent, (uint32_t)total);
+  }
+  // the padded entries, put together in the key array
+  float* ew = (float*)T.key;
+  uint8_t* el = (uint8_t*)(ew + tile_ent_stride(kTileSlots));
+  for (int e = threadIdx.x; e < total; e += kTileThreads) {
+    ((uint32_t*)ew)[e] = kPadWeight;
+    el[e] = 0;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kTileSpan; ++u) {
+    const int i = i0 + u;
+    if (i >= ne) break;
+    const int o = prank[r.qp[u]];
+    const int e = soff[o / kSlicePieces] + (i - T.rstart[r.qp[u]]) * kSlicePieces + o % kSlicePieces;
+    ew[e] = w[u];
+    el[e] = lp[u];
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < total; e += kTileThreads) ent_w[t * estride + e] = ew[e];
+  for (int e = threadIdx.x; e < total / 4; e += kTileThreads)
+    ((uint32_t*)(ent_lp + t * estride))[e] = ((const uint32_t*)el)[e];
 }
 
 // Hashing and first occurrences, one group of kInsEntries / (d+1)
@@ -1134,7 +1183,7 @@ int build_attempt(sgp_lattice* L, const float* X, const double* f, double load_f
   uint32_t* tab_first = (uint32_t*)tr.ptr[T_FIRST];
   uint32_t* counts = (uint32_t*)tr.ptr[T_COUNTS];
   uint32_t* offs = (uint32_t*)tr.ptr[T_OFFS];
-  uint32_t* words = (uint32_t*)tr.ptr[T_WORDS];  // [0] flags, [1] m, [2] m again, [4..] min/max
+  uint32_t* words = (uint32_t*)tr.ptr[T_WORDS];  // [0] flags, [1] m, [2] m again, [3] longest padded entry list, [4..] min/max
   float* w_orig = (float*)tr.ptr[T_W];
   int32_t* rmin = (int32_t*)(words + 4);
   int32_t* rmax = rmin + kMaxD;
@@ -1217,7 +1266,7 @@ int build_attempt(sgp_lattice* L, const float* X, const double* f, double load_f
   uint32_t* va = (uint32_t*)tr.ptr[T_VA];
   uint32_t* vb = (uint32_t*)tr.ptr[T_VB];
   uint32_t* sort_tmp = (uint32_t*)tr.ptr[T_SORTTMP];
-  for (sgp::DevBuf* b : {&L->perm, &L->loc, &L->ws, &L->tile_off, &L->tile_verts, &L->piece,
+  for (sgp::DevBuf* b : {&L->perm, &L->loc, &L->ws, &L->tile_off, &L->tile_verts, &L->slice, &L->tile_ent,
                          &L->ent_lp, &L->ent_w, &L->occ_ptr, &L->run_dst, &L->row_vert, &L->stile_off, &L->nbr, &L->int2can})
     dev_free(*b);
   if ((rc = dev_alloc(L->perm, sizeof(uint32_t) * n, st))) return rc;
@@ -1413,10 +1462,11 @@ int build_attempt(sgp_lattice* L, const float* X, const double* f, double load_f
     L->max_tile_runs = mx;
     L->max_tile_pieces = msx;
     if ((rc = dev_alloc(L->tile_verts, sizeof(int32_t) * Q, st))) return rc;
-    // four spare bytes: the splat reads entry points four at a time
-    if ((rc = dev_alloc(L->ent_lp, sizeof(uint8_t) * (Lel + 4), st))) return rc;
-    if ((rc = dev_alloc(L->ent_w, sizeof(float) * Lel, st))) return rc;
-    if ((rc = dev_alloc(L->piece, sizeof(uint32_t) * Qs, st))) return rc;
+    const int estride = tile_ent_stride(P * D);
+    if ((rc = dev_alloc(L->ent_lp, sizeof(uint8_t) * ntiles * estride, st))) return rc;
+    if ((rc = dev_alloc(L->ent_w, sizeof(float) * ntiles * estride, st))) return rc;
+    if ((rc = dev_alloc(L->slice, sizeof(uint32_t) * tile_slice0(Qs, ntiles), st))) return rc;
+    if ((rc = dev_alloc(L->tile_ent, sizeof(int32_t) * ntiles, st))) return rc;
     if ((rc = dev_alloc(L->occ_ptr, sizeof(int32_t) * (m + 1), st))) return rc;
     if ((rc = dev_alloc(L->run_dst, sizeof(int32_t) * Qs, st))) return rc;
     if ((rc = dev_alloc(L->row_vert, sizeof(int32_t) * Qs, st))) return rc;
@@ -1425,10 +1475,11 @@ int build_attempt(sgp_lattice* L, const float* X, const double* f, double load_f
     {
       ProfScope ps(KK_ORDER, st);
       hipLaunchKernelGGL(k_tile_fill, dim3((unsigned)ntiles), dim3(kTileThreads), 0, st,
-                         (const sgp_entry*)tr.ptr[T_PM], (const uint16_t*)ord, n, D, P, kPiece,
+                         (const sgp_entry*)tr.ptr[T_PM], (const uint16_t*)ord, n, D, P, kPiece, estride,
                          (const int32_t*)tile_off, (const int32_t*)stile_off, (int32_t*)L->tile_verts.ptr,
                          (uint16_t*)L->loc.ptr, (float*)L->ws.ptr, (uint8_t*)L->ent_lp.ptr,
-                         (float*)L->ent_w.ptr, (uint32_t*)L->piece.ptr, (int32_t*)sub);
+                         (float*)L->ent_w.ptr, (uint32_t*)L->slice.ptr, (int32_t*)L->tile_ent.ptr, (int32_t*)sub,
+                         words + 3);
       SGP_LAUNCH_CHECK("k_tile_fill");
     }
     // pieces grouped by lattice point (32-bit keys; reuses the sort buffers)
@@ -1450,9 +1501,10 @@ int build_attempt(sgp_lattice* L, const float* X, const double* f, double load_f
       SGP_LAUNCH_CHECK("k_occ_fill");
     }
   }
-  SGP_HIP(hipMemcpyAsync(host_word, words, sizeof(uint32_t) * 3, hipMemcpyDeviceToHost, st));
+  SGP_HIP(hipMemcpyAsync(host_word, words, sizeof(uint32_t) * 4, hipMemcpyDeviceToHost, st));
   SGP_HIP(hipStreamSynchronize(st));
   tr.idle = true;  // every kernel of this attempt has finished
+  L->max_tile_ents = (int)host_word[3];
   if (host_word[0] & BF_ORDER) {
     set_error("lattice_build: internal error, a tile's sorted order is not a permutation");
     return SGP_EHASH;

@@ -52,7 +52,8 @@ struct SplatArgs {
   int vec_perm;  // V rows, reached through perm, are whole 16-byte vectors (C == G)
   int cvec;   // rows of C channels start 16-byte aligned
   double pp_scale;  // CG: factor of each tile's p . p (the noise variance)
-  SplatLds lds;
+  int estride;  // entries between tiles' lists
+  SplatLists lds;  // after the values [P+1][G] (TU; row P stays zero)
 };
 
 // W^T restricted to one tile (Section 3.2, Splat). The block stages the
@@ -73,7 +74,8 @@ struct SplatArgs {
 // from the staged values.
 template <typename TU, int G, bool DIR>
 __global__ __launch_bounds__(kSplatBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_splat_tile(
-    const int32_t* __restrict__ tile_off, const uint32_t* __restrict__ piece,
+    const int32_t* __restrict__ tile_off, const int32_t* __restrict__ tile_ent,
+    const uint32_t* __restrict__ slice,
     const int32_t* __restrict__ run_dst, const uint8_t* __restrict__ ent_lp,
     const float* __restrict__ ent_w, const TU* __restrict__ V, const uint32_t* __restrict__ perm,
     TU* __restrict__ part, double* __restrict__ pp, SplatArgs<TU> a, CgDirUpdate up) {
@@ -84,30 +86,21 @@ __global__ __launch_bounds__(kSplatBlock) __attribute__((amdgpu_waves_per_eu(4))
   __shared__ int s_active[DIR ? kMaxCgCols : 1];
   constexpr bool upd = DIR && sizeof(TU) == 8 && S::VEC;
   TU* lv = (TU*)smem;
-  float* lw = (float*)(smem + a.lds.w);
-  int32_t* ldst = (int32_t*)(smem + a.lds.dst);
-  uint32_t* lpc = (uint32_t*)(smem + a.lds.pc);
-  uint8_t* llp = smem + a.lds.lp;
-  int* lnext = (int*)(smem + a.lds.next);
   const int tid = threadIdx.x;
   constexpr int N = Vec16<TU>::N;
 
   TU v[S::VPT];
-  float w[S::EPT];
-  uint32_t lp4[S::EPT / 4];  // entry points, four per register
-  uint32_t pc[S::RPT];
-  int32_t dst[S::RPT];
-  int nq = 0, ne = 0, q0 = 0;
+  SplatFetch<kSplatBlock> lists;
+  int nq = 0, ne = 0, np = 0, q0 = 0;
   // Every load below is unconditional (indices clamped into the tile), so
-  // the whole tile is in flight at once. The tile's values and entries are
-  // read once per MVM: non-temporal, so that they do not push the partial
-  // rows, which the gather reads next, out of the caches.
+  // the whole tile is in flight at once. The values are read once per MVM:
+  // non-temporal, as the lists (SplatFetch).
   auto fetch = [&](int64_t item) {
     const int64_t t = item / a.chunks;
     const int ch = (int)(item - t * a.chunks);
     const int64_t p0 = t * a.P;
-    const int np = (int)(a.n - p0 < a.P ? a.n - p0 : a.P);
-    ne = np * a.D;
+    np = (int)(a.n - p0 < a.P ? a.n - p0 : a.P);
+    ne = tile_ent[t];
     q0 = tile_off[t];
     nq = tile_off[t + 1] - q0;
     if (S::VEC && (DIR || a.vec_v)) {
@@ -144,27 +137,7 @@ __global__ __launch_bounds__(kSplatBlock) __attribute__((amdgpu_waves_per_eu(4))
         v[u] = V[src * a.C + (c < a.C ? c : a.C - 1)];
       }
     }
-    const float* gw = ent_w + p0 * a.D;
-#pragma unroll
-    for (int u = 0; u < S::EPT; ++u) {
-      const int e = tid + u * kSplatBlock;
-      w[u] = __builtin_nontemporal_load(gw + (e < ne ? e : ne - 1));
-    }
-    // the tile starts 4-byte aligned (P is a multiple of 4) and the array
-    // has spare bytes past its end
-    const uint32_t* glp4 = (const uint32_t*)(ent_lp + p0 * a.D);
-    const int nw = (ne + 3) / 4;
-#pragma unroll
-    for (int u = 0; u < S::EPT / 4; ++u) {
-      const int wi = tid + u * kSplatBlock;
-      lp4[u] = __builtin_nontemporal_load(glp4 + (wi < nw ? wi : nw - 1));
-    }
-#pragma unroll
-    for (int u = 0; u < S::RPT; ++u) {
-      const int q = tid + u * kSplatBlock;
-      pc[u] = piece[q0 + (q < nq ? q : nq - 1)];
-      dst[u] = run_dst[q0 + (q < nq ? q : nq - 1)];
-    }
+    lists.load(ent_w + t * a.estride, ent_lp + t * a.estride, run_dst + q0, slice + tile_slice0(q0, t), ne, nq);
   };
 
   __shared__ double sh_pp[sizeof(TU) == 8 ? 16 * G : 1];
@@ -189,7 +162,7 @@ __global__ __launch_bounds__(kSplatBlock) __attribute__((amdgpu_waves_per_eu(4))
   }
   if (item < end) fetch(item);
   for (; item < end; item += step) {
-    const int cur_nq = nq, cur_ne = ne, cur_q0 = q0;
+    const int cur_nq = nq, cur_ne = ne, cur_np = np, cur_q0 = q0;
     __syncthreads();  // the previous tile's pieces are done with the LDS
     if constexpr (sizeof(TU) == 8) {
       if (pp) finish_pp();
@@ -199,7 +172,7 @@ __global__ __launch_bounds__(kSplatBlock) __attribute__((amdgpu_waves_per_eu(4))
 #pragma unroll
       for (int u = 0; u < S::VPT / N; ++u) {
         const int vi = tid + u * kSplatBlock;
-        if (vi * N < cur_ne / a.D * G) {
+        if (vi * N < cur_np * G) {
           typename Vec16<TU>::T x;
           const int f = vi * N;  // N consecutive elements of one row
           if constexpr (upd) {
@@ -236,7 +209,7 @@ __global__ __launch_bounds__(kSplatBlock) __attribute__((amdgpu_waves_per_eu(4))
 #pragma unroll
       for (int u = 0; u < S::VPT; ++u) {
         const int f = tid + u * kSplatBlock;
-        if (f < cur_ne / a.D * G) {
+        if (f < cur_np * G) {
           TU x = v[u];
           if constexpr (DIR && sizeof(TU) == 8 && !S::VEC) {
             // the direction update element by element (C == G here)
@@ -253,30 +226,11 @@ __global__ __launch_bounds__(kSplatBlock) __attribute__((amdgpu_waves_per_eu(4))
         }
       }
     }
-#pragma unroll
-    for (int u = 0; u < S::EPT; ++u) {
-      const int e = tid + u * kSplatBlock;
-      if (e < cur_ne) lw[e] = w[u];
+    {
+      const int64_t t = item / a.chunks;
+      lists.stage(smem, a.lds, ent_w + t * a.estride, ent_lp + t * a.estride, run_dst + cur_q0,
+                  slice + tile_slice0(cur_q0, t), cur_ne, cur_nq, S::RS * (int)sizeof(TU), a.P);
     }
-#pragma unroll
-    for (int u = 0; u < S::EPT / 4; ++u) {
-      const int wi = tid + u * kSplatBlock;
-      if (4 * wi < cur_ne) ((uint32_t*)llp)[wi] = lp4[u];
-    }
-#pragma unroll
-    for (int u = 0; u < S::RPT; ++u) {
-      const int q = tid + u * kSplatBlock;
-      if (q < cur_nq) {
-        lpc[q] = pc[u];
-        ldst[q] = dst[u];
-      }
-    }
-    // pieces past the prefetched ones (tiles with very many distinct points)
-    for (int q = S::RPT * kSplatBlock + tid; q < cur_nq; q += kSplatBlock) {
-      lpc[q] = piece[cur_q0 + q];
-      ldst[q] = run_dst[cur_q0 + q];
-    }
-    if (tid == 0) *lnext = S::NG;  // pieces 0 .. NG-1 start on their own group
     __syncthreads();
     if (item + step < end) fetch(item + step);  // in flight while this tile is reduced
 
@@ -287,14 +241,13 @@ __global__ __launch_bounds__(kSplatBlock) __attribute__((amdgpu_waves_per_eu(4))
         // depend on the channel chunk. Consecutive lanes take consecutive
         // columns of one block (a column's blocks are 16 padded rows apart,
         // the same LDS bank); finish_pp adds the blocks after the next barrier.
-        const int np = cur_ne / a.D;
-        if (tid < 16 * G) sh_pp[tid] = block_sumsq<S::RS>(lv, tid / G, tid % G, np);
+        if (tid < 16 * G) sh_pp[tid] = block_sumsq<S::RS>(lv, tid / G, tid % G, cur_np);
         pp_item = item;
       }
     }
 
-    splat_pieces<TU, S>(lv, a.P, lw, llp, lpc, ldst, lnext, cur_nq, part, a.C,
-                        (int)(item % a.chunks) * G, a.cvec != 0);
+    splat_pieces<TU, G, kSplatBlock>(smem, smem, a.lds, cur_nq, part, a.C, (int)(item % a.chunks) * G,
+                                     a.cvec != 0);
   }
   if constexpr (sizeof(TU) == 8) {
     __syncthreads();
@@ -1131,6 +1084,13 @@ size_t mvm_work_elems(const sgp_lattice* L, int C, bool cg) {
   return (size_t)((cg ? 5 : 4) * L->m + L->npiece + 2 * gather_ranges(L)) * (size_t)C;
 }
 
+// LDS of k_splat_tile: values [P+1][G], then the entry lists.
+template <typename TU>
+SplatLists splat_lds(const sgp_lattice* L, int G) {
+  const int rs = G * (int)sizeof(TU) >= 64 ? G + 16 / (int)sizeof(TU) : G;
+  return splat_lists((int)sizeof(TU) * (L->tile_points + 1) * rs, L->max_tile_ents, L->max_tile_pieces);
+}
+
 // cgm (CG only, else null): V is the direction p, out the residual r (both
 // internal order), and the MVM finishes the CG step (CgMvm).
 template <typename TU, int G>
@@ -1160,7 +1120,8 @@ int mvm_g(const sgp_lattice* L, const TU* V, const uint32_t* perm, int C, TU* ou
   sa.vec_v = (TileShape<TU, G, kSplatBlock>::VEC && !perm && C == G && aligned16(V)) ? 1 : 0;
   sa.vec_perm = (TileShape<TU, G, kSplatBlock>::VEC && perm && C == G && aligned16(V)) ? 1 : 0;
   sa.cvec = (C % Vec16<TU>::N == 0 && aligned16(part)) ? 1 : 0;
-  sa.lds = splat_lds<TU>(P, D, L->max_tile_pieces, G);
+  sa.estride = tile_ent_stride(P * D);
+  sa.lds = splat_lds<TU>(L, G);
   sa.pp_scale = cgm ? (double)noise : 0.0;
   double* pp = cgm ? cgm->pp : nullptr;
   // the previous CG iteration's direction update: in this splat where its
@@ -1175,15 +1136,15 @@ int mvm_g(const sgp_lattice* L, const TU* V, const uint32_t* perm, int C, TU* ou
     ProfScope ps(KK_SPLAT, s);
     const void* kern =
         dir_fused ? (const void*)&k_splat_tile<TU, G, true> : (const void*)&k_splat_tile<TU, G, false>;
-    const unsigned grid = persistent_grid(kern, kSplatBlock, sa.lds.total, sa.items, lc.splat_bpc);
+    const unsigned grid = persistent_grid(kern, kSplatBlock, (size_t)sa.lds.end, sa.items, lc.splat_bpc);
     if (dir_fused)
-      hipLaunchKernelGGL((k_splat_tile<TU, G, true>), dim3(grid), dim3(kSplatBlock), sa.lds.total, s,
-                         (const int32_t*)L->stile_off.ptr, (const uint32_t*)L->piece.ptr,
+      hipLaunchKernelGGL((k_splat_tile<TU, G, true>), dim3(grid), dim3(kSplatBlock), (size_t)sa.lds.end, s,
+                         (const int32_t*)L->stile_off.ptr, (const int32_t*)L->tile_ent.ptr, (const uint32_t*)L->slice.ptr,
                          (const int32_t*)L->run_dst.ptr, (const uint8_t*)L->ent_lp.ptr,
                          (const float*)L->ent_w.ptr, V, perm, part, pp, sa, *up);
     else
-      hipLaunchKernelGGL((k_splat_tile<TU, G, false>), dim3(grid), dim3(kSplatBlock), sa.lds.total, s,
-                         (const int32_t*)L->stile_off.ptr, (const uint32_t*)L->piece.ptr,
+      hipLaunchKernelGGL((k_splat_tile<TU, G, false>), dim3(grid), dim3(kSplatBlock), (size_t)sa.lds.end, s,
+                         (const int32_t*)L->stile_off.ptr, (const int32_t*)L->tile_ent.ptr, (const uint32_t*)L->slice.ptr,
                          (const int32_t*)L->run_dst.ptr, (const uint8_t*)L->ent_lp.ptr,
                          (const float*)L->ent_w.ptr, V, perm, part, pp, sa, CgDirUpdate{});
     SGP_LAUNCH_CHECK("k_splat_tile");
@@ -1368,11 +1329,11 @@ constexpr int kMaxChunk = 16;
 int chunk_lanes(const sgp_lattice* L, int C, size_t elem) {
   int g = lanes_for(C);
   if (g > kMaxChunk) g = kMaxChunk;
-  const int D = L->d + 1, P = L->tile_points, maxq = L->max_tile_runs, maxp = L->max_tile_pieces;
+  const int D = L->d + 1, P = L->tile_points, maxq = L->max_tile_runs;
   const size_t budget = (size_t)tuning().lds_budget;
   const size_t slice_budget = (size_t)tuning().slice_lds_budget;
   while (g > 1) {
-    const size_t splat = elem == 8 ? splat_lds<double>(P, D, maxp, g).total : splat_lds<float>(P, D, maxp, g).total;
+    const size_t splat = elem == 8 ? splat_lds<double>(L, g).end : splat_lds<float>(L, g).end;
     const size_t slice = elem == 8 ? slice_lds_g<double>(P, D, maxq, g) : slice_lds_g<float>(P, D, maxq, g);
     if (splat <= budget && slice <= slice_budget) break;
     g >>= 1;

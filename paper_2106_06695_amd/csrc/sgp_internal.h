@@ -18,6 +18,24 @@ constexpr int kMaxCgCols = 64;  // columns per cg_solve call
 constexpr int kRedBlocks = 512; // blocks (and partial sums) of the reducing vector kernels
 constexpr int kPiece = 32;      // longest run piece the splat reduces in one go
 
+// The splat's entries: pieces in slices of kSlicePieces (see k_tile_fill).
+constexpr int kSlicePieces = 16;
+constexpr int kShortPiece = 8;  // slices of longer pieces are padded to a multiple of 4
+constexpr uint32_t kPadWeight = 0xffffffffu;  // weight bits of a padding entry (no weight is NaN)
+// Room for the padded entries of a tile of ne entries, a multiple of 4: pads
+// of sorted pieces telescope to 16 * 32 at most; a slice padded to a multiple
+// of 4 holds more than 16 * 8 entries, unless it is the last such.
+constexpr int tile_ent_stride(int ne) {
+  return (ne + kSlicePieces * kPiece + 3 * kSlicePieces * (ne / (kSlicePieces * (kShortPiece + 1)) + 1) + 3) & ~3;
+}
+// Place of a tile's first slice word: ceil(pieces / 16) words a tile fit.
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+constexpr int64_t tile_slice0(int64_t first_piece, int64_t tile) {
+  return first_piece / kSlicePieces + tile;
+}
+
 // Launch-shape knobs of the MVM kernels. Defaults are the measured best on
 // MI355X; SGP_LDS_BUDGET, SGP_SLICE_LDS_BUDGET, SGP_TILE_BLOCKS_PER_CU and
 // SGP_BLUR_SEQ_MIB in the environment override them (read once per process).
@@ -164,16 +182,18 @@ struct sgp_lattice {
   int max_tile_runs = 0;    // longest tile vertex list
   int64_t npiece = 0;       // runs cut into pieces of at most kPiece entries (splat)
   int max_tile_pieces = 0;  // longest tile piece list
+  int max_tile_ents = 0;    // longest tile entry list of the splat, pads included
   sgp::DevBuf perm;       // n uint32: sorted position -> caller's point index
   sgp::DevBuf loc;        // n(d+1) uint16: run of (sorted point, vertex) within its tile
   sgp::DevBuf ws;         // n(d+1) fp32: barycentric weight, sorted point order
   sgp::DevBuf tile_off;   // ntiles+1 int32: first run of each tile
   sgp::DevBuf tile_verts; // nrun int32: internal lattice point of each run (ascending per tile)
   sgp::DevBuf stile_off;  // ntiles+1 int32: first piece of each tile
-  sgp::DevBuf piece;      // npiece uint32: first entry of each piece, relative to its tile's entries,
-                          //   and its length << 16; a tile's pieces are stored longest first
-  sgp::DevBuf ent_lp;     // n(d+1) uint8: point within its tile, entries grouped by run
-  sgp::DevBuf ent_w;      // n(d+1) fp32: weight of each entry, grouped by run
+  sgp::DevBuf slice;      // per tile, from tile_slice0 on: a word per kSlicePieces pieces (stored longest
+                          //   first): first entry within the tile's, depth << 16
+  sgp::DevBuf tile_ent;   // ntiles int32: entries of each tile, pads included
+  sgp::DevBuf ent_lp;     // ntiles x tile_ent_stride uint8: point within the tile, interleaved by slice
+  sgp::DevBuf ent_w;      // ntiles x tile_ent_stride fp32: weight of each entry (kPadWeight bits: none)
   sgp::DevBuf occ_ptr;    // m+1 int32: first partial row of each lattice point
   sgp::DevBuf row_vert;   // npiece int32: lattice point of each partial row
   sgp::DevBuf run_dst;    // npiece int32: partial row of each piece; a lattice point's

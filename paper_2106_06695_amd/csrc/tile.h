@@ -156,107 +156,182 @@ struct TileShape {
   static constexpr bool VEC = VPT >= Vec16<TU>::N && VPT % Vec16<TU>::N == 0;
 };
 
-// LDS layout of k_splat_tile: values [P+1][G] (TU; row P stays zero) | weights [P*D] (fp32) |
-// partial rows [maxq] (int32) | pieces [maxq] (uint32) | entry points [P*D]
-// (uint8) | next unclaimed piece (int32).
-struct SplatLds {
-  size_t w, dst, pc, lp, next, total;
+// Lanes of the splat: SLPR lanes of SVW channels sum a piece, so a wave takes
+// whole slices of kSlicePieces pieces.
+template <int G>
+struct SplatLanes {
+  static constexpr int LPR = G < 4 ? G : 4;
+  static constexpr int VW = G / LPR;
+  static constexpr int GPW = 64 / LPR;             // pieces per wave
+  static constexpr int SPW = GPW / kSlicePieces;   // slices per wave
 };
-template <typename TU>
-__host__ __device__ inline SplatLds splat_lds(int P, int D, int maxq, int G) {
-  SplatLds o;
-  const int rs = G * (int)sizeof(TU) >= 64 ? G + 16 / (int)sizeof(TU) : G;
-  size_t b = sizeof(TU) * (size_t)(P + 1) * rs;
+
+// The splat's entry lists of a tile in LDS, at byte offsets: weights [maxe]
+// (fp32) | row offsets [maxe] (uint16) | partial rows [maxq] (int32) | slices
+// [maxq / 16 + 1] (uint32) | next unclaimed batch, then a spare word (int32).
+struct SplatLists {
+  int w, off, dst, sl, next, end;
+};
+__host__ __device__ inline SplatLists splat_lists(int base, int maxe, int maxq) {
+  SplatLists o;
+  int b = (base + 15) & ~15;
   o.w = b;
-  b += sizeof(float) * (size_t)P * D;
+  b += 4 * maxe;
+  o.off = b;
+  b += (2 * maxe + 15) & ~15;
   o.dst = b;
-  b += sizeof(int32_t) * (size_t)maxq;
-  o.pc = b;
-  b += sizeof(uint32_t) * (size_t)maxq;
-  o.lp = b;
-  b += ((size_t)P * D + 3) & ~(size_t)3;
+  b += 4 * maxq;
+  o.sl = b;
+  b += 4 * (maxq / kSlicePieces + 1);
   o.next = b;
-  b += sizeof(int);
-  o.total = (b + 15) & ~(size_t)15;
+  o.end = b + 8;
   return o;
 }
 
-// A piece as the build stores it: first entry within its tile, length.
-__device__ __forceinline__ int piece_start(uint32_t pc) { return (int)(pc & 0xffffu); }
-__device__ __forceinline__ int piece_len(uint32_t pc) { return (int)(pc >> 16); }
+// The lists of one tile on their way from global memory to LDS: four
+// consecutive entries per thread and round. NT * 4 * ROUNDS entries and
+// NT * QR pieces travel in registers, the rest of longer lists (tiles with
+// very many distinct points) is copied when staged.
+template <int NT>
+struct SplatFetch {
+  static constexpr int ROUNDS = 4096 / (4 * NT);
+  static constexpr int QR = NT >= 1024 ? 1 : NT == 512 ? 2 : 4;
+  fvec4 w[ROUNDS];
+  uint32_t lp[ROUNDS];
+  int32_t dst[QR];
+  uint32_t sl;
+  // Entries are read once per MVM: non-temporal, so that they do not push
+  // the partial rows, which the gather reads next, out of the caches.
+  __device__ __forceinline__ void load(const float* ew, const uint8_t* elp, const int32_t* run_dst,
+                                       const uint32_t* slice, int ne, int nq) {
+    const int tid = threadIdx.x;
+#pragma unroll
+    for (int u = 0; u < ROUNDS; ++u) {
+      const int e4 = tid + u * NT, i = e4 < ne / 4 ? e4 : ne / 4 - 1;
+      w[u] = __builtin_nontemporal_load((const fvec4*)ew + i);
+      lp[u] = __builtin_nontemporal_load((const uint32_t*)elp + i);
+    }
+#pragma unroll
+    for (int u = 0; u < QR; ++u) {
+      const int q = tid + u * NT;
+      dst[u] = run_dst[q < nq ? q : nq - 1];
+    }
+    const int ns = (nq + kSlicePieces - 1) / kSlicePieces;
+    sl = slice[tid < ns ? tid : ns - 1];
+  }
+  // row: bytes of a staged row; pads read the zero row with weight 0
+  __device__ __forceinline__ static void put(unsigned char* smem, const SplatLists& l, int i, fvec4 ww, uint32_t p,
+                                             int row, int zrow) {
+    typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
+    u16x4 o;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float f = ww[j];
+      const bool pad = __float_as_uint(f) == kPadWeight;
+      o[j] = (uint16_t)((pad ? zrow : (int)((p >> (8 * j)) & 0xffu)) * row);
+      ww[j] = pad ? 0.f : f;
+    }
+    *(fvec4*)(smem + l.w + 16 * i) = ww;
+    *(u16x4*)(smem + l.off + 8 * i) = o;
+  }
+  __device__ __forceinline__ void stage(unsigned char* smem, const SplatLists& l, const float* ew,
+                                        const uint8_t* elp, const int32_t* run_dst, const uint32_t* slice,
+                                        int ne, int nq, int row, int zrow) const {
+    const int tid = threadIdx.x;
+    const int ns = (nq + kSlicePieces - 1) / kSlicePieces;
+#pragma unroll
+    for (int u = 0; u < ROUNDS; ++u) {
+      const int i = tid + u * NT;
+      if (i < ne / 4) put(smem, l, i, w[u], lp[u], row, zrow);
+    }
+    for (int i = tid + ROUNDS * NT; i < ne / 4; i += NT)
+      put(smem, l, i, ((const fvec4*)ew)[i], ((const uint32_t*)elp)[i], row, zrow);
+#pragma unroll
+    for (int u = 0; u < QR; ++u) {
+      const int q = tid + u * NT;
+      if (q < nq) ((int32_t*)(smem + l.dst))[q] = dst[u];
+    }
+    for (int q = tid + QR * NT; q < nq; q += NT) ((int32_t*)(smem + l.dst))[q] = run_dst[q];
+    if (tid < ns) ((uint32_t*)(smem + l.sl))[tid] = sl;
+    for (int q = tid + NT; q < ns; q += NT) ((uint32_t*)(smem + l.sl))[q] = slice[q];
+    if (tid == 0) *(int*)(smem + l.next) = NT / 64;  // batches 0 .. NT/64-1 start on a wave each
+  }
+};
 
-// The pieces of a staged tile: each is summed in entry order by LPR lanes of
-// VW channels and stored as its partial row. A wave takes 64 / LPR
-// consecutive pieces at a time, claiming the next batch (lnext) before it
-// sums this one. Pieces are stored longest first, so the pieces of a batch
-// are about equally long and the wave runs one uniform loop of passes of
-// four entries; with pieces in run order every pass of a wave waited for
-// whichever of its 16 groups had just finished a piece to claim, look up and
-// start another (a dependent chain of four LDS accesses): at n = 2M, d = 11,
-// C = 16 (306 pieces of 1 to 32 entries a tile) that took 4 to 7 us of a
-// tile's 14. k_splat_tile there: fp32 156 -> 118 us, fp64 with the direction
-// update 287 -> 262 us (now at the copy rate of its HBM bytes).
-// Entries past a piece's end read the zero row with weight 0: fma(0, 0, acc)
-// is acc exactly, as acc is never -0. A piece's sum does not depend on the
-// wave that takes it.
-template <typename TU, typename S>
-__device__ __forceinline__ void splat_pieces(const TU* lv, int zrow, const float* lw, const uint8_t* llp,
-                                             const uint32_t* lpc, const int32_t* ldst, int* lnext, int nq,
-                                             TU* part, int C, int c0, bool cvec) {
-  constexpr int GPW = 64 / S::LPR;  // pieces per wave
-  const int lane = threadIdx.x & 63, g = lane / S::LPR;
-  const int cl = (lane % S::LPR) * S::VW, cg = c0 + cl;
-  int q0 = (int)(threadIdx.x >> 6) * GPW;
-  while (q0 < nq) {
+// N entries of a piece, from its lane's position in the lists on: their rows
+// are read together and added in entry order.
+template <int N, typename TU, int VW>
+__device__ __forceinline__ void splat_step(const unsigned char* rows, const uint16_t* po, const float* pw,
+                                           TU (&acc)[VW]) {
+  TU x[N][VW], w[N];
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    w[u] = (TU)pw[u * kSlicePieces];
+    read_row<TU, VW>((const TU*)(rows + po[u * kSlicePieces]), x[u]);
+  }
+#pragma unroll
+  for (int u = 0; u < N; ++u)
+#pragma unroll
+    for (int i = 0; i < VW; ++i) acc[i] = fma_t(w[u], x[u][i], acc[i]);
+}
+
+template <typename TU, int VW>
+__device__ __forceinline__ void store_piece(TU* o, const TU (&acc)[VW], int cg, int C, bool cvec) {
+  if (cvec && cg + VW <= C) {
+    write_row<TU, VW>(o, acc);
+  } else {
+#pragma unroll
+    for (int i = 0; i < VW; ++i)
+      if (cg + i < C) o[i] = acc[i];
+  }
+}
+
+// The pieces of a staged tile: each is summed in entry order and stored as
+// its partial row. A wave takes a slice of 16 pieces of about equal length
+// (SPW slices where fewer lanes share a piece), claiming its next before it
+// sums this one, and steps through the interleaved entries with one address
+// per lane. This is bound by instruction issue: with the pieces in run order,
+// one lane group per piece, every step waited for whichever of a wave's 16
+// groups had just finished a piece to claim, look up and start another, and
+// an entry cost ten instructions of addressing and bounds beside its sums.
+// A piece's sum does not depend on the wave that takes it.
+template <typename TU, int G, int NT>
+__device__ __forceinline__ void splat_pieces(const unsigned char* rows, unsigned char* smem, const SplatLists& l,
+                                             int nq, TU* part, int C, int c0, bool cvec) {
+  using W = SplatLanes<G>;
+  const int lane = threadIdx.x & 63, g = lane / W::LPR;
+  const int cl = (lane % W::LPR) * W::VW, cg = c0 + cl;
+  const uint32_t* lsl = (const uint32_t*)(smem + l.sl);
+  const int32_t* ldst = (const int32_t*)(smem + l.dst);
+  const unsigned char* lrows = rows + cl * sizeof(TU);
+  const int ns = (nq + kSlicePieces - 1) / kSlicePieces;
+  int b = (int)(threadIdx.x >> 6);
+  while (b * W::SPW < ns) {
     int nx = 0;
-    if (lane == 0) nx = atomicAdd(lnext, GPW);
-    const int q = q0 + g < nq ? q0 + g : nq - 1;
-    const uint32_t pc = lpc[q];
-    const int dq = ldst[q];
-    const int e0 = piece_start(pc), len = q0 + g < nq ? piece_len(pc) : 0;
-    // the wave's first piece is its longest
-    const int passes = (__builtin_amdgcn_readfirstlane(len) + 3) / 4;
-    int lp[4];
-    float wv[4];
-    auto entries = [&](int p) {
+    if (lane == 0) nx = atomicAdd((int*)(smem + l.next), 1);
+    const int s = b * W::SPW + g / kSlicePieces;
+    uint32_t sw = lsl[s < ns ? s : ns - 1];
+    if constexpr (W::SPW == 1) sw = __builtin_amdgcn_readfirstlane(sw);
+    const int m = s < ns ? (int)(sw >> 16) : 0;
+    const int e = (int)(sw & 0xffffu) + g % kSlicePieces;
+    const int q = s * kSlicePieces + g % kSlicePieces;
+    const int dq = ldst[q < nq ? q : nq - 1];
+    const uint16_t* po = (const uint16_t*)(smem + l.off) + e;
+    const float* pw = (const float*)(smem + l.w) + e;
+    TU acc[W::VW];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int i = 4 * p + u;
-        const int e = e0 + (i < len ? i : 0);
-        const int l = (int)llp[e];
-        const float w = lw[e];
-        lp[u] = i < len ? l : zrow;
-        wv[u] = i < len ? w : 0.f;
-      }
-    };
-    TU acc[S::VW];
-#pragma unroll
-    for (int i = 0; i < S::VW; ++i) acc[i] = 0;
-    entries(0);
-    for (int p = 0; p < passes; ++p) {
-      TU x[4][S::VW], w[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        read_row<TU, S::VW>(lv + lp[u] * S::RS + cl, x[u]);
-        w[u] = (TU)wv[u];
-      }
-      if (p + 1 < passes) entries(p + 1);  // while the rows arrive
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int i = 0; i < S::VW; ++i) acc[i] = fma_t(w[u], x[u][i], acc[i]);
+    for (int i = 0; i < W::VW; ++i) acc[i] = 0;
+    int k = 0;
+    for (; k + 4 <= m; k += 4, po += 4 * kSlicePieces, pw += 4 * kSlicePieces) splat_step<4>(lrows, po, pw, acc);
+    if (k + 2 <= m) {
+      splat_step<2>(lrows, po, pw, acc);
+      k += 2;
+      po += 2 * kSlicePieces;
+      pw += 2 * kSlicePieces;
     }
-    if (len > 0) {
-      TU* o = part + (int64_t)dq * C + cg;
-      if (cvec && cg + S::VW <= C) {
-        write_row<TU, S::VW>(o, acc);
-      } else {
-#pragma unroll
-        for (int i = 0; i < S::VW; ++i)
-          if (cg + i < C) o[i] = acc[i];
-      }
-    }
-    q0 = __builtin_amdgcn_readfirstlane(nx);
+    if (k < m) splat_step<1>(lrows, po, pw, acc);
+    if (q < nq && m > 0) store_piece(part + (int64_t)dq * C + cg, acc, cg, C, cvec);
+    b = __builtin_amdgcn_readfirstlane(nx);
   }
 }
 
@@ -265,6 +340,7 @@ __device__ __forceinline__ void splat_pieces(const TU* lv, int zrow, const float
 template <int RS, typename TU>
 __device__ __forceinline__ double block_sumsq(const TU* lv, int blk, int c, int np) {
   double v = 0.0;
+  asm volatile("" : "+v"(blk));  // keeps the 16 addresses out of the caller's loop-long registers
 #pragma unroll
   for (int u = 0; u < 16; ++u) {
     const int q = blk * 16 + u;
