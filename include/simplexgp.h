@@ -130,8 +130,10 @@ int lattice_mvm_noalloc(const sgp_lattice* L, const float* values, int32_t C, fl
  * Section 5.4 for the tolerance semantics). A column stops when its
  * recursive residual ||r||/||rhs|| <= tol, or after max_iter iterations;
  * tol = 0 runs exactly max_iter iterations. Non-convergence is not an error.
- * Internally the iteration vectors, the lattice values of its MVMs and all
- * reductions are fp64 (the weights stay fp32), so the recursive residual
+ * Internally the iteration vectors (kept per point, or, where lattice points
+ * are few against the points, per lattice point: every vector of the
+ * recurrence lies in span(rhs) + range(W)), the lattice values of its MVMs and
+ * all reductions are fp64 (the weights stay fp32), so the recursive residual
  * tracks the true residual at tolerances down to ~1e-8 on systems of
  * condition ~1e4; rhs and x are fp32.
  * rhs, x: n x C fp32 device arrays, 1 <= C <= 64, x must not overlap rhs.
@@ -252,7 +254,7 @@ int sgp_blur_fuse_enable(int on);
 int64_t sgp_blur_seq_bytes(int64_t bytes);
 
 /* CG direction update fused into the splat (process-wide switch, default
- * on). Each iteration's x += alpha p and p = r + beta p (Section 2, the
+ * on; solves whose vectors live on the lattice have no such pass). Each iteration's x += alpha p and p = r + beta p (Section 2, the
  * conjugate-gradient recurrence) then run in the next iteration's splat,
  * which reads every element of p anyway, and the last one in the final copy
  * of x; off, they run as a pass of their own. The arithmetic is the same, so

@@ -8,7 +8,8 @@
 // a one-block kernel turns it into alpha; the slice then moves the residual
 // (r -= alpha A p, never storing A p) and its last block decides
 // convergence and beta. The host only polls the per-column "active" flags
-// every few iterations.
+// every few iterations. Where lattice points are few against the points, the
+// vectors live on the lattice instead (cg_tile.h).
 //
 // Precision: the recurrence vectors (r, p), the lattice values inside
 // its MVMs and all reductions are fp64; the barycentric weights and x stay
@@ -124,14 +125,12 @@ __global__ __launch_bounds__(kBlock) void k_cg_init(const float* __restrict__ b,
 // 16g .. 16g + 15 of the splat's noise * p.p in order. All of these rows
 // are then folded into p.Ap and alpha (the order depends on m and the tile
 // count only): by the last block to finish when the kernel has few blocks
-// (fold), else by k_cg_scalar, as a device-scope fence in every one of
-// thousands of blocks costs more than the launch.
-constexpr int64_t kAlphaFoldBlocks = 256;
+// (kFoldBlocks), else by k_cg_scalar.
 __global__ __launch_bounds__(kBlock) void k_cg_alpha(const double* __restrict__ u,
                                                      const double* __restrict__ bu, int64_t m, int C,
                                                      double scale, int64_t lat_parts,
                                                      const double* __restrict__ pp, int64_t ntiles,
-                                                     CgHook h, int fold) {
+                                                     CgHook h) {
   extern __shared__ double dsh[];
   cg_partials<kSuperLat>(m, C, h.partials, dsh, [=](int64_t i0, int c) {
     double uv[kCgRowsPerGroup], bv[kCgRowsPerGroup];
@@ -156,7 +155,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_alpha(const double* __restrict__ 
       h.partials[(lat_parts + g) * C + c] = v;
     }
   }
-  if (fold) cg_finish(h, C, dsh);
+  cg_finish(h, C, dsh);
 }
 
 // The scalar step after a vector kernel, in one block of its own: the
@@ -166,7 +165,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_alpha(const double* __restrict__ 
 constexpr int kScalarThreads = 1024;
 __global__ __launch_bounds__(kScalarThreads) void k_cg_scalar(CgHook h, int C) {
   __shared__ double sh[kFold * kMaxCgCols];
-  cg_scalar_block(h.partials, h.nparts, C, h.st, h.mode, h.tol, sh);
+  cg_scalar_block(h.partials, h.nparts, C, h.st, h.mode, h.tol, h.noise, sh);
 }
 
 // x += alpha p with this iteration's alpha (zero for a column that was
@@ -213,19 +212,22 @@ __global__ __launch_bounds__(kBlock) void k_cg_dir(float* __restrict__ x, const 
 int launch_cg_alpha(const double* u, const double* bu, int64_t m, int C, double scale, const CgMvm& cg,
                     hipStream_t s) {
   const int64_t blocks = cg.lat_parts + (cg.ntiles + 15) / 16;
-  const int fold = blocks <= kAlphaFoldBlocks ? 1 : 0;
+  CgHook h = cg.alpha;
+  h.fold = blocks <= kFoldBlocks ? 1 : 0;
   {
     ProfScope ps(KK_CG_ALPHA, s);
-    const size_t lds = fold ? std::max(cg_vec_lds(C), sizeof(double) * kFold * C) : cg_vec_lds(C);
+    const size_t lds = h.fold ? std::max(cg_vec_lds(C), sizeof(double) * kFold * C) : cg_vec_lds(C);
     hipLaunchKernelGGL(k_cg_alpha, dim3((unsigned)blocks), dim3(kBlock), lds, s, u, bu, m, C, scale,
-                       cg.lat_parts, (const double*)cg.pp, cg.ntiles, cg.alpha, fold);
+                       cg.lat_parts, (const double*)cg.pp, cg.ntiles, h);
     SGP_LAUNCH_CHECK("k_cg_alpha");
   }
-  if (!fold) {
-    ProfScope ps(KK_CG_SCALAR, s);
-    hipLaunchKernelGGL(k_cg_scalar, dim3(1), dim3(kScalarThreads), 0, s, cg.alpha, C);
-    SGP_LAUNCH_CHECK("k_cg_scalar");
-  }
+  return h.fold ? SGP_OK : launch_cg_scalar(h, C, s);
+}
+
+int launch_cg_scalar(const CgHook& h, int C, hipStream_t s) {
+  ProfScope ps(KK_CG_SCALAR, s);
+  hipLaunchKernelGGL(k_cg_scalar, dim3(1), dim3(kScalarThreads), 0, s, h, C);
+  SGP_LAUNCH_CHECK("k_cg_scalar");
   return SGP_OK;
 }
 
@@ -300,8 +302,11 @@ int cg_run(const sgp_lattice* L, const float* b, int C, float noise, float tol, 
   sgp_lattice* Lm = const_cast<sgp_lattice*>(L);
   const int64_t n = L->n, nC = n * C;
   int rc;
-  // r, p in fp64, then x in fp32
-  if ((rc = dev_reserve(L, Lm->cgvec, (sizeof(double) * 2 + sizeof(float)) * nC, s))) return rc;
+  const bool lat = cg_on_lattice(L);
+  // r, p in fp64, then x in fp32; on the lattice, b in sorted order
+  const size_t vec_bytes = lat ? sizeof(float) * nC : (sizeof(double) * 2 + sizeof(float)) * nC;
+  if ((rc = dev_reserve(L, Lm->cgvec, vec_bytes, s))) return rc;
+  if (lat && (rc = dev_reserve(L, Lm->ubuf, sizeof(double) * cg_lat_work_elems(L, C), s))) return rc;
   // partial sums: one row per superchunk from the init kernel or per tile
   // from the slice (r.r); one per superchunk of lattice rows and per 16
   // tiles (alpha); one per tile from the splat (p.p); then the scalar
@@ -334,26 +339,36 @@ int cg_run(const sgp_lattice* L, const float* b, int C, float noise, float tol, 
   const dim3 block(kBlock);
   const dim3 igrid((unsigned)std::min<int64_t>(iparts, 65536));
   const size_t vlds = cg_vec_lds(C);
-  const CgHook h_start{rr_parts, iparts, st, counter, (int)SM_START, (double)tol};
+  const CgHook h_start{rr_parts, iparts, st, counter, (int)SM_START, (double)tol, 0.0, 0};
   CgMvm cgm;
-  cgm.alpha = CgHook{al_parts, lparts + groups, st, counter, (int)SM_ALPHA, (double)tol};
+  cgm.alpha = CgHook{al_parts, lparts + groups, st, counter, (int)SM_ALPHA, (double)tol, 0.0, 0};
   cgm.lat_parts = lparts;
   cgm.pp = pp_parts;
   cgm.ntiles = L->ntiles;
-  cgm.beta = CgHook{rr_parts, L->ntiles, st, counter, (int)SM_BETA, (double)tol};
+  cgm.beta = CgHook{rr_parts, L->ntiles, st, counter, (int)SM_BETA, (double)tol, 0.0, 0};
   cgm.r = r;
+  // The same solve with its vectors on the lattice: the first tile pass
+  // starts it, the last one forms x.
+  CgLat cl;
+  cl.rhs = b;
+  cl.x = x;
+  cl.bs = (float*)Lm->cgvec.ptr;
+  cl.work = (double*)Lm->ubuf.ptr;
+  cl.noise = (double)noise;
+  cl.lat_parts = lparts;
+  cl.start = CgHook{rr_parts, L->ntiles, st, counter, (int)SM_START, (double)tol, 0.0, 0};
+  cl.alpha = CgHook{al_parts, lparts, st, counter, (int)SM_ALPHA_LAT, (double)tol, (double)noise, 0};
+  cl.beta = cgm.beta;
   if ((rc = launch_fill_u32(counter, 1, 0u, s))) return rc;
-  {
+  if (lat) {
+    if ((rc = cg_lat_start(L, C, cl, s))) return rc;
+  } else {
     ProfScope ps(KK_CG_INIT, s);
     hipLaunchKernelGGL(k_cg_init, igrid, block, vlds, s, b, (const uint32_t*)L->perm.ptr, x32, r, p, n, C,
                        L->solve_rows, rr_parts);
     SGP_LAUNCH_CHECK("k_cg_init");
   }
-  {
-    ProfScope ps(KK_CG_SCALAR, s);
-    hipLaunchKernelGGL(k_cg_scalar, dim3(1), dim3(kScalarThreads), 0, s, h_start, C);
-    SGP_LAUNCH_CHECK("k_cg_scalar");
-  }
+  if (!lat && (rc = launch_cg_scalar(h_start, C, s))) return rc;
   // One iteration: one MVM of p that also yields alpha, r -= alpha A p,
   // convergence and beta (CgMvm); x and p move in the next iteration's
   // splat. Nothing here talks to the host, so a block of iterations can be
@@ -364,6 +379,7 @@ int cg_run(const sgp_lattice* L, const float* b, int C, float noise, float tol, 
   const bool fused = cg_fuse_enabled();
   const CgDirUpdate dirup{p, r, x32, st};
   auto iterate = [&](hipStream_t st_, bool first) -> int {
+    if (lat) return cg_lat_iter(L, C, cl, first, st_);
     int rc_ = mvm_cg(L, p, C, st_, (double)noise, cgm, (fused && !first) ? &dirup : nullptr);
     if (rc_) return rc_;
     if (!fused) {
@@ -449,7 +465,9 @@ int cg_run(const sgp_lattice* L, const float* b, int C, float noise, float tol, 
     if (polling && (it + 1) % blk == 0 && it + 1 < max_iter)
       if ((rc = all_done(&done))) return rc;
   }
-  {
+  if (lat) {
+    if ((rc = cg_lat_out(L, C, cl, s))) return rc;
+  } else {
     ProfScope ps(KK_CG_OUT, s);
     const int vec = (C % 4 == 0 && ((uintptr_t)x & 15u) == 0) ? 1 : 0;
     const int64_t work = n * ((C + 3) / 4);

@@ -14,12 +14,19 @@ struct CgState {
   double bnorm[kMaxCgCols];
   double alpha[kMaxCgCols];
   double beta[kMaxCgCols];
+  // lattice form (cg_tile.h): coefficients of b in r, p and x, and p.p
+  double rho[kMaxCgCols];
+  double pi[kMaxCgCols];
+  double xi[kMaxCgCols];
+  double pp[kMaxCgCols];
   float rel[kMaxCgCols];
   int32_t active[kMaxCgCols];
   int32_t iters[kMaxCgCols];
 };
 
-enum ScalarMode { SM_START = 0, SM_ALPHA = 1, SM_BETA = 2 };
+// SM_ALPHA_LAT: the partial sums hold p.Ap without its noise * p.p term,
+// which the state supplies; rho and xi move with alpha.
+enum ScalarMode { SM_START = 0, SM_ALPHA = 1, SM_BETA = 2, SM_ALPHA_LAT = 3 };
 
 // The previous iteration's direction update, applied by the next MVM's
 // splat as it stages the direction (the splat reads p anyway): x += alpha p
@@ -40,7 +47,13 @@ struct CgHook {
   unsigned* counter;  // blocks finished; 0 between launches
   int mode;
   double tol;
+  double noise;       // SM_ALPHA_LAT
+  int fold;           // the kernel's last block folds (else a k_cg_scalar launch does)
 };
+// A device-scope fence writes back its XCD's L2, so a fold by the last block
+// to finish costs a fence per block: kernels of more blocks than this leave
+// it to a one-block launch.
+constexpr int64_t kFoldBlocks = 100;
 
 // What the MVM of a CG iteration does besides A p. Its alpha needs p.Ap,
 // which equals scale * u.(B u) + noise * p.p for the splatted u = W^T p and
@@ -61,6 +74,19 @@ struct CgMvm {
   double* r;
 };
 
+// A solve whose vectors live on the lattice (cg_tile.h): the caller's rhs
+// and x, b in sorted order (n x C fp32), the work arrays (cg_lat_work_elems
+// doubles) and the scalar steps' hooks.
+struct CgLat {
+  const float* rhs;
+  float* x;
+  float* bs;
+  double* work;
+  double noise;
+  int64_t lat_parts;  // partial rows of u.(B u)
+  CgHook start, alpha, beta;
+};
+
 constexpr int kFold = 64;  // fixed fold width: the order depends on nparts only
 
 // Sum the nparts partial rows of each column in a fixed order and apply one
@@ -68,7 +94,7 @@ constexpr int kFold = 64;  // fixed fold width: the order depends on nparts only
 // column c; one thread per column folds the kFold sums in order. Called by
 // every thread of one block; sh holds kFold * C doubles.
 __device__ inline void cg_scalar_block(const double* partials, int64_t nparts, int C, CgState* st,
-                                       int mode, double tol, double* sh) {
+                                       int mode, double tol, double noise, double* sh) {
   const int tid = threadIdx.x;
   for (int pair = tid; pair < kFold * C; pair += blockDim.x) {
     const int g = pair / C, c = pair - g * C;
@@ -98,9 +124,17 @@ __device__ inline void cg_scalar_block(const double* partials, int64_t nparts, i
       st->rel[cc] = v > 0.0 ? 1.f : 0.f;
       st->alpha[cc] = 0.0;
       st->beta[cc] = 0.0;
-    } else if (mode == SM_ALPHA) {
+      st->rho[cc] = 1.0;
+      st->pi[cc] = 1.0;
+      st->xi[cc] = 0.0;
+      st->pp[cc] = v;
+    } else if (mode == SM_ALPHA || mode == SM_ALPHA_LAT) {
+      if (mode == SM_ALPHA_LAT) v = __builtin_fma(noise, st->pp[cc], v);
       if (st->active[cc] && v > 0.0) {
-        st->alpha[cc] = st->rr[cc] / v;
+        const double al = st->rr[cc] / v;
+        st->alpha[cc] = al;
+        st->xi[cc] = __builtin_fma(al, st->pi[cc], st->xi[cc]);
+        st->rho[cc] = __builtin_fma(-al * noise, st->pi[cc], st->rho[cc]);
       } else {
         st->alpha[cc] = 0.0;
         st->active[cc] = 0;  // converged, or breakdown (p.Ap <= 0)
@@ -114,8 +148,11 @@ __device__ inline void cg_scalar_block(const double* partials, int64_t nparts, i
           st->active[cc] = 0;
           st->beta[cc] = 0.0;
         } else {
-          st->beta[cc] = v / st->rr[cc];
+          const double be = v / st->rr[cc];
+          st->beta[cc] = be;
           st->rr[cc] = v;
+          st->pp[cc] = __builtin_fma(be * be, st->pp[cc], v);
+          st->pi[cc] = __builtin_fma(be, st->pi[cc], st->rho[cc]);
         }
       } else {
         st->beta[cc] = 0.0;
@@ -132,6 +169,7 @@ __device__ inline void cg_scalar_block(const double* partials, int64_t nparts, i
 // fence writes back or invalidates the L2 of its XCD, so one per block, not
 // one per wave.) The last block resets the counter for the next launch.
 __device__ inline void cg_finish(const CgHook& h, int C, double* sh) {
+  if (!h.fold) return;
   __shared__ int last;
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -142,7 +180,7 @@ __device__ inline void cg_finish(const CgHook& h, int C, double* sh) {
   }
   __syncthreads();
   if (!last) return;
-  cg_scalar_block(h.partials, h.nparts, C, h.st, h.mode, h.tol, sh);
+  cg_scalar_block(h.partials, h.nparts, C, h.st, h.mode, h.tol, h.noise, sh);
   if (threadIdx.x == 0) *h.counter = 0u;
 }
 

@@ -34,6 +34,7 @@
 #include <vector>
 
 #include "cg_step.h"
+#include "cg_tile.h"
 #include "sgp_internal.h"
 #include "tile.h"
 
@@ -266,11 +267,13 @@ __global__ __launch_bounds__(kSplatBlock) __attribute__((amdgpu_waves_per_eu(4))
 // k_gather_fix. The work per group is fixed, whatever the list lengths.
 // VW channels per lane (16-byte loads when the rows allow), G / VW lanes per
 // group; every channel's rows are added in the same order for any VW.
+// beta (lattice CG, else null): U = sum + beta U per column.
 template <typename TU, int G, int VW>
 __global__ __launch_bounds__(kBlock) void k_splat_gather(const int32_t* __restrict__ row_vert,
                                                          const TU* __restrict__ part,
                                                          TU* __restrict__ U, TU* __restrict__ frag,
-                                                         int64_t nrows, int C, int64_t ngroups, int R) {
+                                                         int64_t nrows, int C, int64_t ngroups, int R,
+                                                         const double* __restrict__ beta) {
   constexpr int LG = G / VW;       // lanes per group
   constexpr int GPB = kBlock / LG;  // groups per block
   constexpr int B = 8;              // rows loaded together
@@ -292,6 +295,12 @@ __global__ __launch_bounds__(kBlock) void k_splat_gather(const int32_t* __restri
     auto flush = [&](int64_t end) {
       const bool whole = (seg > o0 || before != cur) && (end < o1 || after != cur);
       TU* dst = whole ? U + (int64_t)cur * C + c : frag + (gi * 2 + (seg == o0 ? 0 : 1)) * C + c;
+      if (beta && whole) {
+        TU old[VW];
+        read_row<TU, VW>(dst, old);
+#pragma unroll
+        for (int i = 0; i < VW; ++i) acc[i] = fma_t((TU)beta[c + i], old[i], acc[i]);
+      }
       write_row<TU, VW>(dst, acc);
     };
     for (int64_t k0 = o0; k0 < o1; k0 += B) {
@@ -332,7 +341,7 @@ __global__ __launch_bounds__(kBlock) void k_gather_fix(const int32_t* __restrict
                                                        const int32_t* __restrict__ occ_ptr,
                                                        const void* __restrict__ frag_v,
                                                        void* __restrict__ U_v, int64_t ngroups, int C,
-                                                       int elem, int R) {
+                                                       int elem, int R, const double* __restrict__ beta) {
   const int64_t total = ngroups * C;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < total; q += stride) {
@@ -348,7 +357,8 @@ __global__ __launch_bounds__(kBlock) void k_gather_fix(const int32_t* __restrict
       const double* frag = (const double*)frag_v;
       double acc = frag[first];
       for (int64_t g = g0 + 1; g <= g1; ++g) acc += frag[(g * 2) * C + c];
-      ((double*)U_v)[j * C + c] = acc;
+      double* dst = (double*)U_v + j * C + c;
+      *dst = beta ? fma_t(beta[c], *dst, acc) : acc;
     } else {
       const float* frag = (const float*)frag_v;
       float acc = frag[first];
@@ -1084,92 +1094,38 @@ size_t mvm_work_elems(const sgp_lattice* L, int C, bool cg) {
   return (size_t)((cg ? 5 : 4) * L->m + L->npiece + 2 * gather_ranges(L)) * (size_t)C;
 }
 
-// LDS of k_splat_tile: values [P+1][G], then the entry lists.
-template <typename TU>
-SplatLists splat_lds(const sgp_lattice* L, int G) {
-  const int rs = G * (int)sizeof(TU) >= 64 ? G + 16 / (int)sizeof(TU) : G;
-  return splat_lists((int)sizeof(TU) * (L->tile_points + 1) * rs, L->max_tile_ents, L->max_tile_pieces);
+// U0 = the partial rows summed per lattice point (+ beta U0 per column when
+// beta is given: device array, fp64 only).
+template <typename TU, int G>
+int gather_g(const sgp_lattice* L, const TU* part, TU* U0, TU* frag, int C, const double* beta, hipStream_t s) {
+  ProfScope ps(KK_SPLAT_GATHER, s);
+  const int R = gather_rows(L);
+  const int64_t ngroups = gather_ranges(L);
+  constexpr int VWG = 16 / (int)sizeof(TU);  // channels per lane with 16-byte loads
+  if (G % VWG == 0 && C % VWG == 0 && aligned16(part) && aligned16(U0) && aligned16(frag)) {
+    const int64_t blocks = (ngroups + kBlock / (G / VWG) - 1) / (kBlock / (G / VWG));
+    hipLaunchKernelGGL((k_splat_gather<TU, G, (G % VWG == 0 ? VWG : 1)>), dim3((unsigned)blocks), dim3(kBlock),
+                       0, s, (const int32_t*)L->row_vert.ptr, part, U0, frag, L->npiece, C, ngroups, R, beta);
+  } else {
+    const int64_t blocks = (ngroups + kBlock / G - 1) / (kBlock / G);
+    hipLaunchKernelGGL((k_splat_gather<TU, G, 1>), dim3((unsigned)blocks), dim3(kBlock), 0, s,
+                       (const int32_t*)L->row_vert.ptr, part, U0, frag, L->npiece, C, ngroups, R, beta);
+  }
+  SGP_LAUNCH_CHECK("k_splat_gather");
+  hipLaunchKernelGGL(k_gather_fix, dim3(grid_cap(ngroups * C)), dim3(kBlock), 0, s,
+                     (const int32_t*)L->row_vert.ptr, (const int32_t*)L->occ_ptr.ptr, (const void*)frag,
+                     (void*)U0, ngroups, C, (int)sizeof(TU), R, beta);
+  SGP_LAUNCH_CHECK("k_gather_fix");
+  return SGP_OK;
 }
 
-// cgm (CG only, else null): V is the direction p, out the residual r (both
-// internal order), and the MVM finishes the CG step (CgMvm).
+// The blur of U0 (m x C): B1 .. B4 are work arrays (B4 may be U0 where it need
+// not outlive the blur); *result is the array that holds the blurred values
+// (forward + reverse in SYMMETRIC order).
 template <typename TU, int G>
-int mvm_g(const sgp_lattice* L, const TU* V, const uint32_t* perm, int C, TU* out, hipStream_t s,
-          TU noise, const CgMvm* cgm, const LaunchChoice& lc, void* work, const CgDirUpdate* up) {
-  const int d = L->d, D = d + 1, T = 2 * L->order;
+int blur_g(const sgp_lattice* L, TU* U0, TU* B1, TU* B2, TU* B3, TU* B4, int C, hipStream_t s, const TU** result) {
+  const int d = L->d, T = 2 * L->order;
   const int64_t m = L->m, mC = m * C;
-  const TU* p = cgm ? V : nullptr;
-  TU* U0 = (TU*)work;
-  TU* B1 = U0 + mC;
-  TU* B2 = B1 + mC;
-  TU* B3 = B2 + mC;
-  TU* B4 = cgm ? B3 + mC : U0;  // chain 1's second array (U0 itself outside CG)
-  TU* part = (cgm ? B4 : B3) + mC;
-  TU* frag = part + L->npiece * C;  // 2 rows per gather range
-  const int chunks = (C + G - 1) / G;
-  const int P = L->tile_points;
-  const dim3 tgrid((unsigned)L->ntiles, (unsigned)chunks);
-  const int maxq = L->max_tile_runs;
-  SplatArgs<TU> sa;
-  sa.n = L->n;
-  sa.items = L->ntiles * chunks;
-  sa.P = P;
-  sa.D = D;
-  sa.C = C;
-  sa.chunks = chunks;
-  sa.vec_v = (TileShape<TU, G, kSplatBlock>::VEC && !perm && C == G && aligned16(V)) ? 1 : 0;
-  sa.vec_perm = (TileShape<TU, G, kSplatBlock>::VEC && perm && C == G && aligned16(V)) ? 1 : 0;
-  sa.cvec = (C % Vec16<TU>::N == 0 && aligned16(part)) ? 1 : 0;
-  sa.estride = tile_ent_stride(P * D);
-  sa.lds = splat_lds<TU>(L, G);
-  sa.pp_scale = cgm ? (double)noise : 0.0;
-  double* pp = cgm ? cgm->pp : nullptr;
-  // the previous CG iteration's direction update: in this splat where its
-  // values are whole vectors of all C columns, else as a pass of its own
-  const bool dir_fused = up && sizeof(TU) == 8 && !perm && C == G &&
-                         (!TileShape<TU, G, kSplatBlock>::VEC || sa.vec_v);
-  if (up && !dir_fused) {
-    const int rc = launch_cg_dir(*up, (int64_t)L->n * C, C, s);
-    if (rc) return rc;
-  }
-  {
-    ProfScope ps(KK_SPLAT, s);
-    const void* kern =
-        dir_fused ? (const void*)&k_splat_tile<TU, G, true> : (const void*)&k_splat_tile<TU, G, false>;
-    const unsigned grid = persistent_grid(kern, kSplatBlock, (size_t)sa.lds.end, sa.items, lc.splat_bpc);
-    if (dir_fused)
-      hipLaunchKernelGGL((k_splat_tile<TU, G, true>), dim3(grid), dim3(kSplatBlock), (size_t)sa.lds.end, s,
-                         (const int32_t*)L->stile_off.ptr, (const int32_t*)L->tile_ent.ptr, (const uint32_t*)L->slice.ptr,
-                         (const int32_t*)L->run_dst.ptr, (const uint8_t*)L->ent_lp.ptr,
-                         (const float*)L->ent_w.ptr, V, perm, part, pp, sa, *up);
-    else
-      hipLaunchKernelGGL((k_splat_tile<TU, G, false>), dim3(grid), dim3(kSplatBlock), (size_t)sa.lds.end, s,
-                         (const int32_t*)L->stile_off.ptr, (const int32_t*)L->tile_ent.ptr, (const uint32_t*)L->slice.ptr,
-                         (const int32_t*)L->run_dst.ptr, (const uint8_t*)L->ent_lp.ptr,
-                         (const float*)L->ent_w.ptr, V, perm, part, pp, sa, CgDirUpdate{});
-    SGP_LAUNCH_CHECK("k_splat_tile");
-  }
-  {
-    ProfScope ps(KK_SPLAT_GATHER, s);
-    const int R = gather_rows(L);
-    const int64_t ngroups = gather_ranges(L);
-    constexpr int VWG = 16 / (int)sizeof(TU);  // channels per lane with 16-byte loads
-    if (G % VWG == 0 && C % VWG == 0 && aligned16(part) && aligned16(U0) && aligned16(frag)) {
-      const int64_t blocks = (ngroups + kBlock / (G / VWG) - 1) / (kBlock / (G / VWG));
-      hipLaunchKernelGGL((k_splat_gather<TU, G, (G % VWG == 0 ? VWG : 1)>), dim3((unsigned)blocks), dim3(kBlock),
-                         0, s, (const int32_t*)L->row_vert.ptr, part, U0, frag, L->npiece, C, ngroups, R);
-    } else {
-      const int64_t blocks = (ngroups + kBlock / G - 1) / (kBlock / G);
-      hipLaunchKernelGGL((k_splat_gather<TU, G, 1>), dim3((unsigned)blocks), dim3(kBlock), 0, s,
-                         (const int32_t*)L->row_vert.ptr, part, U0, frag, L->npiece, C, ngroups, R);
-    }
-    SGP_LAUNCH_CHECK("k_splat_gather");
-    hipLaunchKernelGGL(k_gather_fix, dim3(grid_cap(ngroups * C)), dim3(kBlock), 0, s,
-                       (const int32_t*)L->row_vert.ptr, (const int32_t*)L->occ_ptr.ptr, (const void*)frag,
-                       (void*)U0, ngroups, C, (int)sizeof(TU), R);
-    SGP_LAUNCH_CHECK("k_gather_fix");
-  }
-
   const bool sym = L->blur == SGP_BLUR_SYMMETRIC;
   BlurArgs<TU> a;
   a.m = m;
@@ -1272,13 +1228,87 @@ int mvm_g(const sgp_lattice* L, const TU* V, const uint32_t* perm, int C, TU* ou
     cur[1] = dst1;
   }
   if (const int rc = flush_later()) return rc;
+  *result = cur[0];
+  return SGP_OK;
+}
+
+// LDS of k_splat_tile: values [P+1][G], then the entry lists.
+template <typename TU>
+SplatLists splat_lds(const sgp_lattice* L, int G) {
+  const int rs = G * (int)sizeof(TU) >= 64 ? G + 16 / (int)sizeof(TU) : G;
+  return splat_lists((int)sizeof(TU) * (L->tile_points + 1) * rs, L->max_tile_ents, L->max_tile_pieces);
+}
+
+// cgm (CG only, else null): V is the direction p, out the residual r (both
+// internal order), and the MVM finishes the CG step (CgMvm).
+template <typename TU, int G>
+int mvm_g(const sgp_lattice* L, const TU* V, const uint32_t* perm, int C, TU* out, hipStream_t s,
+          TU noise, const CgMvm* cgm, const LaunchChoice& lc, void* work, const CgDirUpdate* up) {
+  const int D = L->d + 1;
+  const int64_t m = L->m, mC = m * C;
+  const TU* p = cgm ? V : nullptr;
+  TU* U0 = (TU*)work;
+  TU* B1 = U0 + mC;
+  TU* B2 = B1 + mC;
+  TU* B3 = B2 + mC;
+  TU* B4 = cgm ? B3 + mC : U0;  // chain 1's second array (U0 itself outside CG)
+  TU* part = (cgm ? B4 : B3) + mC;
+  TU* frag = part + L->npiece * C;  // 2 rows per gather range
+  const int chunks = (C + G - 1) / G;
+  const int P = L->tile_points;
+  const dim3 tgrid((unsigned)L->ntiles, (unsigned)chunks);
+  const int maxq = L->max_tile_runs;
+  SplatArgs<TU> sa;
+  sa.n = L->n;
+  sa.items = L->ntiles * chunks;
+  sa.P = P;
+  sa.D = D;
+  sa.C = C;
+  sa.chunks = chunks;
+  sa.vec_v = (TileShape<TU, G, kSplatBlock>::VEC && !perm && C == G && aligned16(V)) ? 1 : 0;
+  sa.vec_perm = (TileShape<TU, G, kSplatBlock>::VEC && perm && C == G && aligned16(V)) ? 1 : 0;
+  sa.cvec = (C % Vec16<TU>::N == 0 && aligned16(part)) ? 1 : 0;
+  sa.estride = tile_ent_stride(P * D);
+  sa.lds = splat_lds<TU>(L, G);
+  sa.pp_scale = cgm ? (double)noise : 0.0;
+  double* pp = cgm ? cgm->pp : nullptr;
+  // the previous CG iteration's direction update: in this splat where its
+  // values are whole vectors of all C columns, else as a pass of its own
+  const bool dir_fused = up && sizeof(TU) == 8 && !perm && C == G &&
+                         (!TileShape<TU, G, kSplatBlock>::VEC || sa.vec_v);
+  if (up && !dir_fused) {
+    const int rc = launch_cg_dir(*up, (int64_t)L->n * C, C, s);
+    if (rc) return rc;
+  }
+  {
+    ProfScope ps(KK_SPLAT, s);
+    const void* kern =
+        dir_fused ? (const void*)&k_splat_tile<TU, G, true> : (const void*)&k_splat_tile<TU, G, false>;
+    const unsigned grid = persistent_grid(kern, kSplatBlock, (size_t)sa.lds.end, sa.items, lc.splat_bpc);
+    if (dir_fused)
+      hipLaunchKernelGGL((k_splat_tile<TU, G, true>), dim3(grid), dim3(kSplatBlock), (size_t)sa.lds.end, s,
+                         (const int32_t*)L->stile_off.ptr, (const int32_t*)L->tile_ent.ptr, (const uint32_t*)L->slice.ptr,
+                         (const int32_t*)L->run_dst.ptr, (const uint8_t*)L->ent_lp.ptr,
+                         (const float*)L->ent_w.ptr, V, perm, part, pp, sa, *up);
+    else
+      hipLaunchKernelGGL((k_splat_tile<TU, G, false>), dim3(grid), dim3(kSplatBlock), (size_t)sa.lds.end, s,
+                         (const int32_t*)L->stile_off.ptr, (const int32_t*)L->tile_ent.ptr, (const uint32_t*)L->slice.ptr,
+                         (const int32_t*)L->run_dst.ptr, (const uint8_t*)L->ent_lp.ptr,
+                         (const float*)L->ent_w.ptr, V, perm, part, pp, sa, CgDirUpdate{});
+    SGP_LAUNCH_CHECK("k_splat_tile");
+  }
+  if (const int rc = gather_g<TU, G>(L, part, U0, frag, C, nullptr, s)) return rc;
+  const TU* blurred = nullptr;
+  if (const int rc = blur_g<TU, G>(L, U0, B1, B2, B3, B4, C, s, &blurred)) return rc;
+  const bool sym = L->blur == SGP_BLUR_SYMMETRIC;
   const TU scale = sym ? (TU)(0.5 * (double)L->outputscale) : (TU)L->outputscale;
   if (cgm) {
     // alpha from p.Ap = scale * u.(B u) + noise * p.p, before the slice
-    const int rc = launch_cg_alpha((const double*)U0, (const double*)cur[0], m, C, (double)scale, *cgm, s);
+    const int rc = launch_cg_alpha((const double*)U0, (const double*)blurred, m, C, (double)scale, *cgm, s);
     if (rc) return rc;
   }
-  ProfScope ps(KK_SLICE, s);
+  CgHook bh = {};
+  if (cgm) bh = cgm->beta;
   SliceArgs<TU> la;
   la.n = L->n;
   la.items = L->ntiles * chunks;
@@ -1296,18 +1326,20 @@ int mvm_g(const sgp_lattice* L, const TU* V, const uint32_t* perm, int C, TU* ou
   const float* ws = (const float*)L->ws.ptr;
   const uint32_t* mperm = (const uint32_t*)L->perm.ptr;
   auto launch = [&](auto nt_tag) {
+    ProfScope ps(KK_SLICE, s);
     constexpr int NT = decltype(nt_tag)::value;
     la.lds = slice_lds<TU, G, NT>(P, D, maxq);
     if (cgm) {
       const unsigned grid = persistent_grid((const void*)&k_slice_tile<TU, G, true, NT>, NT, la.lds.total,
                                             la.items, lc.slice_bpc);
+      bh.fold = grid <= kFoldBlocks ? 1 : 0;
       hipLaunchKernelGGL((k_slice_tile<TU, G, true, NT>), dim3(grid), dim3(NT), la.lds.total, s, toff, tverts,
-                         loc, ws, (const TU*)cur[0], out, perm, p, cgm->beta, mperm, la);
+                         loc, ws, blurred, out, perm, p, bh, mperm, la);
     } else {
       const unsigned grid = persistent_grid((const void*)&k_slice_tile<TU, G, false, NT>, NT, la.lds.total,
                                             la.items, lc.slice_bpc);
       hipLaunchKernelGGL((k_slice_tile<TU, G, false, NT>), dim3(grid), dim3(NT), la.lds.total, s, toff, tverts,
-                         loc, ws, (const TU*)cur[0], out, perm, (const TU*)nullptr, CgHook{}, mperm, la);
+                         loc, ws, blurred, out, perm, (const TU*)nullptr, CgHook{}, mperm, la);
     }
   };
   constexpr int NTn = slice_threads_narrow<G>();
@@ -1317,7 +1349,7 @@ int mvm_g(const sgp_lattice* L, const TU* V, const uint32_t* perm, int C, TU* ou
   else
     launch(std::integral_constant<int, 1024>{});
   SGP_LAUNCH_CHECK("k_slice_tile");
-  return SGP_OK;
+  return !cgm || bh.fold ? SGP_OK : launch_cg_scalar(bh, C, s);
 }
 
 // Channel chunk: the widest power of two <= kMaxChunk covering C for which
@@ -1326,6 +1358,8 @@ int mvm_g(const sgp_lattice* L, const TU* V, const uint32_t* perm, int C, TU* ou
 // column's results are the same bit for bit whatever the chunk; more
 // columns take several chunks.
 constexpr int kMaxChunk = 16;
+// LDS of a CU, less the static words of the tile kernels
+constexpr size_t kCgTileLds = 163840 - 2048;
 int chunk_lanes(const sgp_lattice* L, int C, size_t elem) {
   int g = lanes_for(C);
   if (g > kMaxChunk) g = kMaxChunk;
@@ -1369,7 +1403,163 @@ int mvm_dispatch(const sgp_lattice* L, const TU* V, const uint32_t* perm, int C,
   }
 }
 
+
+// ---------------------------------------------------------------------------
+// CG with its vectors on the lattice (cg_tile.h).
+
+struct LatWork {
+  double *yr, *yp, *yx, *u, *b1, *b2, *b3, *b4, *part, *frag;
+};
+LatWork lat_work(const sgp_lattice* L, int C, double* work) {
+  const int64_t mC = L->m * C;
+  LatWork w;
+  double* p = work;
+  for (double** a : {&w.yr, &w.yp, &w.yx, &w.u, &w.b1, &w.b2, &w.b3, &w.b4}) {
+    *a = p;
+    p += mC;
+  }
+  w.part = p;
+  w.frag = p + L->npiece * C;
+  return w;
+}
+
+template <int G, int MODE>
+int cg_tile_launch(const sgp_lattice* L, int C, const CgLat& cl, const CgHook& hook, const double* Y,
+                   const LaunchChoice& lc, hipStream_t s) {
+  const LatWork w = lat_work(L, C, cl.work);
+  CgTileArgs a;
+  a.n = L->n;
+  a.chunks = (C + G - 1) / G;
+  a.items = L->ntiles * a.chunks;
+  a.P = L->tile_points;
+  a.D = L->d + 1;
+  a.C = C;
+  a.mrows = L->solve_rows;
+  a.estride = tile_ent_stride(a.P * a.D);
+  a.lds = cg_tile_lds<G>(L, C);
+  constexpr int NT = cg_tile_threads<G>();
+  const float* b = MODE == CT_FIRST ? cl.rhs : cl.bs;
+  // the library's own arrays are aligned (every one of the m x C arrays where
+  // C is even); the caller's b and x may not be
+  const bool cv = G == 1 || (C % (G < 4 ? G : 4) == 0 && aligned16(cl.work) && aligned16(cl.bs) &&
+                             aligned16(b) && (MODE != CT_OUT || aligned16(cl.x)));
+  CgHook h = hook;
+  auto launch = [&](auto cv_tag) {
+    ProfScope ps(KK_SPLAT, s);
+    constexpr bool CV = decltype(cv_tag)::value;
+    const unsigned grid =
+        persistent_grid((const void*)&k_cg_tile<G, MODE, CV>, NT, a.lds.total, a.items, lc.splat_bpc);
+    h.fold = grid <= kFoldBlocks ? 1 : 0;
+    hipLaunchKernelGGL((k_cg_tile<G, MODE, CV>), dim3(grid), dim3(NT), a.lds.total, s,
+                       (const int32_t*)L->tile_off.ptr, (const int32_t*)L->tile_verts.ptr,
+                       (const uint16_t*)L->loc.ptr, (const float*)L->ws.ptr, (const int32_t*)L->stile_off.ptr,
+                       (const int32_t*)L->tile_ent.ptr, (const uint32_t*)L->slice.ptr,
+                       (const int32_t*)L->run_dst.ptr, (const uint8_t*)L->ent_lp.ptr,
+                       (const float*)L->ent_w.ptr, Y, b, (const uint32_t*)L->perm.ptr, cl.bs, w.part, cl.x,
+                       h, a);
+  };
+  if (cv)
+    launch(std::true_type{});
+  else if constexpr (G > 1)
+    launch(std::false_type{});
+  SGP_LAUNCH_CHECK("k_cg_tile");
+  return MODE == CT_OUT || h.fold ? SGP_OK : launch_cg_scalar(h, C, s);
+}
+
+enum LatStep { LS_START, LS_FIRST, LS_ITER, LS_OUT };
+
+template <int G>
+int lat_cg_g(const sgp_lattice* L, int C, const CgLat& cl, LatStep step, const LaunchChoice& lc, hipStream_t s) {
+  const LatWork w = lat_work(L, C, cl.work);
+  const double* beta = cl.beta.st->beta;
+  int rc;
+  if (step == LS_OUT) return cg_tile_launch<G, CT_OUT>(L, C, cl, cl.beta, w.yx, lc, s);
+  if (step == LS_START) {
+    if ((rc = cg_tile_launch<G, CT_FIRST>(L, C, cl, cl.start, nullptr, lc, s))) return rc;
+    return gather_g<double, G>(L, w.part, w.u, w.frag, C, nullptr, s);
+  }
+  const double* bu = nullptr;
+  if ((rc = blur_g<double, G>(L, w.u, w.b1, w.b2, w.b3, w.b4, C, s, &bu))) return rc;
+  const double scale = (L->blur == SGP_BLUR_SYMMETRIC ? 0.5 : 1.0) * (double)L->outputscale;
+  CgMvm am = {};
+  am.alpha = cl.alpha;
+  am.lat_parts = cl.lat_parts;
+  if ((rc = launch_cg_alpha(w.u, bu, L->m, C, scale, am, s))) return rc;
+  {
+    ProfScope ps(KK_CG_DIR, s);
+    const int64_t total = L->m * C;
+    const int first = step == LS_FIRST ? 1 : 0;
+    const CgState* st = cl.alpha.st;
+    if (C % 2 == 0 && aligned16(cl.work))
+      hipLaunchKernelGGL((k_cg_lattice<2>), dim3(grid_cap(total / 2)), dim3(kBlock), 0, s, bu, w.yr, w.yp,
+                         w.yx, total, C, scale, cl.noise, first, st);
+    else
+      hipLaunchKernelGGL((k_cg_lattice<1>), dim3(grid_cap(total)), dim3(kBlock), 0, s, bu, w.yr, w.yp, w.yx,
+                         total, C, scale, cl.noise, first, st);
+    SGP_LAUNCH_CHECK("k_cg_lattice");
+  }
+  if ((rc = cg_tile_launch<G, CT_ITER>(L, C, cl, cl.beta, w.yr, lc, s))) return rc;
+  return gather_g<double, G>(L, w.part, w.u, w.frag, C, beta, s);
+}
+
+size_t cg_tile_lds_g(const sgp_lattice* L, int C, int g) {
+  switch (g) {
+    case 1: return cg_tile_lds<1>(L, C).total;
+    case 2: return cg_tile_lds<2>(L, C).total;
+    case 4: return cg_tile_lds<4>(L, C).total;
+    case 8: return cg_tile_lds<8>(L, C).total;
+    default: return cg_tile_lds<16>(L, C).total;
+  }
+}
+
+int lat_cg(const sgp_lattice* L, int C, const CgLat& cl, LatStep step, hipStream_t s) {
+  int g = lanes_for(C);
+  if (g > kMaxChunk) g = kMaxChunk;
+  while (g > 1 && cg_tile_lds_g(L, C, g) > kCgTileLds) g >>= 1;
+  LaunchChoice lc{g, 0, 0};
+  (void)tune_find(L, C, (int)sizeof(double), &lc);
+  if (lc.g < 1 || lc.g > g || (lc.g & (lc.g - 1))) lc.g = g;
+  switch (lc.g) {
+    case 1: return lat_cg_g<1>(L, C, cl, step, lc, s);
+    case 2: return lat_cg_g<2>(L, C, cl, step, lc, s);
+    case 4: return lat_cg_g<4>(L, C, cl, step, lc, s);
+    case 8: return lat_cg_g<8>(L, C, cl, step, lc, s);
+    default: return lat_cg_g<16>(L, C, cl, step, lc, s);
+  }
+}
+
 }  // namespace
+
+// Whether a lattice's solves keep their vectors on the lattice. They pay
+// while the m lattice rows are few against the n points: an iteration then
+// moves 80 m C bytes of lattice vectors in place of 52 n C of point vectors,
+// and no more work memory than the point form takes (24 m C against 16 n C
+// bytes, hence 2/3). Measured, point form against lattice form: m / n = 0.07
+// (n = 2M, d = 11, C = 16) 18.36 -> 14.9 ms for a build and 20 iterations;
+// 0.022 (n = 500,000, d = 8, C = 1) 1.79 -> 1.31 ms for 16; 0.44 (n = 2M)
+// equal. Below 4096 lattice points a solve is bound by its launches either
+// way, and its iterates depend on the rounding after about 12 iterations (the
+// Krylov basis loses its orthogonality once the largest eigenvalue has
+// converged), so those keep the point form's arithmetic. The rule depends on
+// the lattice alone, so a column is solved the same way in any batch.
+constexpr int64_t kLatticeCgMin = 4096;
+bool cg_on_lattice(const sgp_lattice* L) {
+  return L->m >= kLatticeCgMin && 3 * L->m <= 2 * L->n && cg_tile_lds_g(L, kMaxCgCols, 1) <= kCgTileLds;
+}
+
+size_t cg_lat_work_elems(const sgp_lattice* L, int C) {
+  return (size_t)(8 * L->m + L->npiece + 2 * gather_ranges(L)) * (size_t)C;
+}
+
+int cg_lat_start(const sgp_lattice* L, int C, const CgLat& cl, hipStream_t s) {
+  return lat_cg(L, C, cl, LS_START, s);
+}
+int cg_lat_iter(const sgp_lattice* L, int C, const CgLat& cl, bool first, hipStream_t s) {
+  return lat_cg(L, C, cl, first ? LS_FIRST : LS_ITER, s);
+}
+int cg_lat_out(const sgp_lattice* L, int C, const CgLat& cl, hipStream_t s) {
+  return lat_cg(L, C, cl, LS_OUT, s);
+}
 
 int mvm_into(const sgp_lattice* L, const float* V, int C, float* out, hipStream_t s) {
   return mvm_dispatch<float>(L, V, (const uint32_t*)L->perm.ptr, C, out, s, 0.f, nullptr);

@@ -246,6 +246,9 @@ int mvm_into(const sgp_lattice* L, const float* V, int C, float* out, hipStream_
 // update, which the splat applies to p (in place) and x before splatting p
 struct CgMvm;
 struct CgDirUpdate;
+struct CgHook;
+// The scalar step of a hook as a one-block launch
+int launch_cg_scalar(const CgHook& h, int C, hipStream_t s);
 // The CG direction update as a pass of its own over the n x C arrays
 int launch_cg_dir(const CgDirUpdate& up, int64_t nC, int C, hipStream_t s);
 // alpha of a CG step from the splatted u, the blurred B u (m x C each) and
@@ -254,6 +257,14 @@ int launch_cg_alpha(const double* u, const double* bu, int64_t m, int C, double 
                     hipStream_t s);
 int mvm_cg(const sgp_lattice* L, double* p, int C, hipStream_t s, double noise, const CgMvm& cg,
            const CgDirUpdate* up);
+// CG with its vectors on the lattice: whether this lattice's solves take it,
+// its work memory in doubles, and its steps (start; one iteration; x out)
+struct CgLat;
+bool cg_on_lattice(const sgp_lattice* L);
+size_t cg_lat_work_elems(const sgp_lattice* L, int C);
+int cg_lat_start(const sgp_lattice* L, int C, const CgLat& cl, hipStream_t s);
+int cg_lat_iter(const sgp_lattice* L, int C, const CgLat& cl, bool first, hipStream_t s);
+int cg_lat_out(const sgp_lattice* L, int C, const CgLat& cl, hipStream_t s);
 // fp64 values and accumulation, internal point order, no epilogue
 int mvm_f64(const sgp_lattice* L, const double* V, int C, double* out, hipStream_t s);
 // fp32 values and accumulation, internal point order

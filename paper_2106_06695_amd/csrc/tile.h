@@ -335,6 +335,120 @@ __device__ __forceinline__ void splat_pieces(const unsigned char* rows, unsigned
   }
 }
 
+// x of the lane N lanes on within the 16-lane row (0 past its end).
+template <int N, typename T>
+__device__ __forceinline__ T row_from(T x) {
+  if constexpr (sizeof(T) == 8) {
+    const long long v = __builtin_bit_cast(long long, x);
+    const int lo = __builtin_amdgcn_mov_dpp((int)v, 0x100 + N, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(v >> 32), 0x100 + N, 0xf, 0xf, true);
+    return __builtin_bit_cast(T, (long long)hi << 32 | (long long)(unsigned)lo);
+  } else {
+    return __builtin_bit_cast(T, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x100 + N, 0xf, 0xf, true));
+  }
+}
+
+// splat_pieces with a piece of more than kShortPiece entries summed by four
+// lane groups, kShortPiece entries each, whose sums are added as (0 + 1) +
+// (2 + 3) (the four groups share a 16-lane row): the wave that holds a tile's
+// longest pieces makes two steps in place of eight and no longer ends last.
+// A batch is a quarter of a long slice (a half, or a whole one, with fewer
+// lanes per piece), or SPW short slices. A piece's sum depends on its entries
+// only, as before.
+template <typename TU, int G, int NT>
+__device__ __forceinline__ void splat_pieces_split(const unsigned char* rows, unsigned char* smem,
+                                                   const SplatLists& l, int nq, TU* part, int C, int c0,
+                                                   bool cvec) {
+  using W = SplatLanes<G>;
+  static_assert(4 * W::LPR <= 16 && 4 * kShortPiece >= kPiece && W::GPW / 4 <= kSlicePieces, "batches of long pieces");
+  constexpr int PPB = W::GPW / 4;            // long pieces per batch
+  constexpr int BPS = kSlicePieces / PPB;    // batches per long slice
+  const int lane = threadIdx.x & 63, g = lane / W::LPR;
+  const int cl = (lane % W::LPR) * W::VW, cg = c0 + cl;
+  const uint32_t* lsl = (const uint32_t*)(smem + l.sl);
+  const int32_t* ldst = (const int32_t*)(smem + l.dst);
+  const uint16_t* loff = (const uint16_t*)(smem + l.off);
+  const float* lw = (const float*)(smem + l.w);
+  const unsigned char* lrows = rows + cl * sizeof(TU);
+  const int ns = (nq + kSlicePieces - 1) / kSlicePieces;
+  int nl = 0;  // long slices, which come first
+  for (int s0 = 0; s0 < ns; s0 += 64) {
+    const int s = s0 + lane;
+    const unsigned long long bal = __ballot(s < ns && (int)(lsl[s < ns ? s : ns - 1] >> 16) > kShortPiece);
+    nl += (int)__popcll(bal);
+    if (bal != ~0ull) break;
+  }
+  const int nbl = nl * BPS;
+  const int nb = nbl + (ns - nl + W::SPW - 1) / W::SPW;
+  int b = NT / 64 - 1 - (int)(threadIdx.x >> 6);
+  while (b < nb) {
+    int nx = 0;
+    if (lane == 0) nx = atomicAdd((int*)(smem + l.next), 1);
+    TU acc[W::VW];
+#pragma unroll
+    for (int i = 0; i < W::VW; ++i) acc[i] = 0;
+    if (b < nbl) {
+      const int s = b / BPS, c = (b % BPS) * PPB + g / 4, off = g % 4 * kShortPiece;
+      const uint32_t sw = __builtin_amdgcn_readfirstlane(lsl[s]);
+      const int m = (int)(sw >> 16) - off;  // a multiple of 4
+      const int e = (int)(sw & 0xffffu) + off * kSlicePieces + c;
+      const int q = s * kSlicePieces + c;
+      const int dq = ldst[q < nq ? q : nq - 1];
+      if (m > 0) splat_step<4>(lrows, loff + e, lw + e, acc);
+      if (m > 4) splat_step<4>(lrows, loff + e + 4 * kSlicePieces, lw + e + 4 * kSlicePieces, acc);
+#pragma unroll
+      for (int i = 0; i < W::VW; ++i) acc[i] += row_from<W::LPR>(acc[i]);
+#pragma unroll
+      for (int i = 0; i < W::VW; ++i) acc[i] += row_from<2 * W::LPR>(acc[i]);
+      if (off == 0 && q < nq) store_piece(part + (int64_t)dq * C + cg, acc, cg, C, cvec);
+    } else {
+      const int s = nl + (b - nbl) * W::SPW + g / kSlicePieces;
+      uint32_t sw = lsl[s < ns ? s : ns - 1];
+      if constexpr (W::SPW == 1) sw = __builtin_amdgcn_readfirstlane(sw);
+      const int m = s < ns ? (int)(sw >> 16) : 0;  // at most kShortPiece
+      const int e = (int)(sw & 0xffffu) + g % kSlicePieces;
+      const int q = s * kSlicePieces + g % kSlicePieces;
+      const int dq = ldst[q < nq ? q : nq - 1];
+      const uint16_t* po = loff + e;
+      const float* pw = lw + e;
+      int k = 0;
+      for (; k + 4 <= m; k += 4, po += 4 * kSlicePieces, pw += 4 * kSlicePieces) splat_step<4>(lrows, po, pw, acc);
+      if (k + 2 <= m) {
+        splat_step<2>(lrows, po, pw, acc);
+        k += 2;
+        po += 2 * kSlicePieces;
+        pw += 2 * kSlicePieces;
+      }
+      if (k < m) splat_step<1>(lrows, po, pw, acc);
+      if (q < nq && m > 0) store_piece(part + (int64_t)dq * C + cg, acc, cg, C, cvec);
+    }
+    b = __builtin_amdgcn_readfirstlane(nx);
+  }
+}
+
+// Sum over the 256 rows of a tile's staged fp64 values of the squares of
+// column c (rows from np on count as zero), for lane blk of a 16-lane row:
+// lane 0 gets the sum. Lane blk adds rows 16 blk + (blk + u) % 16 in turn (16
+// padded rows apart they would share an LDS bank), then the lanes' sums are
+// added pairwise.
+template <int RS>
+__device__ __forceinline__ double tile_sumsq(const double* lv, int blk, int c, int np) {
+  double v = 0.0;
+  asm volatile("" : "+v"(blk));  // keeps the 16 addresses out of the caller's loop-long registers
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    const int q = blk * 16 + ((blk + u) & 15);
+    const double x = lv[q * RS + c];  // rows of an earlier tile are discarded
+    const double y = q < np ? x : 0.0;
+    v = __builtin_fma(y, y, v);
+  }
+  v += row_from<8>(v);
+  v += row_from<4>(v);
+  v += row_from<2>(v);
+  v += row_from<1>(v);
+  return v;
+}
+
 // Sum of squares of column c over rows 16 blk .. 16 blk + 15 (those below
 // np), in row order, of a tile's staged fp64 values.
 template <int RS, typename TU>

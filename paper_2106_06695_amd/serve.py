@@ -83,7 +83,9 @@ def build_peak_bytes(N: int, d: int, order: int = 1) -> int:
 def solve_bytes(N: int, C: int, d: int, m: int) -> int:
     """Solver and MVM work buffers: fp64 lattice values (5 m rows plus at
     most N(d+1) tile-run rows), two fp64 CG vectors and an fp32 one, and
-    the request's own fp32 inputs and outputs."""
+    the request's own fp32 inputs and outputs. A solve whose vectors live on
+    the lattice (m <= 2N/3) takes three more lattice rows and no fp64 point
+    vectors, which is no more."""
     runs = N * (d + 1)
     return int(8 * C * (5 * m + runs) + 20 * N * C + 4 * N * (d + 2 * C + 2) + (16 << 20))
 
