@@ -509,6 +509,79 @@ __global__ __launch_bounds__(kBlock) void k_nbr_internal(const int32_t* __restri
   }
 }
 
+// Chains of lattice points along each direction (three-tap stencil), for the
+// blur in place: maximal runs of neighbours, by length 2, 3, 4 and more (the
+// class), each chain's points together in direction order (only the first for
+// the longest class). Points without a neighbour are in no list: the blur
+// leaves them as they are. Direction k's lists share list[2 k m ..]: pairs
+// upwards from the start, triples downwards from m, quadruples upwards from
+// m, heads of longer chains downwards from 2 m (chains share no point, so
+// neither half overflows). A wave takes kChainSpan consecutive points, so that
+// a list follows the internal numbering in pieces of that size. cnt:
+// [direction][class] counts, then the longest chain met (walked up to
+// kMaxChain).
+constexpr int kChainRounds = 8;
+constexpr int kChainSpan = 64 * kChainRounds;
+__global__ __launch_bounds__(kBlock) void k_chains(const int32_t* __restrict__ nbr, int64_t m, int D,
+                                                   uint32_t* __restrict__ cnt, int32_t* __restrict__ list) {
+  const int k = (int)blockIdx.y, lane = threadIdx.x & 63;
+  const int64_t w = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+  const int64_t j0 = w * kChainSpan;
+  if (j0 >= m) return;
+  const int32_t* nb = nbr + (int64_t)k * m * 2;
+  int len[kChainRounds], longest = 0;
+  int32_t e1[kChainRounds], e2[kChainRounds], e3[kChainRounds];  // the chain's next points
+#pragma unroll
+  for (int i = 0; i < kChainRounds; ++i) {
+    const int64_t j = j0 + i * 64 + lane;
+    const int2 lh = *(const int2*)(nb + 2 * (j < m ? j : m - 1));
+    const bool head = j < m && lh.x < 0 && lh.y >= 0;
+    e1[i] = head ? lh.y : -1;
+  }
+#pragma unroll
+  for (int i = 0; i < kChainRounds; ++i) e2[i] = e1[i] >= 0 ? nb[2 * (int64_t)e1[i] + 1] : -1;
+#pragma unroll
+  for (int i = 0; i < kChainRounds; ++i) e3[i] = e2[i] >= 0 ? nb[2 * (int64_t)e2[i] + 1] : -1;
+#pragma unroll
+  for (int i = 0; i < kChainRounds; ++i) {
+    int32_t nx = e3[i] >= 0 ? nb[2 * (int64_t)e3[i] + 1] : -1;
+    int l = e1[i] < 0 ? 0 : e2[i] < 0 ? 2 : e3[i] < 0 ? 3 : nx < 0 ? 4 : 5;
+    len[i] = l;
+    while (nx >= 0 && l <= kMaxChain) {
+      nx = nb[2 * (int64_t)nx + 1];
+      l += nx >= 0 ? 1 : 0;
+    }
+    longest = l > longest ? l : longest;
+  }
+  int32_t* lk = list + 2 * (int64_t)k * m;
+#pragma unroll
+  for (int c = 0; c < kChainClasses; ++c) {
+    int tot = 0;
+#pragma unroll
+    for (int i = 0; i < kChainRounds; ++i) tot += (int)__popcll(__ballot(len[i] == c + 2));
+    if (tot == 0) continue;
+    uint32_t base = 0;
+    if (lane == 0) base = atomicAdd(cnt + k * kChainClasses + c, (uint32_t)tot);
+    int pos = (int)__shfl(base, 0);
+#pragma unroll
+    for (int i = 0; i < kChainRounds; ++i) {
+      const unsigned long long bal = __ballot(len[i] == c + 2);
+      if (len[i] == c + 2) {
+        const int at = pos + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32),
+                                                            __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0));
+        int32_t* dst = lk + chain_at(c, at, m);
+        dst[0] = (int32_t)(j0 + i * 64 + lane);
+        if (c < 3) dst[1] = e1[i];
+        if (c == 1 || c == 2) dst[2] = e2[i];
+        if (c == 2) dst[3] = e3[i];
+      }
+      pos += (int)__popcll(bal);
+    }
+  }
+  for (int off = 32; off > 0; off >>= 1) longest = max(longest, __shfl_down(longest, off));
+  if (lane == 0 && longest > 0) atomicMax(cnt + D * kChainClasses, (uint32_t)longest);
+}
+
 // ---------------------------------------------------------------------------
 // Tiles of P consecutive sorted points. Within a tile, entries are ordered by
 // (internal lattice point, entry): equal lattice points form a "run" (one
@@ -1165,7 +1238,7 @@ int build_attempt(sgp_lattice* L, const float* X, const double* f, double load_f
   int rc;
   enum {
     T_R0, T_RANK, T_SLOT, T_TAB, T_FIRST, T_COUNTS, T_OFFS, T_WORDS, T_W, T_NBRC,
-    T_SLOTS, T_FIRST2, T_CAN2INT, T_KA, T_KB, T_VA, T_VB, T_SORTTMP, T_PM, T_SUB, T_ORD, T_CNT, T_BITS
+    T_SLOTS, T_FIRST2, T_CAN2INT, T_KA, T_KB, T_VA, T_VB, T_SORTTMP, T_PM, T_SUB, T_ORD, T_CNT, T_BITS, T_CHAIN
   };
   if ((rc = tr.alloc(T_R0, sizeof(int32_t) * n * d))) return rc;
   if ((rc = tr.alloc(T_RANK, sizeof(uint8_t) * n * d))) return rc;
@@ -1267,7 +1340,7 @@ int build_attempt(sgp_lattice* L, const float* X, const double* f, double load_f
   uint32_t* vb = (uint32_t*)tr.ptr[T_VB];
   uint32_t* sort_tmp = (uint32_t*)tr.ptr[T_SORTTMP];
   for (sgp::DevBuf* b : {&L->perm, &L->loc, &L->ws, &L->tile_off, &L->tile_verts, &L->slice, &L->tile_ent,
-                         &L->ent_lp, &L->ent_w, &L->occ_ptr, &L->run_dst, &L->row_vert, &L->stile_off, &L->nbr, &L->int2can})
+                         &L->ent_lp, &L->ent_w, &L->occ_ptr, &L->run_dst, &L->row_vert, &L->stile_off, &L->nbr, &L->chains, &L->int2can})
     dev_free(*b);
   if ((rc = dev_alloc(L->perm, sizeof(uint32_t) * n, st))) return rc;
   // two spare slots: the slice reads slots in aligned pairs
@@ -1412,6 +1485,22 @@ int build_attempt(sgp_lattice* L, const float* X, const double* f, double load_f
                        (int32_t*)L->nbr.ptr);
     SGP_LAUNCH_CHECK("k_nbr_internal");
   }
+  // ---- chains of neighbours, for the blur in place
+  const size_t chain_words = (size_t)D * kChainClasses + 1;
+  const bool chains = L->order == 1 && m >= kChainMin;
+  uint32_t* chain_cnt = nullptr;
+  if (chains) {
+    if ((rc = dev_alloc(L->chains, sizeof(int32_t) * 2 * m * D, st))) return rc;
+    if ((rc = tr.alloc(T_CHAIN, sizeof(uint32_t) * chain_words))) return rc;
+    chain_cnt = (uint32_t*)tr.ptr[T_CHAIN];
+    if ((rc = launch_fill_u32(chain_cnt, chain_words, 0u, st))) return rc;
+    ProfScope ps(KK_NEIGHBORS, st);
+    const int64_t waves = (m + kChainSpan - 1) / kChainSpan;
+    const dim3 grid((unsigned)((waves + kBlock / 64 - 1) / (kBlock / 64)), (unsigned)D);
+    hipLaunchKernelGGL(k_chains, grid, dim3(kBlock), 0, st, (const int32_t*)L->nbr.ptr, m, D, chain_cnt,
+                       (int32_t*)L->chains.ptr);
+    SGP_LAUNCH_CHECK("k_chains");
+  }
   // ---- tiles of consecutive sorted points, their runs, and runs per lattice point
   {
     L->tile_points = P;
@@ -1502,9 +1591,22 @@ int build_attempt(sgp_lattice* L, const float* X, const double* f, double load_f
     }
   }
   SGP_HIP(hipMemcpyAsync(host_word, words, sizeof(uint32_t) * 4, hipMemcpyDeviceToHost, st));
+  if (chains)
+    SGP_HIP(hipMemcpyAsync(host_word + 4, chain_cnt, sizeof(uint32_t) * (D * kChainClasses + 1),
+                           hipMemcpyDeviceToHost, st));
   SGP_HIP(hipStreamSynchronize(st));
   tr.idle = true;  // every kernel of this attempt has finished
   L->max_tile_ents = (int)host_word[3];
+  // a chain longer than 4 points is walked by one lane group: few of them, and
+  // none of them long
+  int64_t nshort = 0, nlong = 0;
+  if (chains)
+    for (int k = 0; k < D; ++k)
+      for (int c = 0; c < kChainClasses; ++c) {
+        L->chain_count[k][c] = (int32_t)host_word[4 + k * kChainClasses + c];
+        (c < kChainClasses - 1 ? nshort : nlong) += L->chain_count[k][c];
+      }
+  L->has_chains = chains && host_word[4 + D * kChainClasses] <= (uint32_t)kMaxChain && 20 * nlong <= nshort;
   if (host_word[0] & BF_ORDER) {
     set_error("lattice_build: internal error, a tile's sorted order is not a permutation");
     return SGP_EHASH;
@@ -1635,7 +1737,8 @@ extern "C" int lattice_build(const float* X, int64_t n, int32_t d, const double*
   for (int j = 0; j < d; ++j) L->ell[j] = lengthscales[j];
 
   int rc = SGP_OK;
-  uint32_t* host_word = (uint32_t*)pinned_scratch(sizeof(uint32_t) * (4 + 2 * kMaxD));
+  uint32_t* host_word = (uint32_t*)pinned_scratch(
+      sizeof(uint32_t) * std::max(4 + 2 * kMaxD, 4 + (kMaxD + 1) * kChainClasses + 1));
   {
     hipError_t e = hipGetDevice(&L->device);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&L->last_use, hipEventDisableTiming);

@@ -29,6 +29,7 @@
 // Row ranges of consecutive blocks go to the same XCD (blocks are dealt
 // round-robin over the 8 XCDs), so tiles that share lattice points share
 // an L2.
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 #include <vector>
@@ -650,6 +651,144 @@ __global__ __launch_bounds__(kBlock) void k_blur2_split(Blur2Args<TU> a) {
   }
 }
 
+// One blur step in place, over the chains of neighbours of its direction
+// (three-tap stencil): a lane group takes a whole chain, reads its rows once,
+// forms every row's step from them as k_blur would (a missing neighbour adds
+// 0) and writes them back. Chains share no point, and a point without a
+// neighbour is left as it is: its step is its own value, since the middle tap
+// is 1. Against the fused pair of steps, which reads nine rows and five index
+// pairs per row of two steps, a row with neighbours is read and written once a
+// step with one index, and a third to two thirds of the rows not at all.
+template <typename TU>
+struct ChainArgs {
+  TU* u[2];                 // chain's array
+  const int32_t* list[2];   // its direction's lists
+  int32_t n[2][kChainClasses];
+  int64_t m;
+  int C;
+  int chain0, halves;       // as in Blur2Args
+  unsigned blocks;          // of one half
+  int vec;
+  TU st[3];
+};
+template <int G, typename TU>
+constexpr int chain_vw() { return G < 16 / (int)sizeof(TU) ? G : 16 / (int)sizeof(TU); }
+// Chains a lane group takes at once, by class: all their rows are in flight
+// together.
+constexpr int chain_items(int cls) { return cls < 2 ? 4 : cls == 2 ? 2 : 1; }
+
+template <typename TU, int VW>
+__device__ __forceinline__ void chain_load(const TU* u, int64_t row, int C, int c, bool vec, TU (&v)[VW]) {
+  const TU* src = u + row * C + c;
+  if (vec) {
+    read_row<TU, VW>(src, v);
+  } else {
+#pragma unroll
+    for (int i = 0; i < VW; ++i) v[i] = c + i < C ? src[i] : (TU)0;
+  }
+}
+// The step of one row from its own value and its neighbours', stored.
+template <typename TU, int VW>
+__device__ __forceinline__ void chain_store(TU* u, int64_t row, int C, int c, bool vec, const TU* st,
+                                            const TU (&lo)[VW], const TU (&v)[VW], const TU (&hi)[VW]) {
+  TU o[VW];
+#pragma unroll
+  for (int i = 0; i < VW; ++i) o[i] = fma_t(st[2], hi[i], fma_t(st[1], v[i], fma_t(st[0], lo[i], (TU)0)));
+  TU* dst = u + row * C + c;
+  if (vec) {
+    write_row<TU, VW>(dst, o);
+  } else {
+#pragma unroll
+    for (int i = 0; i < VW; ++i)
+      if (c + i < C) dst[i] = o[i];
+  }
+}
+// ITEMS chains of N points, from item i of a direction's lists on, R items
+// apart.
+template <int N, int ITEMS, typename TU, int VW>
+__device__ __forceinline__ void chain_steps(TU* u, const int32_t* list, int64_t m, int i, int n, int R, int C, int c,
+                                            bool vec, const TU* st) {
+  int32_t row[ITEMS][N];
+  TU v[ITEMS][N + 2][VW];
+#pragma unroll
+  for (int t = 0; t < ITEMS; ++t) {
+    const int64_t at = chain_at(N - 2, i + t * R < n ? i + t * R : n - 1, m);
+#pragma unroll
+    for (int x = 0; x < N; ++x) row[t][x] = list[at + x];
+  }
+#pragma unroll
+  for (int t = 0; t < ITEMS; ++t) {
+#pragma unroll
+    for (int x = 0; x < N; ++x) chain_load<TU, VW>(u, row[t][x], C, c, vec, v[t][x + 1]);
+#pragma unroll
+    for (int q = 0; q < VW; ++q) v[t][0][q] = v[t][N + 1][q] = 0;
+  }
+#pragma unroll
+  for (int t = 0; t < ITEMS; ++t)
+    if (i + t * R < n) {
+#pragma unroll
+      for (int x = 0; x < N; ++x) chain_store<TU, VW>(u, row[t][x], C, c, vec, st, v[t][x], v[t][x + 1], v[t][x + 2]);
+    }
+}
+
+// A block takes chains of one class.
+template <typename TU, int G>
+__global__ __launch_bounds__(kBlock) void k_blur_chain(const int32_t* __restrict__ nbr0,
+                                                       const int32_t* __restrict__ nbr1, ChainArgs<TU> a) {
+  constexpr int VW = chain_vw<G, TU>();
+  constexpr int LPR = G / VW;
+  constexpr int R = kBlock / LPR;
+  const int half = blockIdx.x >= a.blocks ? 1 : 0;
+  const int ch = a.chain0 + half;
+  TU* u = a.u[ch];
+  const int32_t* list = a.list[ch];
+  int b = (int)xcd_block(blockIdx.x - half * a.blocks, a.blocks);
+  int cls = 0, n = 0;
+  for (; cls < kChainClasses; ++cls) {
+    n = a.n[ch][cls];
+    const int per = R * chain_items(cls), blocks = (n + per - 1) / per;
+    if (b < blocks) break;
+    b -= blocks;
+  }
+  if (cls == kChainClasses) return;  // the other half has more blocks
+  const int i = b * (R * chain_items(cls)) + (int)threadIdx.x / LPR;
+  if (i >= n) return;
+  for (int c = (int)(threadIdx.x % LPR) * VW; c < a.C; c += G) {
+    const bool vec = a.vec && c + VW <= a.C;
+    if (cls == 0) {
+      chain_steps<2, chain_items(0), TU, VW>(u, list, a.m, i, n, R, a.C, c, vec, a.st);
+    } else if (cls == 1) {
+      chain_steps<3, chain_items(1), TU, VW>(u, list, a.m, i, n, R, a.C, c, vec, a.st);
+    } else if (cls == 2) {
+      chain_steps<4, chain_items(2), TU, VW>(u, list, a.m, i, n, R, a.C, c, vec, a.st);
+    } else {
+      // a longer chain: its points follow one another through the neighbour table
+      const int32_t* nb = half ? nbr1 : nbr0;
+      int64_t row = list[chain_at(3, i, a.m)];
+      TU lo[VW], v[VW], hi[VW];
+#pragma unroll
+      for (int x = 0; x < VW; ++x) lo[x] = 0;
+      chain_load<TU, VW>(u, row, a.C, c, vec, v);
+      while (row >= 0) {
+        const int64_t nx = nb[2 * row + 1];
+        if (nx >= 0) {
+          chain_load<TU, VW>(u, nx, a.C, c, vec, hi);
+        } else {
+#pragma unroll
+          for (int x = 0; x < VW; ++x) hi[x] = 0;
+        }
+        chain_store<TU, VW>(u, row, a.C, c, vec, a.st, lo, v, hi);
+        row = nx;
+#pragma unroll
+        for (int x = 0; x < VW; ++x) {
+          lo[x] = v[x];
+          v[x] = hi[x];
+        }
+      }
+    }
+  }
+}
+
 // LDS layout of k_slice_tile: lattice rows [RC][G] (TU; also the CG
 // reduction area) | weights [P*D] (fp32) | slots [P*D] (uint16).
 struct SliceLds {
@@ -1154,7 +1293,7 @@ int blur_g(const sgp_lattice* L, TU* U0, TU* B1, TU* B2, TU* B3, TU* B4, int C, 
   // Infinity Cache): the chains' split launches run one chain after the
   // other (all of chain 0's, then chain 1's), so that a launch's input and
   // output arrays sit in the cache together.
-  const bool seq = fuse && sym && blur_seq_for(4.0 * (double)mC * sizeof(TU));
+  bool seq = fuse && sym && blur_seq_for(4.0 * (double)mC * sizeof(TU));
   std::vector<Blur2Args<TU>> later;  // chain 1's split launches, in order
   auto launch2 = [&](const Blur2Args<TU>& b, unsigned grid) -> int {
     ProfScope ps(KK_BLUR, s);
@@ -1173,10 +1312,70 @@ int blur_g(const sgp_lattice* L, TU* U0, TU* B1, TU* B2, TU* B3, TU* B4, int C, 
     later.clear();
     return SGP_OK;
   };
+  // In place over the chains (all steps but the first two and the last; the
+  // first launch copies out of U0, the last one sums) where an array outgrows
+  // the 32 MiB of the XCDs' L2s together: the fused pair's nine row reads then
+  // miss it. Blur of one MVM, pair against chains: 44 MB (m = 681,000, d = 20,
+  // C = 8, fp64) 652 -> 422 us, 112 MB (m = 874,000, d = 11, C = 16, fp64)
+  // 893 -> 755 us; 18 MB (m = 141,000, d = 11, C = 16, fp64) 140 -> 144 us, 9 MB
+  // (fp32) 87 -> 117 us.
+  const bool in_place = fuse && L->has_chains && d >= 3 && (double)mC * sizeof(TU) > 32.0 * (1 << 20);
+  // In place a launch only touches the chains' own two arrays: one after the
+  // other pays from 256 MiB of them on (112 MB each: 845 against 755 us for
+  // both together; 267 MB each: 3.66 against 3.74 ms).
+  if (in_place) seq = seq && 2.0 * (double)mC * sizeof(TU) > 256.0 * (1 << 20);
+  auto chain_launch = [&](int step, int chain0, int halves, TU* a0, TU* a1) -> int {
+    ChainArgs<TU> b;
+    b.u[0] = a0;
+    b.u[1] = a1;
+    b.m = m;
+    b.C = C;
+    b.chain0 = chain0;
+    b.halves = halves;
+    b.vec = (C % chain_vw<G, TU>() == 0 && aligned16(a0) && aligned16(a1)) ? 1 : 0;
+    for (int t = 0; t < 3; ++t) b.st[t] = a.st[t];
+    const int32_t* nb[2];
+    int64_t most = 0;
+    for (int ch = 0; ch < 2; ++ch) {
+      const int k = kdir(step, ch);
+      nb[ch] = nbr + (int64_t)k * T * m;
+      b.list[ch] = (const int32_t*)L->chains.ptr + 2 * (int64_t)k * m;
+      int64_t tot = 0;
+      for (int q = 0; q < kChainClasses; ++q) {
+        b.n[ch][q] = L->chain_count[k][q];
+        const int per = kBlock / (G / chain_vw<G, TU>()) * chain_items(q);
+        tot += (b.n[ch][q] + per - 1) / per;
+      }
+      if (ch >= chain0 && ch < chain0 + halves) most = std::max(most, tot);
+    }
+    if (most == 0) return SGP_OK;
+    b.blocks = (unsigned)most;
+    ProfScope ps(KK_BLUR, s);
+    hipLaunchKernelGGL((k_blur_chain<TU, G>), dim3(b.blocks * halves), dim3(kBlock), 0, s, nb[chain0],
+                       nb[chain0 + halves - 1], b);
+    SGP_LAUNCH_CHECK("k_blur_chain");
+    return SGP_OK;
+  };
   for (int step = 0; step <= d;) {
+    if (in_place && step == 2) {
+      TU *a0 = (TU*)cur[0], *a1 = a.chains == 2 ? (TU*)cur[1] : (TU*)cur[0];
+      int rc;
+      if (seq) {
+        for (int q = step; q < d; ++q)
+          if ((rc = chain_launch(q, 0, 1, a0, a1))) return rc;
+        if ((rc = flush_later())) return rc;
+        for (int q = step; q < d; ++q)
+          if ((rc = chain_launch(q, 1, 1, a0, a1))) return rc;
+      } else {
+        for (int q = step; q < d; ++q)
+          if ((rc = chain_launch(q, 0, a.chains, a0, a1))) return rc;
+      }
+      step = d;
+      continue;
+    }
     TU* dst0 = next0(cur[0]);
     TU* dst1 = next1(cur[1]);
-    if (fuse && step + 1 <= d) {
+    if (fuse && step + 1 <= d && !(in_place && step == d)) {
       Blur2Args<TU> b2;
       b2.in[0] = cur[0];
       b2.in[1] = cur[1];

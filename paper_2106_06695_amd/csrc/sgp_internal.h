@@ -36,6 +36,21 @@ constexpr int64_t tile_slice0(int64_t first_piece, int64_t tile) {
   return first_piece / kSlicePieces + tile;
 }
 
+// The blur in place (k_blur_chain): lattices of at least kChainMin points
+// (smaller ones reach its 32 MiB of values a chain only in batches of more
+// than 32 fp64 columns) whose chains of neighbours have at most kMaxChain
+// points, and rarely more than 4, keep chain lists, by length 2, 3, 4 and more.
+constexpr int64_t kChainMin = 131072;
+constexpr int kMaxChain = 16;
+constexpr int kChainClasses = 4;
+// Place of item i of class c in a direction's lists of 2 m words.
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+constexpr int64_t chain_at(int c, int64_t i, int64_t m) {
+  return c == 0 ? 2 * i : c == 1 ? m - 3 * (i + 1) : c == 2 ? m + 4 * i : 2 * m - 1 - i;
+}
+
 // Launch-shape knobs of the MVM kernels. Defaults are the measured best on
 // MI355X; SGP_LDS_BUDGET, SGP_SLICE_LDS_BUDGET, SGP_TILE_BLOCKS_PER_CU and
 // SGP_BLUR_SEQ_MIB in the environment override them (read once per process).
@@ -199,6 +214,11 @@ struct sgp_lattice {
   sgp::DevBuf run_dst;    // npiece int32: partial row of each piece; a lattice point's
                           //   pieces occupy rows occ_ptr[j] .. occ_ptr[j+1]-1 in piece order
   sgp::DevBuf nbr;        // (d+1) x m x 2r int32: [direction][internal vertex][offset]
+  // three-tap stencils on large lattices: chains of neighbours along each
+  // direction (k_chains), 2 m int32 a direction, and their counts by class
+  sgp::DevBuf chains;
+  bool has_chains = false;
+  int32_t chain_count[sgp::kMaxD + 1][sgp::kChainClasses] = {};
   sgp::DevBuf int2can;    // m int32: internal vertex -> canonical index
   sgp::DevBuf keys;       // m x d int32 in canonical order (first occurrence in caller's order)
 

@@ -73,11 +73,11 @@ def build_peak_bytes(N: int, d: int, order: int = 1) -> int:
     transient hash tables (load factor 1/2) and sort buffers included, with
     every vertex distinct. Per splat entry (N(d+1) of them): 48 bytes of hash
     table, 12 of slots and unsorted entries, about 40 of sort and order
-    buffers, 27 of the kept structure, 4 d of keys and 8 order (d+1) of
-    neighbour table."""
+    buffers, 35 of the kept structure, 4 d of keys, 8 order (d+1) of
+    neighbour table and, for order 1, 8 (d+1) of chain lists."""
     D = d + 1
     L = N * D
-    return int((128 + 4 * d + 8 * order * D) * L + 8 * N * d + (64 << 20))
+    return int((136 + 4 * d + 8 * (order + (order == 1)) * D) * L + 8 * N * d + (64 << 20))
 
 
 def solve_bytes(N: int, C: int, d: int, m: int) -> int:
