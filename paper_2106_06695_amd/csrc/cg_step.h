@@ -89,6 +89,52 @@ struct CgLat {
 
 constexpr int kFold = 64;  // fixed fold width: the order depends on nparts only
 
+// One step of the scalar recurrence of column cc, from the folded sum v.
+__device__ inline void cg_scalar_column(CgState* st, int cc, int mode, double tol, double noise, double v) {
+  if (mode == SM_START) {
+    st->rr[cc] = v;
+    st->bnorm[cc] = sqrt(v);
+    st->active[cc] = v > 0.0 ? 1 : 0;
+    st->iters[cc] = 0;
+    st->rel[cc] = v > 0.0 ? 1.f : 0.f;
+    st->alpha[cc] = 0.0;
+    st->beta[cc] = 0.0;
+    st->rho[cc] = 1.0;
+    st->pi[cc] = 1.0;
+    st->xi[cc] = 0.0;
+    st->pp[cc] = v;
+  } else if (mode == SM_ALPHA || mode == SM_ALPHA_LAT) {
+    if (mode == SM_ALPHA_LAT) v = __builtin_fma(noise, st->pp[cc], v);
+    if (st->active[cc] && v > 0.0) {
+      const double al = st->rr[cc] / v;
+      st->alpha[cc] = al;
+      st->xi[cc] = __builtin_fma(al, st->pi[cc], st->xi[cc]);
+      st->rho[cc] = __builtin_fma(-al * noise, st->pi[cc], st->rho[cc]);
+    } else {
+      st->alpha[cc] = 0.0;
+      st->active[cc] = 0;  // converged, or breakdown (p.Ap <= 0)
+    }
+  } else {
+    if (st->active[cc]) {
+      st->iters[cc] += 1;
+      const double rel = sqrt(v) / st->bnorm[cc];
+      st->rel[cc] = (float)rel;
+      if (rel <= tol) {
+        st->active[cc] = 0;
+        st->beta[cc] = 0.0;
+      } else {
+        const double be = v / st->rr[cc];
+        st->beta[cc] = be;
+        st->rr[cc] = v;
+        st->pp[cc] = __builtin_fma(be * be, st->pp[cc], v);
+        st->pi[cc] = __builtin_fma(be, st->pi[cc], st->rho[cc]);
+      }
+    } else {
+      st->beta[cc] = 0.0;
+    }
+  }
+}
+
 // Sum the nparts partial rows of each column in a fixed order and apply one
 // step of the scalar recurrence. Pair (g, c) sums rows g, g + kFold, ... of
 // column c; one thread per column folds the kFold sums in order. Called by
@@ -115,49 +161,7 @@ __device__ inline void cg_scalar_block(const double* partials, int64_t nparts, i
   if (tid < C) {
     double v = 0.0;
     for (int gg = 0; gg < kFold; ++gg) v += sh[gg * C + tid];
-    const int cc = tid;
-    if (mode == SM_START) {
-      st->rr[cc] = v;
-      st->bnorm[cc] = sqrt(v);
-      st->active[cc] = v > 0.0 ? 1 : 0;
-      st->iters[cc] = 0;
-      st->rel[cc] = v > 0.0 ? 1.f : 0.f;
-      st->alpha[cc] = 0.0;
-      st->beta[cc] = 0.0;
-      st->rho[cc] = 1.0;
-      st->pi[cc] = 1.0;
-      st->xi[cc] = 0.0;
-      st->pp[cc] = v;
-    } else if (mode == SM_ALPHA || mode == SM_ALPHA_LAT) {
-      if (mode == SM_ALPHA_LAT) v = __builtin_fma(noise, st->pp[cc], v);
-      if (st->active[cc] && v > 0.0) {
-        const double al = st->rr[cc] / v;
-        st->alpha[cc] = al;
-        st->xi[cc] = __builtin_fma(al, st->pi[cc], st->xi[cc]);
-        st->rho[cc] = __builtin_fma(-al * noise, st->pi[cc], st->rho[cc]);
-      } else {
-        st->alpha[cc] = 0.0;
-        st->active[cc] = 0;  // converged, or breakdown (p.Ap <= 0)
-      }
-    } else {
-      if (st->active[cc]) {
-        st->iters[cc] += 1;
-        const double rel = sqrt(v) / st->bnorm[cc];
-        st->rel[cc] = (float)rel;
-        if (rel <= tol) {
-          st->active[cc] = 0;
-          st->beta[cc] = 0.0;
-        } else {
-          const double be = v / st->rr[cc];
-          st->beta[cc] = be;
-          st->rr[cc] = v;
-          st->pp[cc] = __builtin_fma(be * be, st->pp[cc], v);
-          st->pi[cc] = __builtin_fma(be, st->pi[cc], st->rho[cc]);
-        }
-      } else {
-        st->beta[cc] = 0.0;
-      }
-    }
+    cg_scalar_column(st, tid, mode, tol, noise, v);
   }
 }
 

@@ -36,6 +36,7 @@
 
 #include "cg_step.h"
 #include "cg_tile.h"
+#include "lattice_col.h"
 #include "sgp_internal.h"
 #include "tile.h"
 
@@ -1234,9 +1235,11 @@ size_t mvm_work_elems(const sgp_lattice* L, int C, bool cg) {
 }
 
 // U0 = the partial rows summed per lattice point (+ beta U0 per column when
-// beta is given: device array, fp64 only).
+// beta is given: device array, fp64 only). fix: points whose rows span ranges
+// are finished here (else k_lattice_col does that).
 template <typename TU, int G>
-int gather_g(const sgp_lattice* L, const TU* part, TU* U0, TU* frag, int C, const double* beta, hipStream_t s) {
+int gather_g(const sgp_lattice* L, const TU* part, TU* U0, TU* frag, int C, const double* beta, bool fix,
+             hipStream_t s) {
   ProfScope ps(KK_SPLAT_GATHER, s);
   const int R = gather_rows(L);
   const int64_t ngroups = gather_ranges(L);
@@ -1251,11 +1254,51 @@ int gather_g(const sgp_lattice* L, const TU* part, TU* U0, TU* frag, int C, cons
                        (const int32_t*)L->row_vert.ptr, part, U0, frag, L->npiece, C, ngroups, R, beta);
   }
   SGP_LAUNCH_CHECK("k_splat_gather");
+  if (!fix) return SGP_OK;
   hipLaunchKernelGGL(k_gather_fix, dim3(grid_cap(ngroups * C)), dim3(kBlock), 0, s,
                      (const int32_t*)L->row_vert.ptr, (const int32_t*)L->occ_ptr.ptr, (const void*)frag,
                      (void*)U0, ngroups, C, (int)sizeof(TU), R, beta);
   SGP_LAUNCH_CHECK("k_gather_fix");
   return SGP_OK;
+}
+
+// Whether an MVM's lattice part runs as one block per column: a three-tap
+// lattice of up to 2,048 points and (inside CG) few partial sums of p.Ap. Its
+// launches (the fix-up, a launch per two directions, alpha and its fold) are
+// then one, which they are too short to fill. Here | separate launches, one
+// MVM and ten CG iterations, C = 1 and 8: m = 851 (d = 3) 33 us, 327 us;
+// 34, 342 | 39, 419; 41, 461. m = 1,460 (d = 6) 39, 404; 42, 441 | 64, 512;
+// 63, 570. Beyond, one CU per column takes longer than the launches that it
+// saves: with four rows a thread, m = 4,453 (d = 6) 55, 571; 63, 651 |
+// 66, 503; 68, 571. No rule on the columns: each has a CU for itself.
+bool col_path(const sgp_lattice* L, int64_t parts) {
+  return L->order == 1 && L->m <= kColRows && parts <= kColParts && blur_fuse_enabled();
+}
+
+template <typename TU, int MODE>
+int col_launch(const sgp_lattice* L, TU* U, const TU* frag, TU* Bu, int C, double scale, const CgMvm& cgm,
+               hipStream_t s) {
+  ColArgs a = {};
+  a.m = (int)L->m;
+  a.C = C;
+  a.D = L->d + 1;
+  while ((1 << a.rshift) < gather_rows(L)) ++a.rshift;
+  a.first = L->blur != SGP_BLUR_REVERSE ? 1 : 0;
+  a.rev = L->blur != SGP_BLUR_FORWARD ? 1 : 0;
+  a.lat_parts = MODE == CM_CG ? (int)cgm.lat_parts : 0;
+  a.ntiles = MODE == CM_CG ? (int)cgm.ntiles : 0;
+  a.scale = scale;
+  for (int t = 0; t < 3; ++t) a.st[t] = L->stencil64[t];
+  const size_t lds = col_lds<TU, MODE>(a);
+  auto launch = [&](auto nr_tag) -> int {
+    ProfScope ps(KK_BLUR, s);
+    hipLaunchKernelGGL((k_lattice_col<TU, decltype(nr_tag)::value, MODE>), dim3((unsigned)C), dim3(kColThreads), lds,
+                       s, U, frag, (const int32_t*)L->occ_ptr.ptr, (const int32_t*)L->nbr.ptr, Bu, cgm.pp, cgm.alpha,
+                       a);
+    SGP_LAUNCH_CHECK("k_lattice_col");
+    return SGP_OK;
+  };
+  return a.m <= kColThreads ? launch(std::integral_constant<int, 1>{}) : launch(std::integral_constant<int, 2>{});
 }
 
 // The blur of U0 (m x C): B1 .. B4 are work arrays (B4 may be U0 where it need
@@ -1496,12 +1539,23 @@ int mvm_g(const sgp_lattice* L, const TU* V, const uint32_t* perm, int C, TU* ou
                          (const float*)L->ent_w.ptr, V, perm, part, pp, sa, CgDirUpdate{});
     SGP_LAUNCH_CHECK("k_splat_tile");
   }
-  if (const int rc = gather_g<TU, G>(L, part, U0, frag, C, nullptr, s)) return rc;
-  const TU* blurred = nullptr;
-  if (const int rc = blur_g<TU, G>(L, U0, B1, B2, B3, B4, C, s, &blurred)) return rc;
+  const bool col = col_path(L, cgm ? cgm->alpha.nparts : 0);
+  if (const int rc = gather_g<TU, G>(L, part, U0, frag, C, nullptr, !col, s)) return rc;
+  const TU* blurred = B1;
   const bool sym = L->blur == SGP_BLUR_SYMMETRIC;
   const TU scale = sym ? (TU)(0.5 * (double)L->outputscale) : (TU)L->outputscale;
-  if (cgm) {
+  if (col) {
+    int rc;
+    if constexpr (sizeof(TU) == 8)
+      rc = cgm ? col_launch<TU, CM_CG>(L, U0, frag, B1, C, (double)scale, *cgm, s)
+               : col_launch<TU, CM_MVM>(L, U0, frag, B1, C, 0.0, CgMvm{}, s);
+    else
+      rc = col_launch<TU, CM_MVM>(L, U0, frag, B1, C, 0.0, CgMvm{}, s);
+    if (rc) return rc;
+  } else if (const int rc = blur_g<TU, G>(L, U0, B1, B2, B3, B4, C, s, &blurred)) {
+    return rc;
+  }
+  if (cgm && !col) {
     // alpha from p.Ap = scale * u.(B u) + noise * p.p, before the slice
     const int rc = launch_cg_alpha((const double*)U0, (const double*)blurred, m, C, (double)scale, *cgm, s);
     if (rc) return rc;
@@ -1675,7 +1729,7 @@ int lat_cg_g(const sgp_lattice* L, int C, const CgLat& cl, LatStep step, const L
   if (step == LS_OUT) return cg_tile_launch<G, CT_OUT>(L, C, cl, cl.beta, w.yx, lc, s);
   if (step == LS_START) {
     if ((rc = cg_tile_launch<G, CT_FIRST>(L, C, cl, cl.start, nullptr, lc, s))) return rc;
-    return gather_g<double, G>(L, w.part, w.u, w.frag, C, nullptr, s);
+    return gather_g<double, G>(L, w.part, w.u, w.frag, C, nullptr, true, s);
   }
   const double* bu = nullptr;
   if ((rc = blur_g<double, G>(L, w.u, w.b1, w.b2, w.b3, w.b4, C, s, &bu))) return rc;
@@ -1698,7 +1752,7 @@ int lat_cg_g(const sgp_lattice* L, int C, const CgLat& cl, LatStep step, const L
     SGP_LAUNCH_CHECK("k_cg_lattice");
   }
   if ((rc = cg_tile_launch<G, CT_ITER>(L, C, cl, cl.beta, w.yr, lc, s))) return rc;
-  return gather_g<double, G>(L, w.part, w.u, w.frag, C, beta, s);
+  return gather_g<double, G>(L, w.part, w.u, w.frag, C, beta, true, s);
 }
 
 size_t cg_tile_lds_g(const sgp_lattice* L, int C, int g) {
