@@ -539,7 +539,7 @@ int lattice_info(const sgp_lattice* L, int64_t* n, int32_t* d, int64_t* m, int64
   if (device_bytes)
     *device_bytes = (int64_t)(L->perm.bytes + L->loc.bytes + L->ws.bytes + L->tile_off.bytes + L->stile_off.bytes +
                               L->tile_verts.bytes + L->slice.bytes + L->tile_ent.bytes + L->ent_lp.bytes + L->ent_w.bytes +
-                              L->occ_ptr.bytes + L->run_dst.bytes + L->row_vert.bytes + L->nbr.bytes + L->chains.bytes + L->int2can.bytes +
+                              L->occ_ptr.bytes + L->run_dst.bytes + L->row_vert.bytes + L->nbr.bytes + L->group_rows.bytes + L->int2can.bytes +
                               L->keys.bytes + L->ubuf.bytes + L->cgvec.bytes + L->cgred.bytes);
   return SGP_OK;
 }
@@ -603,7 +603,7 @@ void lattice_free(sgp_lattice* L) {
   // failed build frees its lattice on the way out and reports its own error
   if (L->last_use) (void)hipEventSynchronize(L->last_use);
   for (DevBuf* b : {&L->perm, &L->loc, &L->ws, &L->tile_off, &L->stile_off, &L->tile_verts, &L->slice, &L->tile_ent,
-                   &L->ent_lp, &L->ent_w, &L->occ_ptr, &L->run_dst, &L->row_vert, &L->nbr, &L->chains, &L->int2can, &L->keys})
+                   &L->ent_lp, &L->ent_w, &L->occ_ptr, &L->run_dst, &L->row_vert, &L->nbr, &L->group_rows, &L->int2can, &L->keys})
     dev_free(*b);
   dev_free(L->ubuf);
   dev_free(L->cgvec);

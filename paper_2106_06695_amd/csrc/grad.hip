@@ -181,13 +181,13 @@ extern "C" int lattice_mvm_grad(const sgp_lattice* L, const float* X, const floa
   } guard{bufs, s};
   const int kb = std::max(1, std::min((int)C, 128 / CH));  // columns per batch
   // channels per MVM: all of a batch's, unless the lattice arrays of m x W
-  // fp32 would be large. The blur in place reads and writes each row once a
-  // step, so that rows of at least 64 bytes (W = 16) use whole cache lines,
-  // whatever the arrays' size: m = 4.2M, d = 16, 8 columns 137, 94 and 115 ms
-  // with W = 8, 16 and 32. Without chain lists the fused pairs want the two
-  // arrays near the 256 MiB Infinity Cache.
+  // fp32 would be large. The blur by groups reads and writes each row once a
+  // group, so that rows of at least 64 bytes (W = 16) pay, whatever the arrays'
+  // size: m = 4.2M, d = 16, 8 columns: blur and gather of a pass 31 and
+  // 6.7 ms with W = 16, 30 and 10 ms with W = 32. Without groups the fused pairs
+  // want the two arrays near the 256 MiB Infinity Cache.
   int W = 64;
-  while (W > (L->has_chains ? 16 : 4) && 2.0 * (double)L->m * W * sizeof(float) > 320.0 * (1 << 20)) W >>= 1;
+  while (W > (L->ngroups ? 16 : 4) && 2.0 * (double)L->m * W * sizeof(float) > 320.0 * (1 << 20)) W >>= 1;
   if (W >= kb * CH) W = kb * CH;
   const int nblk_max = (kb * CH + W - 1) / W;
   const size_t hbytes = sizeof(float) * (size_t)n * nblk_max * W;

@@ -1,0 +1,234 @@
+// Groups of blur directions (three-tap stencil): for up to kGroupDirs
+// consecutive directions, the lattice points that are connected through
+// neighbours along them (a part) are brought together in tiles of kGroupRows
+// rows, so that the blur takes the whole group of directions in one pass
+// (k_blur_group). A point set of bounded extent has few points per part: four
+// directions join at most 132 of them at m = 141,000 (d = 11), 189 at
+// m = 874,000 (d = 11), 166 at m = 4.2M (d = 16). To find and place them takes
+// 0.1 ms of a build at m = 141,000 (d = 11), 0.4 ms at 681,000 (d = 20), 3.0 ms
+// at 4.2M (d = 16), random accesses to the roots; a blur there gains 0.1, 0.3
+// and 2 ms.
+#ifndef SGP_GROUPS_H
+#define SGP_GROUPS_H
+#include <hip/hip_runtime.h>
+
+#include "sgp_internal.h"
+
+namespace sgp {
+namespace {
+
+// Parts are kept by size class, so that tiles fill without a search: sizes
+// 1 .. 15 have a class each, larger ones share the class of as many parts a
+// tile (15 .. 1). A tile's last row stays empty.
+__host__ __device__ constexpr int group_class(int size) { return size <= 15 ? size - 1 : 30 - kGroupPart / size; }
+__host__ __device__ constexpr int group_per_tile(int c) { return c < 15 ? kGroupPart / (c + 1) : 30 - c; }
+__host__ __device__ constexpr int group_stride(int c) { return c < 15 ? c + 1 : kGroupPart / (30 - c); }
+
+struct GroupSpec {
+  int first[kMaxGroups], dirs[kMaxGroups];
+  int skip[kMaxGroups];       // parts known already
+  int64_t tile0[kMaxGroups];  // first tile
+};
+
+// The root of x: every entry points to a smaller index or, at a root, to
+// itself. Other threads join roots meanwhile; a value read too early is still
+// one of x's ancestors. HALVE shortens the path on the way.
+template <bool HALVE>
+__device__ __forceinline__ int32_t group_find(int32_t* parent, int32_t x) {
+  int32_t p = parent[x];
+  while (p != x) {
+    const int32_t g = parent[p];
+    if (HALVE && g != p) parent[x] = g;
+    x = p;
+    p = g;
+  }
+  return x;
+}
+
+// parent = the smallest of a point and its neighbours along the group;
+// also clears the sizes and the class counts.
+__global__ __launch_bounds__(256) void k_group_init(const int32_t* __restrict__ nbr, int64_t m, GroupSpec sp,
+                                                    int32_t* __restrict__ parent, int32_t* __restrict__ info,
+                                                    uint32_t* __restrict__ cnt) {
+  const int g = (int)blockIdx.y;
+  if (sp.skip[g]) return;
+  if (blockIdx.x == 0 && threadIdx.x < kGroupWords) cnt[g * kGroupWords + threadIdx.x] = 0;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < m; j += stride) {
+    int32_t p = (int32_t)j;
+#pragma unroll
+    for (int t = 0; t < kGroupDirs; ++t)
+      if (t < sp.dirs[g]) {
+        const int2 lh = ((const int2*)nbr)[(int64_t)(sp.first[g] + t) * m + j];
+        if (lh.x >= 0 && lh.x < p) p = lh.x;
+        if (lh.y >= 0 && lh.y < p) p = lh.y;
+      }
+    parent[g * m + j] = p;
+    info[g * m + j] = 0;
+  }
+}
+
+// Join the two ends of every neighbour pair. A root is only ever linked to a
+// smaller index, by compare-and-swap, so every loop here goes strictly down
+// and ends.
+__global__ __launch_bounds__(256) void k_group_join(const int32_t* __restrict__ nbr, int64_t m, GroupSpec sp,
+                                                    int32_t* __restrict__ parents) {
+  const int g = (int)blockIdx.y;
+  if (sp.skip[g]) return;
+  int32_t* parent = parents + g * m;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < m; j += stride) {
+    int32_t hi[kGroupDirs];
+#pragma unroll
+    for (int t = 0; t < kGroupDirs; ++t)
+      hi[t] = t < sp.dirs[g] ? nbr[2 * ((int64_t)(sp.first[g] + t) * m + j) + 1] : -1;
+    int32_t a = (int32_t)j;
+#pragma unroll
+    for (int t = 0; t < kGroupDirs; ++t) {
+      if (hi[t] < 0) continue;
+      a = group_find<true>(parent, a);
+      int32_t b = group_find<true>(parent, hi[t]);
+      while (a != b) {
+        if (a < b) {
+          const int32_t x = a;
+          a = b;
+          b = x;
+        }
+        const int32_t old = (int32_t)atomicCAS((uint32_t*)parent + a, (uint32_t)a, (uint32_t)b);
+        if (old == a) break;
+        a = group_find<true>(parent, old);
+      }
+      a = a < b ? a : b;
+    }
+  }
+}
+
+// Every point's root, its place among the part's points, and the part's size
+// (in info, at the root). Points of a wave with its first lane's root are
+// counted together: a part of a lattice without gaps may hold every point.
+__global__ __launch_bounds__(256) void k_group_count(int64_t m, GroupSpec sp, int32_t* __restrict__ parents,
+                                                     int32_t* __restrict__ infos, int32_t* __restrict__ place) {
+  if (sp.skip[blockIdx.y]) return;
+  const int64_t at = blockIdx.y * m;
+  int32_t* parent = parents + at;
+  int32_t* info = infos + at;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  const int lane = threadIdx.x & 63;
+  for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < m; j += stride) {
+    const int32_t r = group_find<false>(parent, (int32_t)j);
+    parent[j] = r;  // the only store here: a late one of an ancestor would undo it
+    const int32_t r0 = __builtin_amdgcn_readfirstlane(r);
+    const unsigned long long same = __ballot(r == r0);
+    const int lead = (int)__ffsll(same) - 1;
+    int before = 0;
+    if (r == r0)
+      before = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(same >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)same, 0));
+    int base = 0;
+    if (r != r0 || lane == lead) base = atomicAdd(info + r, r == r0 ? (int)__popcll(same) : 1);
+    const int base0 = __shfl(base, lead);
+    place[at + j] = (r == r0 ? base0 : base) + before;
+  }
+}
+
+// Number the parts within their size classes: at a root, info becomes
+// (number << 5) | class. cnt: a group's parts by class, then the largest.
+constexpr int kGroupSpan = 8;
+__global__ __launch_bounds__(256) void k_group_class(int64_t m, GroupSpec sp, const int32_t* __restrict__ parents,
+                                                     int32_t* __restrict__ infos, uint32_t* __restrict__ cnts) {
+  __shared__ uint32_t hist[kGroupClasses], first[kGroupClasses];
+  __shared__ int largest;
+  if (sp.skip[blockIdx.y]) return;
+  const int64_t at = blockIdx.y * m;
+  uint32_t* cnt = cnts + blockIdx.y * kGroupWords;
+  const int tid = threadIdx.x;
+  if (tid < kGroupClasses) hist[tid] = 0;
+  if (tid == 0) largest = 0;
+  __syncthreads();
+  int cls[kGroupSpan];
+  uint32_t num[kGroupSpan];
+#pragma unroll
+  for (int i = 0; i < kGroupSpan; ++i) {
+    const int64_t j = ((int64_t)blockIdx.x * kGroupSpan + i) * 256 + tid;
+    cls[i] = -1;
+    num[i] = 0;
+    if (j < m && parents[at + j] == (int32_t)j) {
+      const int size = infos[at + j];
+      cls[i] = group_class(size < kGroupPart ? size : kGroupPart);
+      if (size > kGroupRows / 2) atomicMax(&largest, size);
+      num[i] = atomicAdd(&hist[cls[i]], 1u);
+    }
+  }
+  __syncthreads();
+  if (tid < kGroupClasses) first[tid] = hist[tid] ? atomicAdd(cnt + tid, hist[tid]) : 0u;
+  if (tid == 0 && largest) atomicMax(cnt + kGroupClasses, (uint32_t)largest);
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kGroupSpan; ++i)
+    if (cls[i] >= 0) {
+      const int64_t j = ((int64_t)blockIdx.x * kGroupSpan + i) * 256 + tid;
+      infos[at + j] = (int32_t)(((first[cls[i]] + num[i]) << 5) | (uint32_t)cls[i]);
+    }
+}
+
+// Tiles of a group's classes before class c.
+__host__ __device__ inline int64_t group_tiles(const uint32_t* cnt, int c) {
+  int64_t t = 0;
+  for (int i = 0; i < c; ++i) {
+    const uint32_t q = (uint32_t)group_per_tile(i);
+    t += (cnt[i] + q - 1) / q;
+  }
+  return t;
+}
+
+// Each point's row in the group's tiles. No part has more than kGroupPart
+// points.
+__global__ __launch_bounds__(256) void k_group_place(int64_t m, const int32_t* __restrict__ parents,
+                                                     const int32_t* __restrict__ infos,
+                                                     const uint32_t* __restrict__ cnts, int32_t* __restrict__ place) {
+  __shared__ uint32_t cnt[kGroupClasses];
+  __shared__ int32_t tile[kGroupClasses];
+  const int g = (int)blockIdx.y;
+  const int64_t at = g * m;
+  if (threadIdx.x < kGroupClasses) cnt[threadIdx.x] = cnts[g * kGroupWords + threadIdx.x];
+  __syncthreads();
+  if (threadIdx.x < kGroupClasses) tile[threadIdx.x] = (int32_t)group_tiles(cnt, threadIdx.x);
+  __syncthreads();
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < m; j += stride) {
+    const uint32_t inf = (uint32_t)infos[at + parents[at + j]];
+    const int c = (int)(inf & 31);
+    const uint32_t i = inf >> 5, q = (uint32_t)group_per_tile(c);
+    place[at + j] +=
+        (tile[c] + (int32_t)(i / q)) * kGroupRows + (int32_t)(i % q) * group_stride(c);
+  }
+}
+
+// The rows' records: the lattice point, and its neighbours within the tile, a
+// byte each: (low, high) per direction, the tile's empty row where there is
+// none. Rows without a point keep all bits set.
+__global__ __launch_bounds__(256) void k_group_rows(const int32_t* __restrict__ nbr, int64_t m, GroupSpec sp,
+                                                    const int32_t* __restrict__ places,
+                                                    GroupRow* __restrict__ rows) {
+  const int g = (int)blockIdx.y;
+  const int32_t* place = places + g * m;
+  GroupRow* out = rows + sp.tile0[g] * kGroupRows;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < m; j += stride) {
+    int2 lh[kGroupDirs];
+#pragma unroll
+    for (int t = 0; t < kGroupDirs; ++t)
+      lh[t] = t < sp.dirs[g] ? ((const int2*)nbr)[(int64_t)(sp.first[g] + t) * m + j] : int2{-1, -1};
+    uint32_t s[2] = {0u, 0u};
+#pragma unroll
+    for (int t = 0; t < kGroupDirs; ++t) {
+      const uint32_t lo = lh[t].x >= 0 ? (uint32_t)place[lh[t].x] % kGroupRows : kGroupRows - 1;
+      const uint32_t hi = lh[t].y >= 0 ? (uint32_t)place[lh[t].y] % kGroupRows : kGroupRows - 1;
+      s[t >> 1] |= (lo | hi << 8) << (16 * (t & 1));
+    }
+    out[place[j]] = GroupRow{(int32_t)j, s[0], s[1]};
+  }
+}
+
+}  // namespace
+}  // namespace sgp
+#endif  // SGP_GROUPS_H

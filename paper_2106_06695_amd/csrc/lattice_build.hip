@@ -32,6 +32,7 @@
 #include <mutex>
 #include <vector>
 
+#include "groups.h"
 #include "sgp_internal.h"
 
 namespace sgp {
@@ -507,79 +508,6 @@ __global__ __launch_bounds__(kBlock) void k_nbr_internal(const int32_t* __restri
     const int32_t nb = nbr_can[(k * T + ti) * m + int2can[j]];
     nbr_int[g] = nb >= 0 ? can2int[nb] : -1;
   }
-}
-
-// Chains of lattice points along each direction (three-tap stencil), for the
-// blur in place: maximal runs of neighbours, by length 2, 3, 4 and more (the
-// class), each chain's points together in direction order (only the first for
-// the longest class). Points without a neighbour are in no list: the blur
-// leaves them as they are. Direction k's lists share list[2 k m ..]: pairs
-// upwards from the start, triples downwards from m, quadruples upwards from
-// m, heads of longer chains downwards from 2 m (chains share no point, so
-// neither half overflows). A wave takes kChainSpan consecutive points, so that
-// a list follows the internal numbering in pieces of that size. cnt:
-// [direction][class] counts, then the longest chain met (walked up to
-// kMaxChain).
-constexpr int kChainRounds = 8;
-constexpr int kChainSpan = 64 * kChainRounds;
-__global__ __launch_bounds__(kBlock) void k_chains(const int32_t* __restrict__ nbr, int64_t m, int D,
-                                                   uint32_t* __restrict__ cnt, int32_t* __restrict__ list) {
-  const int k = (int)blockIdx.y, lane = threadIdx.x & 63;
-  const int64_t w = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
-  const int64_t j0 = w * kChainSpan;
-  if (j0 >= m) return;
-  const int32_t* nb = nbr + (int64_t)k * m * 2;
-  int len[kChainRounds], longest = 0;
-  int32_t e1[kChainRounds], e2[kChainRounds], e3[kChainRounds];  // the chain's next points
-#pragma unroll
-  for (int i = 0; i < kChainRounds; ++i) {
-    const int64_t j = j0 + i * 64 + lane;
-    const int2 lh = *(const int2*)(nb + 2 * (j < m ? j : m - 1));
-    const bool head = j < m && lh.x < 0 && lh.y >= 0;
-    e1[i] = head ? lh.y : -1;
-  }
-#pragma unroll
-  for (int i = 0; i < kChainRounds; ++i) e2[i] = e1[i] >= 0 ? nb[2 * (int64_t)e1[i] + 1] : -1;
-#pragma unroll
-  for (int i = 0; i < kChainRounds; ++i) e3[i] = e2[i] >= 0 ? nb[2 * (int64_t)e2[i] + 1] : -1;
-#pragma unroll
-  for (int i = 0; i < kChainRounds; ++i) {
-    int32_t nx = e3[i] >= 0 ? nb[2 * (int64_t)e3[i] + 1] : -1;
-    int l = e1[i] < 0 ? 0 : e2[i] < 0 ? 2 : e3[i] < 0 ? 3 : nx < 0 ? 4 : 5;
-    len[i] = l;
-    while (nx >= 0 && l <= kMaxChain) {
-      nx = nb[2 * (int64_t)nx + 1];
-      l += nx >= 0 ? 1 : 0;
-    }
-    longest = l > longest ? l : longest;
-  }
-  int32_t* lk = list + 2 * (int64_t)k * m;
-#pragma unroll
-  for (int c = 0; c < kChainClasses; ++c) {
-    int tot = 0;
-#pragma unroll
-    for (int i = 0; i < kChainRounds; ++i) tot += (int)__popcll(__ballot(len[i] == c + 2));
-    if (tot == 0) continue;
-    uint32_t base = 0;
-    if (lane == 0) base = atomicAdd(cnt + k * kChainClasses + c, (uint32_t)tot);
-    int pos = (int)__shfl(base, 0);
-#pragma unroll
-    for (int i = 0; i < kChainRounds; ++i) {
-      const unsigned long long bal = __ballot(len[i] == c + 2);
-      if (len[i] == c + 2) {
-        const int at = pos + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32),
-                                                            __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0));
-        int32_t* dst = lk + chain_at(c, at, m);
-        dst[0] = (int32_t)(j0 + i * 64 + lane);
-        if (c < 3) dst[1] = e1[i];
-        if (c == 1 || c == 2) dst[2] = e2[i];
-        if (c == 2) dst[3] = e3[i];
-      }
-      pos += (int)__popcll(bal);
-    }
-  }
-  for (int off = 32; off > 0; off >>= 1) longest = max(longest, __shfl_down(longest, off));
-  if (lane == 0 && longest > 0) atomicMax(cnt + D * kChainClasses, (uint32_t)longest);
 }
 
 // ---------------------------------------------------------------------------
@@ -1208,6 +1136,136 @@ int bits_for(uint64_t range) {  // bits to hold values 0..range
   return b;
 }
 
+// Groups of blur directions in the making: device arrays of `room` x m words
+// (the points' roots, then info and place behind them), the class counts and
+// their copy on the host.
+struct GroupBuild {
+  int n = 0, room = 0;
+  GroupSpec sp = {}, div = {};  // and a division in the making
+  int32_t* parent = nullptr;
+  uint32_t* cnt = nullptr;
+  uint32_t* host = nullptr;
+};
+
+// Find the parts of the groups that are not to be skipped; their counts are on
+// the host once the stream has been synchronised.
+int group_parts(sgp_lattice* L, const GroupBuild& gb, hipStream_t st) {
+  const int64_t m = L->m;
+  int32_t* info = gb.parent + gb.room * m;
+  int32_t* place = info + gb.room * m;
+  const int32_t* nbr = (const int32_t*)L->nbr.ptr;
+  const dim3 grid((unsigned)grid_for(m, kBlock, 4096), (unsigned)gb.n);
+  ProfScope ps(KK_NEIGHBORS, st);
+  hipLaunchKernelGGL(k_group_init, grid, dim3(kBlock), 0, st, nbr, m, gb.sp, gb.parent, info, gb.cnt);
+  SGP_LAUNCH_CHECK("k_group_init");
+  hipLaunchKernelGGL(k_group_join, grid, dim3(kBlock), 0, st, nbr, m, gb.sp, gb.parent);
+  SGP_LAUNCH_CHECK("k_group_join");
+  hipLaunchKernelGGL(k_group_count, grid, dim3(kBlock), 0, st, m, gb.sp, gb.parent, info, place);
+  SGP_LAUNCH_CHECK("k_group_count");
+  const int64_t span = (int64_t)kGroupSpan * kBlock;
+  hipLaunchKernelGGL(k_group_class, dim3((unsigned)((m + span - 1) / span), (unsigned)gb.n), dim3(kBlock), 0, st, m,
+                     gb.sp, (const int32_t*)gb.parent, info, gb.cnt);
+  SGP_LAUNCH_CHECK("k_group_class");
+  SGP_HIP(hipMemcpyAsync(gb.host, gb.cnt, sizeof(uint32_t) * gb.n * kGroupWords, hipMemcpyDeviceToHost, st));
+  return SGP_OK;
+}
+
+// The directions split evenly into groups of at most kGroupDirs, and their
+// parts. words: 2 (d + 1) m.
+int group_start(sgp_lattice* L, GroupBuild& gb, int32_t* words, uint32_t* cnt, uint32_t* host, hipStream_t st) {
+  const int D = L->d + 1;
+  gb.n = (D + kGroupDirs - 1) / kGroupDirs;
+  gb.room = 2 * D / 3;
+  gb.parent = words;
+  gb.cnt = cnt;
+  gb.host = host;
+  for (int g = 0; g < gb.n; ++g) {
+    gb.sp.first[g] = g ? gb.sp.first[g - 1] + gb.sp.dirs[g - 1] : 0;
+    gb.sp.dirs[g] = D / gb.n + (g < D % gb.n ? 1 : 0);
+  }
+  return group_parts(L, gb, st);
+}
+
+// Divide each run of neighbouring groups that have a part too large for a tile
+// into more groups, of at most `most` directions. True if there were any.
+bool group_divide(GroupBuild& gb, int D, int most) {
+  std::vector<int> at(D, -1), bad;  // group by first direction; groups to do again
+  for (int g = 0; g < gb.n; ++g) {
+    gb.sp.skip[g] = gb.host[g * kGroupWords + kGroupClasses] <= (uint32_t)kGroupPart;
+    at[gb.sp.first[g]] = g;
+    if (!gb.sp.skip[g]) bad.push_back(g);
+  }
+  if (bad.empty()) return false;
+  size_t used = 0;
+  for (int k = 0; k < D;) {
+    if (gb.sp.skip[at[k]]) {
+      k += gb.sp.dirs[at[k]];
+      continue;
+    }
+    const int k0 = k;
+    int had = 0;
+    for (; k < D && !gb.sp.skip[at[k]]; k += gb.sp.dirs[at[k]]) ++had;
+    const int nd = k - k0, want = std::min(nd, std::max((nd + most - 1) / most, had + 1));
+    int first = k0;
+    for (int i = 0; i < want; ++i) {
+      const int g = used < bad.size() ? bad[used++] : gb.n++;
+      if (g >= gb.room) return true;
+      gb.div.first[g] = first;
+      gb.div.dirs[g] = nd / want + (i < nd % want ? 1 : 0);
+      first += gb.div.dirs[g];
+    }
+  }
+  for (int g = 0; g < gb.n; ++g)
+    if (!gb.sp.skip[g]) {
+      gb.sp.first[g] = gb.div.first[g];
+      gb.sp.dirs[g] = gb.div.dirs[g];
+    }
+  return true;
+}
+
+// Place the parts in tiles. Groups whose parts outgrow a tile are divided, to
+// three and then to two directions; a lattice on which that does not help, or
+// whose tiles would be more than a fifth empty, keeps no groups.
+int group_place(sgp_lattice* L, GroupBuild& gb, hipStream_t st) {
+  const int64_t m = L->m;
+  for (int most = kGroupDirs - 1; most >= 2 && group_divide(gb, L->d + 1, most); --most) {
+    if (gb.n > gb.room) return SGP_OK;
+    if (const int rc = group_parts(L, gb, st)) return rc;
+    SGP_HIP(hipStreamSynchronize(st));
+  }
+  int64_t tiles = 0;
+  for (int g = 0; g < gb.n; ++g) {
+    const uint32_t* cnt = gb.host + g * kGroupWords;
+    if (cnt[kGroupClasses] > (uint32_t)kGroupPart) return SGP_OK;
+    gb.sp.tile0[g] = tiles;
+    tiles += group_tiles(cnt, kGroupClasses);
+  }
+  if (tiles * kGroupRows > gb.n * (m + m / 4 + 2 * kGroupClasses * kGroupRows)) return SGP_OK;
+  const int64_t rows = tiles * kGroupRows;
+  int rc;
+  if ((rc = dev_alloc(L->group_rows, sizeof(GroupRow) * rows, st))) return rc;
+  if ((rc = launch_fill_u32((uint32_t*)L->group_rows.ptr, (size_t)rows * (sizeof(GroupRow) / 4), 0xffffffffu, st)))
+    return rc;
+  const int32_t* info = gb.parent + gb.room * m;
+  int32_t* place = gb.parent + 2 * gb.room * m;
+  const dim3 grid((unsigned)grid_for(m, kBlock, 4096), (unsigned)gb.n);
+  ProfScope ps(KK_NEIGHBORS, st);
+  hipLaunchKernelGGL(k_group_place, grid, dim3(kBlock), 0, st, m, (const int32_t*)gb.parent, info,
+                     (const uint32_t*)gb.cnt, place);
+  SGP_LAUNCH_CHECK("k_group_place");
+  hipLaunchKernelGGL(k_group_rows, grid, dim3(kBlock), 0, st, (const int32_t*)L->nbr.ptr, m, gb.sp,
+                     (const int32_t*)place, (GroupRow*)L->group_rows.ptr);
+  SGP_LAUNCH_CHECK("k_group_rows");
+  for (int k = 0; k <= L->d; ++k)  // in order of their directions
+    for (int g = 0; g < gb.n; ++g)
+      if (gb.sp.first[g] == k) {
+        L->group_dirs[L->ngroups] = gb.sp.dirs[g];
+        L->group_tile[L->ngroups] = gb.sp.tile0[g];
+        L->group_tiles[L->ngroups++] = (int32_t)group_tiles(gb.host + g * kGroupWords, kGroupClasses);
+      }
+  return SGP_OK;
+}
+
 // shrink > 0 starts from a table 2^shrink times smaller than the bound
 // L / load_factor (most lattices have far fewer distinct points than
 // simplex vertices); *grow reports that it filled up, and the caller then
@@ -1238,7 +1296,7 @@ int build_attempt(sgp_lattice* L, const float* X, const double* f, double load_f
   int rc;
   enum {
     T_R0, T_RANK, T_SLOT, T_TAB, T_FIRST, T_COUNTS, T_OFFS, T_WORDS, T_W, T_NBRC,
-    T_SLOTS, T_FIRST2, T_CAN2INT, T_KA, T_KB, T_VA, T_VB, T_SORTTMP, T_PM, T_SUB, T_ORD, T_CNT, T_BITS, T_CHAIN
+    T_SLOTS, T_FIRST2, T_CAN2INT, T_KA, T_KB, T_VA, T_VB, T_SORTTMP, T_PM, T_SUB, T_ORD, T_CNT, T_BITS, T_GROUP
   };
   if ((rc = tr.alloc(T_R0, sizeof(int32_t) * n * d))) return rc;
   if ((rc = tr.alloc(T_RANK, sizeof(uint8_t) * n * d))) return rc;
@@ -1340,7 +1398,7 @@ int build_attempt(sgp_lattice* L, const float* X, const double* f, double load_f
   uint32_t* vb = (uint32_t*)tr.ptr[T_VB];
   uint32_t* sort_tmp = (uint32_t*)tr.ptr[T_SORTTMP];
   for (sgp::DevBuf* b : {&L->perm, &L->loc, &L->ws, &L->tile_off, &L->tile_verts, &L->slice, &L->tile_ent,
-                         &L->ent_lp, &L->ent_w, &L->occ_ptr, &L->run_dst, &L->row_vert, &L->stile_off, &L->nbr, &L->chains, &L->int2can})
+                         &L->ent_lp, &L->ent_w, &L->occ_ptr, &L->run_dst, &L->row_vert, &L->stile_off, &L->nbr, &L->group_rows, &L->int2can})
     dev_free(*b);
   if ((rc = dev_alloc(L->perm, sizeof(uint32_t) * n, st))) return rc;
   // two spare slots: the slice reads slots in aligned pairs
@@ -1485,21 +1543,14 @@ int build_attempt(sgp_lattice* L, const float* X, const double* f, double load_f
                        (int32_t*)L->nbr.ptr);
     SGP_LAUNCH_CHECK("k_nbr_internal");
   }
-  // ---- chains of neighbours, for the blur in place
-  const size_t chain_words = (size_t)D * kChainClasses + 1;
-  const bool chains = L->order == 1 && m >= kChainMin;
-  uint32_t* chain_cnt = nullptr;
-  if (chains) {
-    if ((rc = dev_alloc(L->chains, sizeof(int32_t) * 2 * m * D, st))) return rc;
-    if ((rc = tr.alloc(T_CHAIN, sizeof(uint32_t) * chain_words))) return rc;
-    chain_cnt = (uint32_t*)tr.ptr[T_CHAIN];
-    if ((rc = launch_fill_u32(chain_cnt, chain_words, 0u, st))) return rc;
-    ProfScope ps(KK_NEIGHBORS, st);
-    const int64_t waves = (m + kChainSpan - 1) / kChainSpan;
-    const dim3 grid((unsigned)((waves + kBlock / 64 - 1) / (kBlock / 64)), (unsigned)D);
-    hipLaunchKernelGGL(k_chains, grid, dim3(kBlock), 0, st, (const int32_t*)L->nbr.ptr, m, D, chain_cnt,
-                       (int32_t*)L->chains.ptr);
-    SGP_LAUNCH_CHECK("k_chains");
+  // ---- groups of blur directions: parts and their counts (the placing waits
+  // for the counts, further on)
+  GroupBuild gb;
+  L->ngroups = 0;
+  if (L->order == 1 && d >= 5 && m >= kGroupMin && m <= kGroupMax) {
+    if ((rc = tr.alloc(T_GROUP, sizeof(uint32_t) * kMaxGroups * kGroupWords))) return rc;
+    // T_NBRC has been read: 2 (d + 1) words a point, three a group
+    if ((rc = group_start(L, gb, nbr_can, (uint32_t*)tr.ptr[T_GROUP], host_word + 4 + 2 * kMaxD, st))) return rc;
   }
   // ---- tiles of consecutive sorted points, their runs, and runs per lattice point
   {
@@ -1536,6 +1587,7 @@ int build_attempt(sgp_lattice* L, const float* X, const double* f, double load_f
     SGP_HIP(hipMemcpyAsync(toff.data(), tile_off, sizeof(int32_t) * (ntiles + 1), hipMemcpyDeviceToHost, st));
     SGP_HIP(hipMemcpyAsync(soff.data(), stile_off, sizeof(int32_t) * (ntiles + 1), hipMemcpyDeviceToHost, st));
     SGP_HIP(hipStreamSynchronize(st));
+    if (gb.n && (rc = group_place(L, gb, st))) return rc;
     const int64_t Q = toff[ntiles], Qs = soff[ntiles];
     if (Q < 1 || Q > Lel || Qs < Q || Qs > Lel) {
       set_error("lattice_build: inconsistent run / piece counts %lld / %lld", (long long)Q, (long long)Qs);
@@ -1591,22 +1643,9 @@ int build_attempt(sgp_lattice* L, const float* X, const double* f, double load_f
     }
   }
   SGP_HIP(hipMemcpyAsync(host_word, words, sizeof(uint32_t) * 4, hipMemcpyDeviceToHost, st));
-  if (chains)
-    SGP_HIP(hipMemcpyAsync(host_word + 4, chain_cnt, sizeof(uint32_t) * (D * kChainClasses + 1),
-                           hipMemcpyDeviceToHost, st));
   SGP_HIP(hipStreamSynchronize(st));
   tr.idle = true;  // every kernel of this attempt has finished
   L->max_tile_ents = (int)host_word[3];
-  // a chain longer than 4 points is walked by one lane group: few of them, and
-  // none of them long
-  int64_t nshort = 0, nlong = 0;
-  if (chains)
-    for (int k = 0; k < D; ++k)
-      for (int c = 0; c < kChainClasses; ++c) {
-        L->chain_count[k][c] = (int32_t)host_word[4 + k * kChainClasses + c];
-        (c < kChainClasses - 1 ? nshort : nlong) += L->chain_count[k][c];
-      }
-  L->has_chains = chains && host_word[4 + D * kChainClasses] <= (uint32_t)kMaxChain && 20 * nlong <= nshort;
   if (host_word[0] & BF_ORDER) {
     set_error("lattice_build: internal error, a tile's sorted order is not a permutation");
     return SGP_EHASH;
@@ -1738,7 +1777,7 @@ extern "C" int lattice_build(const float* X, int64_t n, int32_t d, const double*
 
   int rc = SGP_OK;
   uint32_t* host_word = (uint32_t*)pinned_scratch(
-      sizeof(uint32_t) * std::max(4 + 2 * kMaxD, 4 + (kMaxD + 1) * kChainClasses + 1));
+      sizeof(uint32_t) * (4 + 2 * kMaxD + kMaxGroups * kGroupWords));
   {
     hipError_t e = hipGetDevice(&L->device);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&L->last_use, hipEventDisableTiming);

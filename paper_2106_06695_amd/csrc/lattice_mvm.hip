@@ -652,140 +652,127 @@ __global__ __launch_bounds__(kBlock) void k_blur2_split(Blur2Args<TU> a) {
   }
 }
 
-// One blur step in place, over the chains of neighbours of its direction
-// (three-tap stencil): a lane group takes a whole chain, reads its rows once,
-// forms every row's step from them as k_blur would (a missing neighbour adds
-// 0) and writes them back. Chains share no point, and a point without a
-// neighbour is left as it is: its step is its own value, since the middle tap
-// is 1. Against the fused pair of steps, which reads nine rows and five index
-// pairs per row of two steps, a row with neighbours is read and written once a
-// step with one index, and a third to two thirds of the rows not at all.
+// A group of blur directions in one pass over its tiles (groups.h): a block
+// reads a tile's rows into registers and LDS, forms each direction's step as
+// k_blur would (a missing neighbour adds 0) with the neighbours from LDS, and
+// writes the rows back. In place but for a chain's first group, which reads
+// U0, and the reverse chain's last one, which adds the forward chain. Against
+// the fused pair of steps, which reads nine rows and five index pairs per row
+// of two steps, a row is read and written once per three or four. Bound by
+// the memory rate on rows in no order: m = 4.2M, 16 fp32 channels 162 us a
+// group (3.3 TB/s on rows of 64 bytes), m = 874,000, 16 fp64 columns 49 us
+// (4.6 TB/s on rows of 128); from the caches by issue and LDS reads:
+// m = 141,000, 16 fp64 columns, both chains 17 us. Blur of one MVM, groups
+// against pairs (in-place steps of one direction): adjoint of m = 4.2M, d = 16
+// 55 against 141 (95) ms, CG iteration on m = 874,000, d = 11 1.35 against
+// 2.07 (1.71) ms. 512 threads where a row takes eight lanes: 49 against 59 us
+// with 256 (133 registers).
 template <typename TU>
-struct ChainArgs {
-  TU* u[2];                 // chain's array
-  const int32_t* list[2];   // its direction's lists
-  int32_t n[2][kChainClasses];
-  int64_t m;
-  int C;
-  int chain0, halves;       // as in Blur2Args
-  unsigned blocks;          // of one half
+struct GroupArgs {
+  const TU* in[2];          // per chain
+  TU* out[2];
+  const TU* add;            // added to the result (a forward chain's), or null
+  int64_t tile0[2];         // the group's first tile and tiles
+  int32_t tiles[2];
+  int dirs[2], rev[2];      // directions, from the last one down if rev
+  int C, chunks;
+  unsigned blocks;          // of one chain
   int vec;
   TU st[3];
 };
 template <int G, typename TU>
-constexpr int chain_vw() { return G < 16 / (int)sizeof(TU) ? G : 16 / (int)sizeof(TU); }
-// Chains a lane group takes at once, by class: all their rows are in flight
-// together.
-constexpr int chain_items(int cls) { return cls < 2 ? 4 : cls == 2 ? 2 : 1; }
+constexpr int group_vw() { return G < 16 / (int)sizeof(TU) ? G : 16 / (int)sizeof(TU); }
+// Threads of a block: at most 4 rows each, so that registers allow as many
+// waves as LDS does.
+template <int G, typename TU>
+constexpr int group_threads() { return G / group_vw<G, TU>() > 4 ? kGroupRows * 2 : kGroupRows; }
 
-template <typename TU, int VW>
-__device__ __forceinline__ void chain_load(const TU* u, int64_t row, int C, int c, bool vec, TU (&v)[VW]) {
-  const TU* src = u + row * C + c;
-  if (vec) {
-    read_row<TU, VW>(src, v);
-  } else {
-#pragma unroll
-    for (int i = 0; i < VW; ++i) v[i] = c + i < C ? src[i] : (TU)0;
-  }
-}
-// The step of one row from its own value and its neighbours', stored.
-template <typename TU, int VW>
-__device__ __forceinline__ void chain_store(TU* u, int64_t row, int C, int c, bool vec, const TU* st,
-                                            const TU (&lo)[VW], const TU (&v)[VW], const TU (&hi)[VW]) {
-  TU o[VW];
-#pragma unroll
-  for (int i = 0; i < VW; ++i) o[i] = fma_t(st[2], hi[i], fma_t(st[1], v[i], fma_t(st[0], lo[i], (TU)0)));
-  TU* dst = u + row * C + c;
-  if (vec) {
-    write_row<TU, VW>(dst, o);
-  } else {
-#pragma unroll
-    for (int i = 0; i < VW; ++i)
-      if (c + i < C) dst[i] = o[i];
-  }
-}
-// ITEMS chains of N points, from item i of a direction's lists on, R items
-// apart.
-template <int N, int ITEMS, typename TU, int VW>
-__device__ __forceinline__ void chain_steps(TU* u, const int32_t* list, int64_t m, int i, int n, int R, int C, int c,
-                                            bool vec, const TU* st) {
-  int32_t row[ITEMS][N];
-  TU v[ITEMS][N + 2][VW];
-#pragma unroll
-  for (int t = 0; t < ITEMS; ++t) {
-    const int64_t at = chain_at(N - 2, i + t * R < n ? i + t * R : n - 1, m);
-#pragma unroll
-    for (int x = 0; x < N; ++x) row[t][x] = list[at + x];
-  }
-#pragma unroll
-  for (int t = 0; t < ITEMS; ++t) {
-#pragma unroll
-    for (int x = 0; x < N; ++x) chain_load<TU, VW>(u, row[t][x], C, c, vec, v[t][x + 1]);
-#pragma unroll
-    for (int q = 0; q < VW; ++q) v[t][0][q] = v[t][N + 1][q] = 0;
-  }
-#pragma unroll
-  for (int t = 0; t < ITEMS; ++t)
-    if (i + t * R < n) {
-#pragma unroll
-      for (int x = 0; x < N; ++x) chain_store<TU, VW>(u, row[t][x], C, c, vec, st, v[t][x], v[t][x + 1], v[t][x + 2]);
-    }
+// The neighbour bytes of rows in the order of a downward pass over nd
+// directions: 16-bit fields 0 .. nd-1 reversed.
+__device__ __forceinline__ uint2 group_reverse(uint2 s, int nd) {
+  uint2 r = {s.y >> 16 | s.y << 16, s.x >> 16 | s.x << 16};  // fields 3 2 1 0
+  if (nd < 4) r = uint2{r.x >> 16 | r.y << 16, r.y >> 16};
+  if (nd < 3) r = uint2{r.x >> 16 | r.y << 16, r.y >> 16};
+  if (nd < 2) r = uint2{r.x >> 16 | r.y << 16, r.y >> 16};
+  return r;
 }
 
-// A block takes chains of one class.
 template <typename TU, int G>
-__global__ __launch_bounds__(kBlock) void k_blur_chain(const int32_t* __restrict__ nbr0,
-                                                       const int32_t* __restrict__ nbr1, ChainArgs<TU> a) {
-  constexpr int VW = chain_vw<G, TU>();
+__global__ __launch_bounds__((group_threads<G, TU>())) void k_blur_group(
+    const GroupRow* __restrict__ rows, GroupArgs<TU> a) {
+  constexpr int VW = group_vw<G, TU>();
   constexpr int LPR = G / VW;
-  constexpr int R = kBlock / LPR;
-  const int half = blockIdx.x >= a.blocks ? 1 : 0;
-  const int ch = a.chain0 + half;
-  TU* u = a.u[ch];
-  const int32_t* list = a.list[ch];
-  int b = (int)xcd_block(blockIdx.x - half * a.blocks, a.blocks);
-  int cls = 0, n = 0;
-  for (; cls < kChainClasses; ++cls) {
-    n = a.n[ch][cls];
-    const int per = R * chain_items(cls), blocks = (n + per - 1) / per;
-    if (b < blocks) break;
-    b -= blocks;
+  constexpr int RP = group_threads<G, TU>() / LPR;  // rows at a time
+  constexpr int NI = kGroupRows / RP;
+  __shared__ __align__(16) TU A[kGroupRows * G];
+  const int ch = blockIdx.x >= a.blocks ? 1 : 0;
+  const int b = (int)xcd_block(blockIdx.x - ch * a.blocks, a.blocks);
+  const int tile = b / a.chunks;
+  if (tile >= a.tiles[ch]) return;  // the other chain's group has more
+  const int r0 = (int)threadIdx.x / LPR, cl = (int)(threadIdx.x % LPR) * VW;
+  const int c = (b - tile * a.chunks) * G + cl;
+  const bool vec = a.vec && c + VW <= a.C;
+  const int64_t p0 = (a.tile0[ch] + tile) * kGroupRows + r0;
+  const int nd = a.dirs[ch];
+  int32_t row[NI];
+  uint2 nb[NI];
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const GroupRow q = rows[p0 + i * RP];
+    row[i] = q.point;
+    nb[i] = uint2{q.slots[0], q.slots[1]};
   }
-  if (cls == kChainClasses) return;  // the other half has more blocks
-  const int i = b * (R * chain_items(cls)) + (int)threadIdx.x / LPR;
-  if (i >= n) return;
-  for (int c = (int)(threadIdx.x % LPR) * VW; c < a.C; c += G) {
-    const bool vec = a.vec && c + VW <= a.C;
-    if (cls == 0) {
-      chain_steps<2, chain_items(0), TU, VW>(u, list, a.m, i, n, R, a.C, c, vec, a.st);
-    } else if (cls == 1) {
-      chain_steps<3, chain_items(1), TU, VW>(u, list, a.m, i, n, R, a.C, c, vec, a.st);
-    } else if (cls == 2) {
-      chain_steps<4, chain_items(2), TU, VW>(u, list, a.m, i, n, R, a.C, c, vec, a.st);
+  TU v[NI][VW];
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const TU* src = a.in[ch] + (int64_t)row[i] * a.C + c;
+    if (row[i] >= 0 && vec) {
+      read_row<TU, VW>(src, v[i]);
     } else {
-      // a longer chain: its points follow one another through the neighbour table
-      const int32_t* nb = half ? nbr1 : nbr0;
-      int64_t row = list[chain_at(3, i, a.m)];
-      TU lo[VW], v[VW], hi[VW];
 #pragma unroll
-      for (int x = 0; x < VW; ++x) lo[x] = 0;
-      chain_load<TU, VW>(u, row, a.C, c, vec, v);
-      while (row >= 0) {
-        const int64_t nx = nb[2 * row + 1];
-        if (nx >= 0) {
-          chain_load<TU, VW>(u, nx, a.C, c, vec, hi);
-        } else {
+      for (int x = 0; x < VW; ++x) v[i][x] = row[i] >= 0 && c + x < a.C ? src[x] : (TU)0;
+    }
+  }
+  if (a.rev[ch]) {
 #pragma unroll
-          for (int x = 0; x < VW; ++x) hi[x] = 0;
-        }
-        chain_store<TU, VW>(u, row, a.C, c, vec, a.st, lo, v, hi);
-        row = nx;
+    for (int i = 0; i < NI; ++i) nb[i] = group_reverse(nb[i], nd);
+  }
+  const TU* Ac = A + cl;
 #pragma unroll
-        for (int x = 0; x < VW; ++x) {
-          lo[x] = v[x];
-          v[x] = hi[x];
-        }
+  for (int t = 0; t < kGroupDirs; ++t) {
+    if (t >= nd) break;
+    if (t) __syncthreads();  // the last direction's rows have been read
+#pragma unroll
+    for (int i = 0; i < NI; ++i) write_row<TU, VW>(A + (r0 + i * RP) * G + cl, v[i]);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const uint32_t lh = t & 2 ? nb[i].y : nb[i].x;
+      TU l[VW], h[VW];
+      read_row<TU, VW>(Ac + (lh >> (16 * (t & 1)) & 255) * G, l);
+      read_row<TU, VW>(Ac + (lh >> (16 * (t & 1) + 8) & 255) * G, h);
+#pragma unroll
+      for (int x = 0; x < VW; ++x)
+        v[i][x] = fma_t(a.st[2], h[x], fma_t(a.st[1], v[i][x], fma_t(a.st[0], l[x], (TU)0)));
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    if (row[i] < 0) continue;
+    const int64_t at = (int64_t)row[i] * a.C + c;
+    TU* dst = a.out[ch] + at;
+    if (vec) {
+      if (a.add) {
+        TU f[VW];
+        read_row<TU, VW>(a.add + at, f);
+#pragma unroll
+        for (int x = 0; x < VW; ++x) v[i][x] = f[x] + v[i][x];
       }
+      write_row<TU, VW>(dst, v[i]);
+    } else {
+#pragma unroll
+      for (int x = 0; x < VW; ++x)
+        if (c + x < a.C) dst[x] = a.add ? a.add[at + x] + v[i][x] : v[i][x];
     }
   }
 }
@@ -1270,7 +1257,8 @@ int gather_g(const sgp_lattice* L, const TU* part, TU* U0, TU* frag, int C, cons
 // 34, 342 | 39, 419; 41, 461. m = 1,460 (d = 6) 39, 404; 42, 441 | 64, 512;
 // 63, 570. Beyond, one CU per column takes longer than the launches that it
 // saves: with four rows a thread, m = 4,453 (d = 6) 55, 571; 63, 651 |
-// 66, 503; 68, 571. No rule on the columns: each has a CU for itself.
+// 66, 503; 68, 571. As good on many columns: m = 1,460, one MVM of 256 columns
+// 87 | 175 us.
 bool col_path(const sgp_lattice* L, int64_t parts) {
   return L->order == 1 && L->m <= kColRows && parts <= kColParts && blur_fuse_enabled();
 }
@@ -1355,70 +1343,60 @@ int blur_g(const sgp_lattice* L, TU* U0, TU* B1, TU* B2, TU* B3, TU* B4, int C, 
     later.clear();
     return SGP_OK;
   };
-  // In place over the chains (all steps but the first two and the last; the
-  // first launch copies out of U0, the last one sums) where an array outgrows
-  // the 32 MiB of the XCDs' L2s together: the fused pair's nine row reads then
-  // miss it. Blur of one MVM, pair against chains: 44 MB (m = 681,000, d = 20,
-  // C = 8, fp64) 652 -> 422 us, 112 MB (m = 874,000, d = 11, C = 16, fp64)
-  // 893 -> 755 us; 18 MB (m = 141,000, d = 11, C = 16, fp64) 140 -> 144 us, 9 MB
-  // (fp32) 87 -> 117 us.
-  const bool in_place = fuse && L->has_chains && d >= 3 && (double)mC * sizeof(TU) > 32.0 * (1 << 20);
-  // In place a launch only touches the chains' own two arrays: one after the
-  // other pays from 256 MiB of them on (112 MB each: 845 against 755 us for
-  // both together; 267 MB each: 3.66 against 3.74 ms).
-  if (in_place) seq = seq && 2.0 * (double)mC * sizeof(TU) > 256.0 * (1 << 20);
-  auto chain_launch = [&](int step, int chain0, int halves, TU* a0, TU* a1) -> int {
-    ChainArgs<TU> b;
-    b.u[0] = a0;
-    b.u[1] = a1;
-    b.m = m;
+  if (fuse && L->ngroups) {
+    const int ng = L->ngroups;
+    // A launch only touches its chains' own arrays, and one chain after the
+    // other pays late: adjoint of m = 4.2M, d = 16 (254 MiB an array) 54.3
+    // against 57.3 ms for both in one launch; at half that (C = 8) 2.47
+    // against 2.43 ms an MVM, at 44 MB (m = 681,000, fp64) 529 against 492 us.
+    seq = seq && 2.0 * (double)mC * sizeof(TU) > 384.0 * (1 << 20);
+    GroupArgs<TU> b;
     b.C = C;
-    b.chain0 = chain0;
-    b.halves = halves;
-    b.vec = (C % chain_vw<G, TU>() == 0 && aligned16(a0) && aligned16(a1)) ? 1 : 0;
+    b.chunks = (C + G - 1) / G;
+    b.vec = (C % group_vw<G, TU>() == 0 && aligned16(U0) && aligned16(B1) && aligned16(B2)) ? 1 : 0;
     for (int t = 0; t < 3; ++t) b.st[t] = a.st[t];
-    const int32_t* nb[2];
-    int64_t most = 0;
-    for (int ch = 0; ch < 2; ++ch) {
-      const int k = kdir(step, ch);
-      nb[ch] = nbr + (int64_t)k * T * m;
-      b.list[ch] = (const int32_t*)L->chains.ptr + 2 * (int64_t)k * m;
-      int64_t tot = 0;
-      for (int q = 0; q < kChainClasses; ++q) {
-        b.n[ch][q] = L->chain_count[k][q];
-        const int per = kBlock / (G / chain_vw<G, TU>()) * chain_items(q);
-        tot += (b.n[ch][q] + per - 1) / per;
+    // one group of chain 0 (i0 >= 0) and one of chain 1 (i1 >= 0)
+    auto launch = [&](int i0, int i1, bool sum) -> int {
+      unsigned n = 0;
+      int64_t most = 0;
+      for (int ch = 0; ch < 2; ++ch) {
+        const int i = ch ? i1 : i0;
+        if (i < 0) continue;
+        const bool rev = ch || L->blur == SGP_BLUR_REVERSE;
+        const int g = rev ? ng - 1 - i : i;
+        b.in[n] = i ? (ch ? B2 : B1) : U0;
+        b.out[n] = ch && !sum ? B2 : B1;
+        b.tile0[n] = L->group_tile[g];
+        b.tiles[n] = L->group_tiles[g];
+        b.dirs[n] = L->group_dirs[g];
+        b.rev[n] = rev;
+        most = std::max(most, (int64_t)b.tiles[n]);
+        ++n;
       }
-      if (ch >= chain0 && ch < chain0 + halves) most = std::max(most, tot);
+      b.add = sum ? B1 : nullptr;
+      b.blocks = (unsigned)(most * b.chunks);
+      ProfScope ps(KK_BLUR, s);
+      hipLaunchKernelGGL((k_blur_group<TU, G>), dim3(b.blocks * n), dim3((group_threads<G, TU>())), 0, s,
+                         (const GroupRow*)L->group_rows.ptr, b);
+      SGP_LAUNCH_CHECK("k_blur_group");
+      return SGP_OK;
+    };
+    int rc = SGP_OK;
+    *result = B1;
+    if (!sym || seq) {
+      for (int i = 0; !rc && i < ng; ++i) rc = launch(i, -1, false);
+      for (int i = 0; !rc && sym && i < ng; ++i) rc = launch(-1, i, i == ng - 1);
+    } else {
+      for (int i = 0; !rc && i < ng - 1; ++i) rc = launch(i, i, false);
+      if (!rc) rc = launch(ng - 1, -1, false);
+      if (!rc) rc = launch(-1, ng - 1, true);
     }
-    if (most == 0) return SGP_OK;
-    b.blocks = (unsigned)most;
-    ProfScope ps(KK_BLUR, s);
-    hipLaunchKernelGGL((k_blur_chain<TU, G>), dim3(b.blocks * halves), dim3(kBlock), 0, s, nb[chain0],
-                       nb[chain0 + halves - 1], b);
-    SGP_LAUNCH_CHECK("k_blur_chain");
-    return SGP_OK;
-  };
+    return rc;
+  }
   for (int step = 0; step <= d;) {
-    if (in_place && step == 2) {
-      TU *a0 = (TU*)cur[0], *a1 = a.chains == 2 ? (TU*)cur[1] : (TU*)cur[0];
-      int rc;
-      if (seq) {
-        for (int q = step; q < d; ++q)
-          if ((rc = chain_launch(q, 0, 1, a0, a1))) return rc;
-        if ((rc = flush_later())) return rc;
-        for (int q = step; q < d; ++q)
-          if ((rc = chain_launch(q, 1, 1, a0, a1))) return rc;
-      } else {
-        for (int q = step; q < d; ++q)
-          if ((rc = chain_launch(q, 0, a.chains, a0, a1))) return rc;
-      }
-      step = d;
-      continue;
-    }
     TU* dst0 = next0(cur[0]);
     TU* dst1 = next1(cur[1]);
-    if (fuse && step + 1 <= d && !(in_place && step == d)) {
+    if (fuse && step + 1 <= d) {
       Blur2Args<TU> b2;
       b2.in[0] = cur[0];
       b2.in[1] = cur[1];

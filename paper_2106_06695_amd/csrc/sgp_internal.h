@@ -36,20 +36,26 @@ constexpr int64_t tile_slice0(int64_t first_piece, int64_t tile) {
   return first_piece / kSlicePieces + tile;
 }
 
-// The blur in place (k_blur_chain): lattices of at least kChainMin points
-// (smaller ones reach its 32 MiB of values a chain only in batches of more
-// than 32 fp64 columns) whose chains of neighbours have at most kMaxChain
-// points, and rarely more than 4, keep chain lists, by length 2, 3, 4 and more.
-constexpr int64_t kChainMin = 131072;
-constexpr int kMaxChain = 16;
-constexpr int kChainClasses = 4;
-// Place of item i of class c in a direction's lists of 2 m words.
-#ifdef __HIPCC__
-__host__ __device__
-#endif
-constexpr int64_t chain_at(int c, int64_t i, int64_t m) {
-  return c == 0 ? 2 * i : c == 1 ? m - 3 * (i + 1) : c == 2 ? m + 4 * i : 2 * m - 1 - i;
-}
+// The blur by groups of directions (k_blur_group): lattices of at least
+// kGroupMin points keep, per group of up to kGroupDirs directions, tiles of
+// kGroupRows rows that hold whole connected parts of up to kGroupPart points
+// (groups.h). With groups against without: one training step on m = 16,185
+// (d = 11, 20 iterations) 2.66 against 2.83 ms, 16 iterations on m = 11,064
+// (d = 8) 1.27 against 1.32 ms; a request of m = 3,677 (build and 16
+// iterations) 1.62 against 1.58 ms, as the groups cost the build eight
+// launches.
+constexpr int64_t kGroupMin = 8192;
+constexpr int64_t kGroupMax = (int64_t)1 << 26;  // part numbers share a word with their class
+constexpr int kGroupDirs = 4;
+constexpr int kGroupRows = 256;
+constexpr int kGroupPart = kGroupRows - 1;
+constexpr int kMaxGroups = 2 * (kMaxD + 1) / 3;
+constexpr int kGroupClasses = 30;
+constexpr int kGroupWords = kGroupClasses + 1;
+struct GroupRow {
+  int32_t point;
+  uint32_t slots[2];  // four directions' neighbours within the tile, (low, high) bytes
+};
 
 // Launch-shape knobs of the MVM kernels. Defaults are the measured best on
 // MI355X; SGP_LDS_BUDGET, SGP_SLICE_LDS_BUDGET, SGP_TILE_BLOCKS_PER_CU and
@@ -214,11 +220,13 @@ struct sgp_lattice {
   sgp::DevBuf run_dst;    // npiece int32: partial row of each piece; a lattice point's
                           //   pieces occupy rows occ_ptr[j] .. occ_ptr[j+1]-1 in piece order
   sgp::DevBuf nbr;        // (d+1) x m x 2r int32: [direction][internal vertex][offset]
-  // three-tap stencils on large lattices: chains of neighbours along each
-  // direction (k_chains), 2 m int32 a direction, and their counts by class
-  sgp::DevBuf chains;
-  bool has_chains = false;
-  int32_t chain_count[sgp::kMaxD + 1][sgp::kChainClasses] = {};
+  // three-tap stencils: groups of blur directions in order (0: none), each
+  // one's directions and tiles, the tiles' rows
+  int ngroups = 0;
+  int group_dirs[sgp::kMaxGroups] = {};
+  int64_t group_tile[sgp::kMaxGroups] = {};   // first tile
+  int32_t group_tiles[sgp::kMaxGroups] = {};
+  sgp::DevBuf group_rows;  // GroupRow
   sgp::DevBuf int2can;    // m int32: internal vertex -> canonical index
   sgp::DevBuf keys;       // m x d int32 in canonical order (first occurrence in caller's order)
 
