@@ -1,6 +1,6 @@
-// Groups of blur directions (three-tap stencil): for up to kGroupDirs
-// consecutive directions, the lattice points that are connected through
-// neighbours along them (a part) are brought together in tiles of kGroupRows
+// Groups of blur directions: for up to kGroupDirs consecutive directions, the
+// lattice points that are connected through neighbours along them (a part;
+// neighbours are R = 1 or 2 points to either side, the stencil's order) are brought together in tiles of kGroupRows
 // rows, so that the blur takes the whole group of directions in one pass
 // (k_blur_group). A point set of bounded extent has few points per part: four
 // directions join at most 132 of them at m = 141,000 (d = 11), 189 at
@@ -45,8 +45,25 @@ __device__ __forceinline__ int32_t group_find(int32_t* parent, int32_t x) {
   return x;
 }
 
+// A point's neighbours along direction k: -R .. -1, 1 .. R.
+template <int R>
+__device__ __forceinline__ void group_nbrs(const int32_t* nbr, int64_t k, int64_t m, int64_t j, int32_t (&o)[2 * R]) {
+  if constexpr (R == 1) {
+    const int2 v = ((const int2*)nbr)[k * m + j];
+    o[0] = v.x;
+    o[1] = v.y;
+  } else {
+    const int4 v = ((const int4*)nbr)[k * m + j];
+    o[0] = v.x;
+    o[1] = v.y;
+    o[2] = v.z;
+    o[3] = v.w;
+  }
+}
+
 // parent = the smallest of a point and its neighbours along the group;
 // also clears the sizes and the class counts.
+template <int R>
 __global__ __launch_bounds__(256) void k_group_init(const int32_t* __restrict__ nbr, int64_t m, GroupSpec sp,
                                                     int32_t* __restrict__ parent, int32_t* __restrict__ info,
                                                     uint32_t* __restrict__ cnt) {
@@ -59,9 +76,11 @@ __global__ __launch_bounds__(256) void k_group_init(const int32_t* __restrict__ 
 #pragma unroll
     for (int t = 0; t < kGroupDirs; ++t)
       if (t < sp.dirs[g]) {
-        const int2 lh = ((const int2*)nbr)[(int64_t)(sp.first[g] + t) * m + j];
-        if (lh.x >= 0 && lh.x < p) p = lh.x;
-        if (lh.y >= 0 && lh.y < p) p = lh.y;
+        int32_t nb[2 * R];
+        group_nbrs<R>(nbr, sp.first[g] + t, m, j, nb);
+#pragma unroll
+        for (int i = 0; i < 2 * R; ++i)
+          if (nb[i] >= 0 && nb[i] < p) p = nb[i];
       }
     parent[g * m + j] = p;
     info[g * m + j] = 0;
@@ -71,6 +90,7 @@ __global__ __launch_bounds__(256) void k_group_init(const int32_t* __restrict__ 
 // Join the two ends of every neighbour pair. A root is only ever linked to a
 // smaller index, by compare-and-swap, so every loop here goes strictly down
 // and ends.
+template <int R>
 __global__ __launch_bounds__(256) void k_group_join(const int32_t* __restrict__ nbr, int64_t m, GroupSpec sp,
                                                     int32_t* __restrict__ parents) {
   const int g = (int)blockIdx.y;
@@ -78,13 +98,13 @@ __global__ __launch_bounds__(256) void k_group_join(const int32_t* __restrict__ 
   int32_t* parent = parents + g * m;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < m; j += stride) {
-    int32_t hi[kGroupDirs];
+    int32_t hi[R * kGroupDirs];  // each pair from its lower end
 #pragma unroll
-    for (int t = 0; t < kGroupDirs; ++t)
-      hi[t] = t < sp.dirs[g] ? nbr[2 * ((int64_t)(sp.first[g] + t) * m + j) + 1] : -1;
+    for (int t = 0; t < R * kGroupDirs; ++t)
+      hi[t] = t / R < sp.dirs[g] ? nbr[2 * R * ((int64_t)(sp.first[g] + t / R) * m + j) + R + t % R] : -1;
     int32_t a = (int32_t)j;
 #pragma unroll
-    for (int t = 0; t < kGroupDirs; ++t) {
+    for (int t = 0; t < R * kGroupDirs; ++t) {
       if (hi[t] < 0) continue;
       a = group_find<true>(parent, a);
       int32_t b = group_find<true>(parent, hi[t]);
@@ -204,28 +224,41 @@ __global__ __launch_bounds__(256) void k_group_place(int64_t m, const int32_t* _
 }
 
 // The rows' records: the lattice point, and its neighbours within the tile, a
-// byte each: (low, high) per direction, the tile's empty row where there is
-// none. Rows without a point keep all bits set.
+// byte each (-R .. -1, 1 .. R per direction), the tile's empty row where there
+// is none. Rows without a point keep all bits set.
+template <int R>
 __global__ __launch_bounds__(256) void k_group_rows(const int32_t* __restrict__ nbr, int64_t m, GroupSpec sp,
                                                     const int32_t* __restrict__ places,
-                                                    GroupRow* __restrict__ rows) {
+                                                    GroupRow<R>* __restrict__ rows) {
   const int g = (int)blockIdx.y;
   const int32_t* place = places + g * m;
-  GroupRow* out = rows + sp.tile0[g] * kGroupRows;
+  GroupRow<R>* out = rows + sp.tile0[g] * kGroupRows;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < m; j += stride) {
-    int2 lh[kGroupDirs];
-#pragma unroll
-    for (int t = 0; t < kGroupDirs; ++t)
-      lh[t] = t < sp.dirs[g] ? ((const int2*)nbr)[(int64_t)(sp.first[g] + t) * m + j] : int2{-1, -1};
-    uint32_t s[2] = {0u, 0u};
+    int32_t nb[kGroupDirs][2 * R];
 #pragma unroll
     for (int t = 0; t < kGroupDirs; ++t) {
-      const uint32_t lo = lh[t].x >= 0 ? (uint32_t)place[lh[t].x] % kGroupRows : kGroupRows - 1;
-      const uint32_t hi = lh[t].y >= 0 ? (uint32_t)place[lh[t].y] % kGroupRows : kGroupRows - 1;
-      s[t >> 1] |= (lo | hi << 8) << (16 * (t & 1));
+      if (t < sp.dirs[g]) {
+        group_nbrs<R>(nbr, sp.first[g] + t, m, j, nb[t]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 2 * R; ++i) nb[t][i] = -1;
+      }
     }
-    out[place[j]] = GroupRow{(int32_t)j, s[0], s[1]};
+    GroupRow<R> q;
+    q.point = (int32_t)j;
+#pragma unroll
+    for (int w = 0; w < 2 * R; ++w) {
+      uint32_t s = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int e = 4 * w + i;  // byte e is neighbour e % 2R of direction e / 2R
+        const int32_t x = nb[e / (2 * R)][e % (2 * R)];
+        s |= (x >= 0 ? (uint32_t)place[x] % kGroupRows : (uint32_t)(kGroupRows - 1)) << (8 * i);
+      }
+      q.slots[w] = s;
+    }
+    out[place[j]] = q;
   }
 }
 

@@ -1149,6 +1149,7 @@ struct GroupBuild {
 
 // Find the parts of the groups that are not to be skipped; their counts are on
 // the host once the stream has been synchronised.
+template <int R>
 int group_parts(sgp_lattice* L, const GroupBuild& gb, hipStream_t st) {
   const int64_t m = L->m;
   int32_t* info = gb.parent + gb.room * m;
@@ -1156,9 +1157,9 @@ int group_parts(sgp_lattice* L, const GroupBuild& gb, hipStream_t st) {
   const int32_t* nbr = (const int32_t*)L->nbr.ptr;
   const dim3 grid((unsigned)grid_for(m, kBlock, 4096), (unsigned)gb.n);
   ProfScope ps(KK_NEIGHBORS, st);
-  hipLaunchKernelGGL(k_group_init, grid, dim3(kBlock), 0, st, nbr, m, gb.sp, gb.parent, info, gb.cnt);
+  hipLaunchKernelGGL(k_group_init<R>, grid, dim3(kBlock), 0, st, nbr, m, gb.sp, gb.parent, info, gb.cnt);
   SGP_LAUNCH_CHECK("k_group_init");
-  hipLaunchKernelGGL(k_group_join, grid, dim3(kBlock), 0, st, nbr, m, gb.sp, gb.parent);
+  hipLaunchKernelGGL(k_group_join<R>, grid, dim3(kBlock), 0, st, nbr, m, gb.sp, gb.parent);
   SGP_LAUNCH_CHECK("k_group_join");
   hipLaunchKernelGGL(k_group_count, grid, dim3(kBlock), 0, st, m, gb.sp, gb.parent, info, place);
   SGP_LAUNCH_CHECK("k_group_count");
@@ -1171,7 +1172,8 @@ int group_parts(sgp_lattice* L, const GroupBuild& gb, hipStream_t st) {
 }
 
 // The directions split evenly into groups of at most kGroupDirs, and their
-// parts. words: 2 (d + 1) m.
+// parts. words: at least 2 (d + 1) m.
+template <int R>
 int group_start(sgp_lattice* L, GroupBuild& gb, int32_t* words, uint32_t* cnt, uint32_t* host, hipStream_t st) {
   const int D = L->d + 1;
   gb.n = (D + kGroupDirs - 1) / kGroupDirs;
@@ -1183,7 +1185,7 @@ int group_start(sgp_lattice* L, GroupBuild& gb, int32_t* words, uint32_t* cnt, u
     gb.sp.first[g] = g ? gb.sp.first[g - 1] + gb.sp.dirs[g - 1] : 0;
     gb.sp.dirs[g] = D / gb.n + (g < D % gb.n ? 1 : 0);
   }
-  return group_parts(L, gb, st);
+  return group_parts<R>(L, gb, st);
 }
 
 // Divide each run of neighbouring groups that have a part too large for a tile
@@ -1226,11 +1228,12 @@ bool group_divide(GroupBuild& gb, int D, int most) {
 // Place the parts in tiles. Groups whose parts outgrow a tile are divided, to
 // three and then to two directions; a lattice on which that does not help, or
 // whose tiles would be more than a fifth empty, keeps no groups.
+template <int R>
 int group_place(sgp_lattice* L, GroupBuild& gb, hipStream_t st) {
   const int64_t m = L->m;
   for (int most = kGroupDirs - 1; most >= 2 && group_divide(gb, L->d + 1, most); --most) {
     if (gb.n > gb.room) return SGP_OK;
-    if (const int rc = group_parts(L, gb, st)) return rc;
+    if (const int rc = group_parts<R>(L, gb, st)) return rc;
     SGP_HIP(hipStreamSynchronize(st));
   }
   int64_t tiles = 0;
@@ -1243,8 +1246,8 @@ int group_place(sgp_lattice* L, GroupBuild& gb, hipStream_t st) {
   if (tiles * kGroupRows > gb.n * (m + m / 4 + 2 * kGroupClasses * kGroupRows)) return SGP_OK;
   const int64_t rows = tiles * kGroupRows;
   int rc;
-  if ((rc = dev_alloc(L->group_rows, sizeof(GroupRow) * rows, st))) return rc;
-  if ((rc = launch_fill_u32((uint32_t*)L->group_rows.ptr, (size_t)rows * (sizeof(GroupRow) / 4), 0xffffffffu, st)))
+  if ((rc = dev_alloc(L->group_rows, sizeof(GroupRow<R>) * rows, st))) return rc;
+  if ((rc = launch_fill_u32((uint32_t*)L->group_rows.ptr, (size_t)rows * (sizeof(GroupRow<R>) / 4), 0xffffffffu, st)))
     return rc;
   const int32_t* info = gb.parent + gb.room * m;
   int32_t* place = gb.parent + 2 * gb.room * m;
@@ -1253,8 +1256,8 @@ int group_place(sgp_lattice* L, GroupBuild& gb, hipStream_t st) {
   hipLaunchKernelGGL(k_group_place, grid, dim3(kBlock), 0, st, m, (const int32_t*)gb.parent, info,
                      (const uint32_t*)gb.cnt, place);
   SGP_LAUNCH_CHECK("k_group_place");
-  hipLaunchKernelGGL(k_group_rows, grid, dim3(kBlock), 0, st, (const int32_t*)L->nbr.ptr, m, gb.sp,
-                     (const int32_t*)place, (GroupRow*)L->group_rows.ptr);
+  hipLaunchKernelGGL(k_group_rows<R>, grid, dim3(kBlock), 0, st, (const int32_t*)L->nbr.ptr, m, gb.sp,
+                     (const int32_t*)place, (GroupRow<R>*)L->group_rows.ptr);
   SGP_LAUNCH_CHECK("k_group_rows");
   for (int k = 0; k <= L->d; ++k)  // in order of their directions
     for (int g = 0; g < gb.n; ++g)
@@ -1547,10 +1550,11 @@ int build_attempt(sgp_lattice* L, const float* X, const double* f, double load_f
   // for the counts, further on)
   GroupBuild gb;
   L->ngroups = 0;
-  if (L->order == 1 && d >= 5 && m >= kGroupMin && m <= kGroupMax) {
+  if (L->order <= 2 && d >= 5 && m >= kGroupMin && m <= kGroupMax) {
     if ((rc = tr.alloc(T_GROUP, sizeof(uint32_t) * kMaxGroups * kGroupWords))) return rc;
-    // T_NBRC has been read: 2 (d + 1) words a point, three a group
-    if ((rc = group_start(L, gb, nbr_can, (uint32_t*)tr.ptr[T_GROUP], host_word + 4 + 2 * kMaxD, st))) return rc;
+    // T_NBRC has been read: at least 2 (d + 1) words a point, three a group
+    const auto start = L->order == 1 ? group_start<1> : group_start<2>;
+    if ((rc = start(L, gb, nbr_can, (uint32_t*)tr.ptr[T_GROUP], host_word + 4 + 2 * kMaxD, st))) return rc;
   }
   // ---- tiles of consecutive sorted points, their runs, and runs per lattice point
   {
@@ -1587,7 +1591,7 @@ int build_attempt(sgp_lattice* L, const float* X, const double* f, double load_f
     SGP_HIP(hipMemcpyAsync(toff.data(), tile_off, sizeof(int32_t) * (ntiles + 1), hipMemcpyDeviceToHost, st));
     SGP_HIP(hipMemcpyAsync(soff.data(), stile_off, sizeof(int32_t) * (ntiles + 1), hipMemcpyDeviceToHost, st));
     SGP_HIP(hipStreamSynchronize(st));
-    if (gb.n && (rc = group_place(L, gb, st))) return rc;
+    if (gb.n && (rc = (L->order == 1 ? group_place<1> : group_place<2>)(L, gb, st))) return rc;
     const int64_t Q = toff[ntiles], Qs = soff[ntiles];
     if (Q < 1 || Q > Lel || Qs < Q || Qs > Lel) {
       set_error("lattice_build: inconsistent run / piece counts %lld / %lld", (long long)Q, (long long)Qs);

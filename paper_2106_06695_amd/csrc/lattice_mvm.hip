@@ -676,7 +676,9 @@ __global__ __launch_bounds__(kBlock) void k_blur2_split(Blur2Args<TU> a) {
 // against pairs (in-place steps of one direction): adjoint of m = 4.2M, d = 16
 // 55 against 141 (95) ms, CG iteration on m = 874,000, d = 11 1.35 against
 // 2.07 (1.71) ms. 512 threads where a row takes eight lanes: 49 against 59 us
-// with 256 (133 registers).
+// with 256 (133 registers). Order 2 (five taps, R = 2) with groups against a
+// launch per direction: MVM of n = 200,003, d = 9, 5 columns 81 against 138 us,
+// 8 CG iterations at n = 1M, d = 11, 11 columns 3.8 against 6.3 ms.
 template <typename TU>
 struct GroupArgs {
   const TU* in[2];          // per chain
@@ -688,7 +690,7 @@ struct GroupArgs {
   int C, chunks;
   unsigned blocks;          // of one chain
   int vec;
-  TU st[3];
+  TU st[5];
 };
 template <int G, typename TU>
 constexpr int group_vw() { return G < 16 / (int)sizeof(TU) ? G : 16 / (int)sizeof(TU); }
@@ -697,19 +699,30 @@ constexpr int group_vw() { return G < 16 / (int)sizeof(TU) ? G : 16 / (int)sizeo
 template <int G, typename TU>
 constexpr int group_threads() { return G / group_vw<G, TU>() > 4 ? kGroupRows * 2 : kGroupRows; }
 
-// The neighbour bytes of rows in the order of a downward pass over nd
-// directions: 16-bit fields 0 .. nd-1 reversed.
-__device__ __forceinline__ uint2 group_reverse(uint2 s, int nd) {
-  uint2 r = {s.y >> 16 | s.y << 16, s.x >> 16 | s.x << 16};  // fields 3 2 1 0
-  if (nd < 4) r = uint2{r.x >> 16 | r.y << 16, r.y >> 16};
-  if (nd < 3) r = uint2{r.x >> 16 | r.y << 16, r.y >> 16};
-  if (nd < 2) r = uint2{r.x >> 16 | r.y << 16, r.y >> 16};
-  return r;
+// A row's neighbour bytes in the order of a downward pass over nd directions:
+// 16-bit (R = 1) or 32-bit fields 0 .. nd-1 reversed.
+template <int R>
+__device__ __forceinline__ void group_reverse(uint32_t (&s)[2 * R], int nd) {
+  if constexpr (R == 1) {
+    uint32_t x = s[1] >> 16 | s[1] << 16, y = s[0] >> 16 | s[0] << 16;  // fields 3 2 1 0
+    for (int i = nd; i < kGroupDirs; ++i) {
+      x = x >> 16 | y << 16;
+      y >>= 16;
+    }
+    s[0] = x;
+    s[1] = y;
+  } else {
+    const uint32_t t[4] = {s[0], s[1], s[2], s[3]};
+    s[0] = nd == 4 ? t[3] : nd == 3 ? t[2] : nd == 2 ? t[1] : t[0];
+    s[1] = nd == 4 ? t[2] : nd == 3 ? t[1] : t[0];
+    s[2] = nd == 4 ? t[1] : t[0];
+    s[3] = t[0];
+  }
 }
 
-template <typename TU, int G>
+template <typename TU, int G, int R>
 __global__ __launch_bounds__((group_threads<G, TU>())) void k_blur_group(
-    const GroupRow* __restrict__ rows, GroupArgs<TU> a) {
+    const GroupRow<R>* __restrict__ rows, GroupArgs<TU> a) {
   constexpr int VW = group_vw<G, TU>();
   constexpr int LPR = G / VW;
   constexpr int RP = group_threads<G, TU>() / LPR;  // rows at a time
@@ -725,12 +738,13 @@ __global__ __launch_bounds__((group_threads<G, TU>())) void k_blur_group(
   const int64_t p0 = (a.tile0[ch] + tile) * kGroupRows + r0;
   const int nd = a.dirs[ch];
   int32_t row[NI];
-  uint2 nb[NI];
+  uint32_t nb[NI][2 * R];
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
-    const GroupRow q = rows[p0 + i * RP];
+    const GroupRow<R> q = rows[p0 + i * RP];
     row[i] = q.point;
-    nb[i] = uint2{q.slots[0], q.slots[1]};
+#pragma unroll
+    for (int w = 0; w < 2 * R; ++w) nb[i][w] = q.slots[w];
   }
   TU v[NI][VW];
 #pragma unroll
@@ -745,7 +759,7 @@ __global__ __launch_bounds__((group_threads<G, TU>())) void k_blur_group(
   }
   if (a.rev[ch]) {
 #pragma unroll
-    for (int i = 0; i < NI; ++i) nb[i] = group_reverse(nb[i], nd);
+    for (int i = 0; i < NI; ++i) group_reverse<R>(nb[i], nd);
   }
   const TU* Ac = A + cl;
 #pragma unroll
@@ -757,13 +771,19 @@ __global__ __launch_bounds__((group_threads<G, TU>())) void k_blur_group(
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-      const uint32_t lh = t & 2 ? nb[i].y : nb[i].x;
-      TU l[VW], h[VW];
-      read_row<TU, VW>(Ac + (lh >> (16 * (t & 1)) & 255) * G, l);
-      read_row<TU, VW>(Ac + (lh >> (16 * (t & 1) + 8) & 255) * G, h);
+      TU x[2 * R][VW];
 #pragma unroll
-      for (int x = 0; x < VW; ++x)
-        v[i][x] = fma_t(a.st[2], h[x], fma_t(a.st[1], v[i][x], fma_t(a.st[0], l[x], (TU)0)));
+      for (int e = 0; e < 2 * R; ++e) {
+        const int at = 2 * R * t + e;
+        read_row<TU, VW>(Ac + (nb[i][at / 4] >> (8 * (at % 4)) & 255) * G, x[e]);
+      }
+#pragma unroll
+      for (int q = 0; q < VW; ++q) {
+        TU o = 0;
+#pragma unroll
+        for (int e = 0; e < 2 * R + 1; ++e) o = fma_t(a.st[e], e < R ? x[e][q] : e == R ? v[i][q] : x[e - 1][q], o);
+        v[i][q] = o;
+      }
     }
   }
 #pragma unroll
@@ -1341,11 +1361,12 @@ int blur_g(const sgp_lattice* L, TU* U0, TU* B1, TU* B2, TU* B3, TU* B4, int C, 
     return chain == 0 ? ((L->blur == SGP_BLUR_REVERSE) ? d - step : step) : d - step;
   };
   const bool fuse = L->order == 1 && blur_fuse_enabled();
+  const bool groups = L->ngroups && blur_fuse_enabled();
   // Large lattices (the four value arrays over 128 MiB by default, half the
   // Infinity Cache): the chains' split launches run one chain after the
   // other (all of chain 0's, then chain 1's), so that a launch's input and
   // output arrays sit in the cache together.
-  bool seq = fuse && sym && blur_seq_for(4.0 * (double)mC * sizeof(TU));
+  bool seq = (fuse || groups) && sym && blur_seq_for(4.0 * (double)mC * sizeof(TU));
   std::vector<Blur2Args<TU>> later;  // chain 1's split launches, in order
   auto launch2 = [&](const Blur2Args<TU>& b, unsigned grid) -> int {
     ProfScope ps(KK_BLUR, s);
@@ -1364,7 +1385,7 @@ int blur_g(const sgp_lattice* L, TU* U0, TU* B1, TU* B2, TU* B3, TU* B4, int C, 
     later.clear();
     return SGP_OK;
   };
-  if (fuse && L->ngroups) {
+  if (groups) {
     const int ng = L->ngroups;
     // A launch only touches its chains' own arrays, and one chain after the
     // other pays late: adjoint of m = 4.2M, d = 16 (254 MiB an array) 54.3
@@ -1375,7 +1396,7 @@ int blur_g(const sgp_lattice* L, TU* U0, TU* B1, TU* B2, TU* B3, TU* B4, int C, 
     b.C = C;
     b.chunks = (C + G - 1) / G;
     b.vec = (C % group_vw<G, TU>() == 0 && aligned16(U0) && aligned16(B1) && aligned16(B2)) ? 1 : 0;
-    for (int t = 0; t < 3; ++t) b.st[t] = a.st[t];
+    for (int t = 0; t < 2 * L->order + 1; ++t) b.st[t] = a.st[t];
     // one group of chain 0 (i0 >= 0) and one of chain 1 (i1 >= 0)
     auto launch = [&](int i0, int i1, bool sum) -> int {
       unsigned n = 0;
@@ -1397,8 +1418,11 @@ int blur_g(const sgp_lattice* L, TU* U0, TU* B1, TU* B2, TU* B3, TU* B4, int C, 
       b.add = sum ? B1 : nullptr;
       b.blocks = (unsigned)(most * b.chunks);
       ProfScope ps(KK_BLUR, s);
-      hipLaunchKernelGGL((k_blur_group<TU, G>), dim3(b.blocks * n), dim3((group_threads<G, TU>())), 0, s,
-                         (const GroupRow*)L->group_rows.ptr, b);
+      const dim3 grid(b.blocks * n), block(group_threads<G, TU>());
+      if (L->order == 1)
+        hipLaunchKernelGGL((k_blur_group<TU, G, 1>), grid, block, 0, s, (const GroupRow<1>*)L->group_rows.ptr, b);
+      else
+        hipLaunchKernelGGL((k_blur_group<TU, G, 2>), grid, block, 0, s, (const GroupRow<2>*)L->group_rows.ptr, b);
       SGP_LAUNCH_CHECK("k_blur_group");
       return SGP_OK;
     };

@@ -52,9 +52,10 @@ constexpr int kGroupPart = kGroupRows - 1;
 constexpr int kMaxGroups = 2 * (kMaxD + 1) / 3;
 constexpr int kGroupClasses = 30;
 constexpr int kGroupWords = kGroupClasses + 1;
+template <int R>
 struct GroupRow {
   int32_t point;
-  uint32_t slots[2];  // four directions' neighbours within the tile, (low, high) bytes
+  uint32_t slots[2 * R];  // four directions' neighbours within the tile, a byte each
 };
 
 // Launch-shape knobs of the MVM kernels. Defaults are the measured best on
@@ -220,13 +221,13 @@ struct sgp_lattice {
   sgp::DevBuf run_dst;    // npiece int32: partial row of each piece; a lattice point's
                           //   pieces occupy rows occ_ptr[j] .. occ_ptr[j+1]-1 in piece order
   sgp::DevBuf nbr;        // (d+1) x m x 2r int32: [direction][internal vertex][offset]
-  // three-tap stencils: groups of blur directions in order (0: none), each
+  // stencils of order 1 and 2: groups of blur directions in order (0: none), each
   // one's directions and tiles, the tiles' rows
   int ngroups = 0;
   int group_dirs[sgp::kMaxGroups] = {};
   int64_t group_tile[sgp::kMaxGroups] = {};   // first tile
   int32_t group_tiles[sgp::kMaxGroups] = {};
-  sgp::DevBuf group_rows;  // GroupRow
+  sgp::DevBuf group_rows;  // GroupRow<order>
   sgp::DevBuf int2can;    // m int32: internal vertex -> canonical index
   sgp::DevBuf keys;       // m x d int32 in canonical order (first occurrence in caller's order)
 

@@ -74,10 +74,11 @@ def build_peak_bytes(N: int, d: int, order: int = 1) -> int:
     every vertex distinct. Per splat entry (N(d+1) of them): 48 bytes of hash
     table, 12 of slots and unsorted entries, about 40 of sort and order
     buffers, 35 of the kept structure, 4 d of keys, 8 order (d+1) of
-    neighbour table and, for order 1, 10 (d+1) of blur groups."""
+    neighbour table and, for orders 1 and 2, (3 + 7 order) (d+1) of blur
+    groups."""
     D = d + 1
     L = N * D
-    return int((136 + 4 * d + (8 * order + 10 * (order == 1)) * D) * L + 8 * N * d + (64 << 20))
+    return int((136 + 4 * d + (8 * order + (3 + 7 * order if order <= 2 else 0)) * D) * L + 8 * N * d + (64 << 20))
 
 
 def solve_bytes(N: int, C: int, d: int, m: int) -> int:

@@ -2,7 +2,7 @@
 separate launches, with groups of four, three, two and one direction (parts
 that outgrow a tile divide their group), a part of exactly a tile's 255 points,
 a lattice that keeps no groups, whole and broken vectors of columns, every blur
-order, and both chains together or one after the other."""
+order, both chains together or one after the other, and stencils of order 2."""
 import numpy as np
 import pytest
 
@@ -104,5 +104,28 @@ def test_chains_one_after_the_other():
         assert 2 * lat.m * C * 4 > 384 << 20  # bytes of the two chains' arrays
         print(f"blur groups in sequence m={lat.m} C={C}", flush=True)
         _run(sgp, lat, X, C, False)
+    finally:
+        lat.free()
+
+
+@pytest.mark.parametrize("d,n,ell,blur", [(5, 60000, 0.6, "symmetric"), (9, 60000, 1.0, "forward"),
+                                          (11, 17000, 1.0, "symmetric"), (20, 3000, 1.0, "reverse")])
+def test_order_2(d, n, ell, blur):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    import paper_2106_06695_amd as sgp
+    X = _points(d, n, "normal")
+    lat = sgp.lattice_build(torch.from_numpy(X).cuda(), np.full(d, ell), order=2, blur=blur)
+    try:
+        print(f"blur groups, order 2, d={d} n={n} m={lat.m}", flush=True)
+        V = torch.ones((n, 3), device="cuda")
+        sgp.lattice_mvm(lat, V)
+        with sgp.profile() as prof:
+            sgp.lattice_mvm(lat, V)
+            torch.cuda.synchronize()
+        assert prof.results["blur"][0] <= (d + 1) // 2 + 1  # groups, not a launch per direction
+        for C, fp64 in ((1, False), (5, False), (16, False), (1, True), (7, True), (16, True)):
+            _run(sgp, lat, X, C, fp64)
     finally:
         lat.free()
