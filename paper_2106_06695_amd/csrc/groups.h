@@ -200,15 +200,19 @@ __host__ __device__ inline int64_t group_tiles(const uint32_t* cnt, int c) {
   return t;
 }
 
-// Each point's row in the group's tiles. No part has more than kGroupPart
-// points.
+// Each point's row in the group's tiles (no part has more than kGroupPart
+// points); also sets all bits of the rows' records, `words` words.
 __global__ __launch_bounds__(256) void k_group_place(int64_t m, const int32_t* __restrict__ parents,
                                                      const int32_t* __restrict__ infos,
-                                                     const uint32_t* __restrict__ cnts, int32_t* __restrict__ place) {
+                                                     const uint32_t* __restrict__ cnts, int32_t* __restrict__ place,
+                                                     uint32_t* __restrict__ rows, int64_t words) {
   __shared__ uint32_t cnt[kGroupClasses];
   __shared__ int32_t tile[kGroupClasses];
   const int g = (int)blockIdx.y;
   const int64_t at = g * m;
+  for (int64_t i = ((int64_t)g * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x; i < words;
+       i += (int64_t)gridDim.x * gridDim.y * blockDim.x)
+    rows[i] = ~0u;
   if (threadIdx.x < kGroupClasses) cnt[threadIdx.x] = cnts[g * kGroupWords + threadIdx.x];
   __syncthreads();
   if (threadIdx.x < kGroupClasses) tile[threadIdx.x] = (int32_t)group_tiles(cnt, threadIdx.x);

@@ -1258,14 +1258,13 @@ int group_place(sgp_lattice* L, GroupBuild& gb, hipStream_t st) {
   const int64_t rows = tiles * kGroupRows;
   int rc;
   if ((rc = dev_alloc(L->group_rows, sizeof(GroupRow<R>) * rows, st))) return rc;
-  if ((rc = launch_fill_u32((uint32_t*)L->group_rows.ptr, (size_t)rows * (sizeof(GroupRow<R>) / 4), 0xffffffffu, st)))
-    return rc;
   const int32_t* info = gb.parent + gb.room * m;
   int32_t* place = gb.parent + 2 * gb.room * m;
   const dim3 grid((unsigned)grid_for(m, kBlock, 4096), (unsigned)gb.n);
   ProfScope ps(KK_NEIGHBORS, st);
   hipLaunchKernelGGL(k_group_place, grid, dim3(kBlock), 0, st, m, (const int32_t*)gb.parent, info,
-                     (const uint32_t*)gb.cnt, place);
+                     (const uint32_t*)gb.cnt, place, (uint32_t*)L->group_rows.ptr,
+                     rows * (int64_t)(sizeof(GroupRow<R>) / 4));
   SGP_LAUNCH_CHECK("k_group_place");
   hipLaunchKernelGGL(k_group_rows<R>, grid, dim3(kBlock), 0, st, (const int32_t*)L->nbr.ptr, m, gb.sp,
                      (const int32_t*)place, (GroupRow<R>*)L->group_rows.ptr);

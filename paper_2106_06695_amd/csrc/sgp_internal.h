@@ -42,7 +42,7 @@ constexpr int64_t tile_slice0(int64_t first_piece, int64_t tile) {
 // (groups.h). With groups against without: one training step on m = 16,185
 // (d = 11, 20 iterations) 2.66 against 2.83 ms, 16 iterations on m = 11,064
 // (d = 8) 1.27 against 1.32 ms; a request of m = 3,677 (build and 16
-// iterations) 1.62 against 1.58 ms, as the groups cost the build eight
+// iterations) 1.62 against 1.58 ms, as the groups cost the build six
 // launches.
 constexpr int64_t kGroupMin = 8192;
 constexpr int64_t kGroupMax = (int64_t)1 << 26;  // part numbers share a word with their class
