@@ -35,15 +35,19 @@ def kernel_bytes(kind: str, n: int, d: int, m: int, C: int, r: int, sym: bool, c
     the values and lattice accumulators are fp64, in lattice_mvm fp32.
     dir_frac: the share of the splat launches that also apply the CG
     direction update (r and x in, p and x out: 24 bytes per element)."""
-    D, T = d + 1, 2 * r
+    D = d + 1
     chains = 2 if sym else 1
     vb = ub = 8 if cg else 4
     if kind == "splat":      # idx + w, V in, U out (+ the fused direction update)
         return n * D * 8 + n * C * vb + m * C * ub + dir_frac * 24 * n * C
     if kind == "slice":      # idx + w, U (both chains) in, out (+ p and r in inside CG, out being r)
         return n * D * 8 + chains * m * C * ub + n * C * vb + (2 * n * C * vb if cg else 0)
+    if kind == "cg_tile":    # lattice CG: idx + w, the rhs (fp32) and the lattice residual in
+        return n * D * 8 + n * C * 4 + m * C * 8
+    if kind == "cg_lattice":  # B u, y_r, y_p, y_x in, the last three out (fp64)
+        return 7 * m * C * 8
     if kind == "blur":       # average per launch: per chain U in, U out, neighbour lists
-        return blur_bytes_per_mvm(d, m, C, r, sym, cg) / blur_launches(d, r)
+        return blur_bytes_per_mvm(d, m, C, r, sym, cg) / blur_launches(d, m, r, sym)
     if kind == "cg_alpha":   # u and B u in (fp64)
         return 2 * m * C * 8
     if kind == "cg_dir":     # p, r in (fp64), x in (fp32); p out (fp64), x out (fp32)
@@ -73,9 +77,11 @@ def survey_bytes(kind: str, n: int, d: int, m: int, C: int, r: int, sym: bool,
     if kind == "splat":      # k_splat_tile alone: W and V in (U is the gather's)
         return n * D * 8 + n * C * 4 + dir_frac * 16 * n * C
     if kind == "blur":
-        return blur_bytes_per_mvm(d, m, C, r, sym, False) / blur_launches(d, r)
+        return blur_bytes_per_mvm(d, m, C, r, sym, False) / blur_launches(d, m, r, sym)
     if kind == "slice":      # CG variant: idx + w, U, p and r in, r out
         return n * D * 8 + chains * m * C * 4 + 3 * n * C * 4
+    if kind == "cg_tile":    # lattice CG: W, the rhs and the lattice residual in (U is the gather's)
+        return n * D * 8 + n * C * 4 + m * C * 4
     if kind == "cg_alpha":   # u and B u in
         return 2 * m * C * 4
     if kind == "cg_dir":     # p, r, x in; p, x out
@@ -83,21 +89,26 @@ def survey_bytes(kind: str, n: int, d: int, m: int, C: int, r: int, sym: bool,
     return 0.0
 
 
-def blur_launches(d, r):
-    """Launches per blur: with a three-tap stencil two direction steps share
-    a launch (the intermediate lattice values stay in registers)."""
+def blur_passes(d, m, r):
+    """Passes over a chain's lattice values per blur: one per group of up to
+    four directions where the lattice keeps groups, else one per two
+    directions (three-tap stencil) or per direction."""
+    if r <= 2 and d >= 5 and m >= 8192:
+        return (d + 4) // 4
     return (d + 2) // 2 if r == 1 else d + 1
+
+
+def blur_launches(d, m, r, sym):
+    """Launches per blur: with groups, the chains' last passes do not share
+    one."""
+    grouped = r <= 2 and d >= 5 and m >= 8192
+    return blur_passes(d, m, r) + (1 if grouped and sym else 0)
 
 
 def blur_bytes_per_mvm(d, m, C, r, sym, cg):
     ub = 8 if cg else 4
-    T = 2 * r
     chains = 2 if sym else 1
-    if r == 1:
-        pairs, single = (d + 1) // 2, (d + 1) % 2
-        return (pairs * chains * (2 * m * C * ub + 2 * T * m * 4)
-                + single * chains * (2 * m * C * ub + T * m * 4))
-    return (d + 1) * chains * (2 * m * C * ub + T * m * 4)
+    return chains * (blur_passes(d, m, r) * 2 * m * C * ub + (d + 1) * 2 * r * m * 4)
 
 
 def mvm_bytes(n, d, m, C, r, sym, cg=False):
@@ -109,7 +120,9 @@ def mvm_bytes(n, d, m, C, r, sym, cg=False):
 # traffic is reported only while they are unchanged.
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "ws3_traffic.json")
 TRAFFIC_SOURCES = ["paper_2106_06695_amd/csrc/lattice_mvm.hip", "paper_2106_06695_amd/csrc/sgp_internal.h",
-                   "paper_2106_06695_amd/csrc/cg.hip", "paper_2106_06695_amd/csrc/cg_step.h"]
+                   "paper_2106_06695_amd/csrc/cg.hip", "paper_2106_06695_amd/csrc/cg_step.h",
+                   "paper_2106_06695_amd/csrc/cg_tile.h", "paper_2106_06695_amd/csrc/lattice_col.h",
+                   "paper_2106_06695_amd/csrc/tile.h"]
 
 
 def sources_digest() -> dict:
@@ -117,9 +130,8 @@ def sources_digest() -> dict:
     return {f: hashlib.sha256(open(os.path.join(ROOT, f), "rb").read()).hexdigest() for f in TRAFFIC_SOURCES}
 
 
-TRAFFIC_KERNELS = {"splat": ["k_splat_tile"], "splat_stage": ["k_splat_tile", "k_splat_gather", "k_gather_fix"],
-                   "blur": ["k_blur"], "slice": ["k_slice_tile"], "cg_alpha": ["k_cg_alpha"],
-                   "cg_dir": ["k_cg_dir"]}
+TRAFFIC_KERNELS = {"splat": ["k_cg_tile"], "splat_stage": ["k_cg_tile", "k_splat_gather", "k_gather_fix"],
+                   "blur": ["k_blur"], "cg_alpha": ["k_cg_alpha"], "cg_dir": ["k_cg_lattice"]}
 
 
 def stored_traffic(stage: str):
@@ -526,10 +538,14 @@ def main(argv=None):
         torch.cuda.synchronize()
     # every splat but a solve's first applies the previous direction update
     dir_frac = (iters - 1) / iters
+    # where the solve's vectors live on the lattice one kernel (timed as the
+    # splat) slices the residual, sums r.r and splats it
+    lattice_cg = not prof.results["slice"][0]
     kernels = {}
     for kind, (launches, ms) in prof.results.items():
         if launches:
-            b = kernel_bytes(kind, n, d, m, C, 1, sym, cg=True, dir_frac=dir_frac)
+            model = {"splat": "cg_tile", "cg_dir": "cg_lattice"}.get(kind, kind) if lattice_cg else kind
+            b = kernel_bytes(model, n, d, m, C, 1, sym, cg=True, dir_frac=dir_frac)
             avg = ms / launches
             kernels[kind] = {"launches": launches, "total_ms": round(ms, 3), "avg_us": round(avg * 1e3, 2),
                              "algo_GBps": round(b / (avg / 1e3) / 1e9, 1) if b else None}
@@ -552,7 +568,7 @@ def main(argv=None):
                 "operand_bytes_per_launch": native_b}
 
     names = {"splat": "k_splat_tile<double, G, true> (with the fused CG direction update)",
-             "blur": "k_blur2_split / k_blur2",
+             "blur": "k_blur_group",
              "slice": "k_slice_tile<double, G, true> (with the fused CG residual update)",
              "cg_alpha": "k_cg_alpha", "cg_dir": "k_cg_dir"}
     single = {k: kernels[k]["total_ms"] for k in names if k in kernels}
@@ -560,12 +576,23 @@ def main(argv=None):
     splat_native = kernel_bytes("splat", n, d, m, C, 1, sym, cg=True, dir_frac=dir_frac)
     dom_survey = survey_bytes(dom, n, d, m, C, 1, sym, dir_frac=dir_frac)
     dom_native = kernel_bytes(dom, n, d, m, C, 1, sym, cg=True, dir_frac=dir_frac)
-    if dom == "splat":  # the tile kernel alone reads W and V; U is written by the gather
-        dom_native -= m * C * 8
+    if lattice_cg:
+        tile_s, tile_n = (f("cg_tile", n, d, m, C, 1, sym) for f in
+                          (survey_bytes, lambda *a: kernel_bytes(*a, cg=True)))
+        names["cg_dir"] = "k_cg_lattice"
+        if dom == "cg_dir":
+            dom_survey, dom_native = 7 * m * C * 4, 7 * m * C * 8
+        names["splat"] = "k_cg_tile<G, 1, CV> (slice of the residual, r.r and its splat)"
+        if dom == "splat":
+            dom_survey, dom_native = tile_s, tile_n
+        stage = ("k_cg_tile + k_splat_gather + k_gather_fix", tile_s + 2 * m * C * 4, tile_n + 2 * m * C * 8)
+    else:
+        if dom == "splat":  # the tile kernel alone reads W and V; U is written by the gather
+            dom_native -= m * C * 8
+        stage = ("k_splat_tile + k_splat_gather + k_gather_fix",
+                 survey_bytes("splat_stage", n, d, m, C, 1, sym, dir_frac=dir_frac), splat_native)
     roofline = roof(names[dom], [dom], dom_survey, dom_native, dom)
-    splat_stage = roof("k_splat_tile + k_splat_gather + k_gather_fix", ["splat", "splat_gather"],
-                       survey_bytes("splat_stage", n, d, m, C, 1, sym, dir_frac=dir_frac), splat_native,
-                       "splat_stage")
+    splat_stage = roof(stage[0], ["splat", "splat_gather"], stage[1], stage[2], "splat_stage")
 
     # standalone MVMs on a resident lattice (outside the timed steps)
     lat = sgp.lattice_build(X, w.lengthscales, blur=args.blur)
