@@ -76,9 +76,7 @@ __global__ __launch_bounds__(kColThreads) void k_lattice_col(TU* __restrict__ U,
       const int64_t at = (int64_t)j * a.C + c;
       TU x = U[at];
       if (g0 != g1) {  // rows in several ranges: their fragments in range order
-        TU s = frag[((int64_t)g0 * 2 + (js == g0 << a.rshift ? 0 : 1)) * a.C + c];
-        for (int g = g0 + 1; g <= g1; ++g) s += frag[(int64_t)g * 2 * a.C + c];
-        x = s;
+        x = frag_sum(frag, ((int64_t)g0 * 2 + (js == g0 << a.rshift ? 0 : 1)) * a.C + c, g0, g1, a.C, c);
         U[at] = x;
       }
       u[i] = x;

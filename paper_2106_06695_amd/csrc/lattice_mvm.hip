@@ -366,16 +366,11 @@ __global__ __launch_bounds__(kBlock) void k_gather_fix(const int32_t* __restrict
     if (g0 == g1 || (je - 1) / R != g1) continue;  // starts here, or ends further on
     const int64_t first = (g0 * 2 + (js == g0 * R ? 0 : 1)) * C + c;
     if (elem == 8) {
-      const double* frag = (const double*)frag_v;
-      double acc = frag[first];
-      for (int64_t g = g0 + 1; g <= g1; ++g) acc += frag[(g * 2) * C + c];
+      const double acc = frag_sum((const double*)frag_v, first, g0, g1, C, c);
       double* dst = (double*)U_v + j * C + c;
       *dst = beta ? fma_t(beta[c], *dst, acc) : acc;
     } else {
-      const float* frag = (const float*)frag_v;
-      float acc = frag[first];
-      for (int64_t g = g0 + 1; g <= g1; ++g) acc += frag[(g * 2) * C + c];
-      ((float*)U_v)[j * C + c] = acc;
+      ((float*)U_v)[j * C + c] = frag_sum((const float*)frag_v, first, g0, g1, C, c);
     }
   }
 }
