@@ -198,27 +198,36 @@ void idle_cache_info(int64_t* bytes, int32_t* blocks) {
   if (blocks) *blocks = k;
 }
 
-int dev_alloc(DevBuf& b, size_t bytes, hipStream_t s) {
+hipError_t dev_try_alloc(DevBuf& b, size_t bytes, hipStream_t s) {
   b.ptr = nullptr;
   b.bytes = 0;
   b.cap = 0;
-  if (bytes == 0) return SGP_OK;
+  if (bytes == 0) return hipSuccess;
   size_t cap = 0;
   if ((b.ptr = block_take(bytes, &cap))) {
     b.bytes = bytes;
     b.cap = cap;
-    return SGP_OK;
+    return hipSuccess;
   }
   hipError_t e = pool_alloc(&b.ptr, bytes, s);
   if (e != hipSuccess) {
     b.ptr = nullptr;
     (void)hipGetLastError();
-    set_error("device allocation of %zu bytes failed: %s", bytes, hipGetErrorString(e));
-    return e == hipErrorOutOfMemory ? SGP_ENOMEM : SGP_EHIP;
+    return e;
   }
   b.bytes = bytes;
   b.cap = bytes;
-  return SGP_OK;
+  return hipSuccess;
+}
+
+int alloc_failed(size_t bytes, hipError_t e) {
+  set_error("device allocation of %zu bytes failed: %s", bytes, hipGetErrorString(e));
+  return e == hipErrorOutOfMemory ? SGP_ENOMEM : SGP_EHIP;
+}
+
+int dev_alloc(DevBuf& b, size_t bytes, hipStream_t s) {
+  const hipError_t e = dev_try_alloc(b, bytes, s);
+  return e == hipSuccess ? SGP_OK : alloc_failed(bytes, e);
 }
 
 // Device memory comes from a library-owned stream-ordered pool per device

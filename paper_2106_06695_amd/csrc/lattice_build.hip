@@ -1117,18 +1117,20 @@ struct Transient {
   size_t cap[kSlots] = {};
   hipStream_t s = nullptr;
   bool idle = false;
-  int alloc(int slot_i, size_t bytes) {
+  hipError_t try_alloc(int slot_i, size_t bytes) {  // leaves no error message
     if (!bytes) bytes = 16;
-    if ((ptr[slot_i] = block_take(bytes, &cap[slot_i]))) return SGP_OK;
+    if ((ptr[slot_i] = block_take(bytes, &cap[slot_i]))) return hipSuccess;
     cap[slot_i] = bytes;
-    hipError_t e = pool_alloc(&ptr[slot_i], bytes, s);
+    const hipError_t e = pool_alloc(&ptr[slot_i], bytes, s);
     if (e != hipSuccess) {
       ptr[slot_i] = nullptr;
       (void)hipGetLastError();
-      set_error("device allocation of %zu bytes failed: %s", bytes, hipGetErrorString(e));
-      return e == hipErrorOutOfMemory ? SGP_ENOMEM : SGP_EHIP;
     }
-    return SGP_OK;
+    return e;
+  }
+  int alloc(int slot_i, size_t bytes) {
+    const hipError_t e = try_alloc(slot_i, bytes);
+    return e == hipSuccess ? SGP_OK : alloc_failed(bytes, e);
   }
   ~Transient() {
     for (int i = 0; i < kSlots; ++i) {
@@ -1256,8 +1258,10 @@ int group_place(sgp_lattice* L, GroupBuild& gb, hipStream_t st) {
   }
   if (tiles * kGroupRows > gb.n * (m + m / 4 + 2 * kGroupClasses * kGroupRows)) return SGP_OK;
   const int64_t rows = tiles * kGroupRows;
-  int rc;
-  if ((rc = dev_alloc(L->group_rows, sizeof(GroupRow<R>) * rows, st))) return rc;
+  // a lattice that has no room for them does without
+  const hipError_t e = dev_try_alloc(L->group_rows, sizeof(GroupRow<R>) * rows, st);
+  if (e == hipErrorOutOfMemory) return SGP_OK;
+  if (e != hipSuccess) return alloc_failed(sizeof(GroupRow<R>) * rows, e);
   const int32_t* info = gb.parent + gb.room * m;
   int32_t* place = gb.parent + 2 * gb.room * m;
   const dim3 grid((unsigned)grid_for(m, kBlock, 4096), (unsigned)gb.n);
@@ -1564,8 +1568,8 @@ int build_attempt(sgp_lattice* L, const float* X, const double* f, double load_f
   // for the counts, further on)
   GroupBuild gb;
   L->ngroups = 0;
-  if (L->order <= 2 && d >= 5 && m >= kGroupMin && m <= kGroupMax) {
-    if ((rc = tr.alloc(T_GROUP, sizeof(uint32_t) * kMaxGroups * kGroupWords))) return rc;
+  if (L->order <= 2 && d >= 5 && m >= kGroupMin && m <= kGroupMax &&
+      tr.try_alloc(T_GROUP, sizeof(uint32_t) * kMaxGroups * kGroupWords) == hipSuccess) {
     // T_NBRC has been read: at least 2 (d + 1) words a point, three a group
     const auto start = L->order == 1 ? group_start<1> : group_start<2>;
     if ((rc = start(L, gb, nbr_can, (uint32_t*)tr.ptr[T_GROUP], host_word + 4 + 2 * kMaxD, st))) return rc;

@@ -144,6 +144,10 @@ struct DevBuf {
 // the library synchronises the whole device, so lattices driven from
 // different streams overlap.
 int dev_alloc(DevBuf& b, size_t bytes, hipStream_t s);
+// The same where the caller can do without: no error message is left.
+hipError_t dev_try_alloc(DevBuf& b, size_t bytes, hipStream_t s);
+// The message and the return code of an allocation that failed.
+int alloc_failed(size_t bytes, hipError_t e);
 // Release a buffer the device is done with (the caller has waited for its
 // last use): it is kept for reuse by later allocations of a similar size.
 void dev_free(DevBuf& b);
@@ -221,8 +225,9 @@ struct sgp_lattice {
   sgp::DevBuf run_dst;    // npiece int32: partial row of each piece; a lattice point's
                           //   pieces occupy rows occ_ptr[j] .. occ_ptr[j+1]-1 in piece order
   sgp::DevBuf nbr;        // (d+1) x m x 2r int32: [direction][internal vertex][offset]
-  // stencils of order 1 and 2: groups of blur directions in order (0: none), each
-  // one's directions and tiles, the tiles' rows
+  // stencils of order 1 and 2: groups of blur directions in order (0: none, as
+  // where there is no memory for them), each one's directions and tiles, the
+  // tiles' rows
   int ngroups = 0;
   int group_dirs[sgp::kMaxGroups] = {};
   int64_t group_tile[sgp::kMaxGroups] = {};   // first tile

@@ -1,0 +1,95 @@
+"""Allocations that fail. A lattice that has no memory for its blur groups is
+built without them; any other failure is reported and leaves the library
+usable."""
+import gc
+
+import numpy as np
+import pytest
+
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+class Allocator:
+    """Device memory from torch; the failing hook returns no memory for the
+    allocations that `refuse(index, bytes)` names."""
+
+    def __init__(self):
+        import torch
+        self.torch, self.dev = torch, torch.cuda.current_device()
+        self.sizes, self.refuse = [], lambda i, n: False
+
+    def alloc(self, nbytes, stream):
+        self.sizes.append(nbytes)
+        if self.refuse(len(self.sizes) - 1, nbytes):
+            return 0
+        return self.torch.cuda.caching_allocator_alloc(nbytes, self.dev, stream)
+
+    def free(self, ptr, stream):
+        self.torch.cuda.caching_allocator_delete(ptr)
+
+
+@pytest.fixture()
+def mem():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    import paper_2106_06695_amd as sgp
+    a = Allocator()
+    gc.collect()
+    sgp.set_allocator(a.alloc, a.free)
+    try:
+        yield sgp, a
+    finally:
+        gc.collect()
+        sgp.set_allocator(None, None)
+
+
+def _cuda(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda()
+
+
+def _blur_launches(sgp, lat, V):
+    import torch
+    with sgp.profile() as prof:
+        sgp.lattice_mvm(lat, V)
+        torch.cuda.synchronize()
+    return prof.results["blur"][0]
+
+
+@pytest.mark.parametrize("order", [1, 2])
+def test_build_with_an_allocation_refused(mem, order):
+    """Each allocation of a build refused in turn: an error, or a lattice
+    without groups (the fused pairs, or a launch per direction of the wider
+    stencil) whose products are the same bit for bit."""
+    sgp, a = mem
+    d, n = 11, 17000
+    w = workloads.small_case(500, n, d, channels=3, kind="mixture")
+    X, V = _cuda(w.X), _cuda(w.values)
+    lat = sgp.lattice_build(X, w.lengthscales, order=order)
+    count = len(a.sizes)
+    assert lat.m >= 8192 and _blur_launches(sgp, lat, V) == 4  # three groups
+    ref = sgp.lattice_mvm(lat, V).cpu().numpy()
+    lat.free()
+    without = 0
+    for i in range(count):
+        print(f"build order={order}: allocation {i} of {count} refused", flush=True)
+        a.sizes.clear()
+        a.refuse = lambda k, nbytes: k == i
+        try:
+            lat = sgp.lattice_build(X, w.lengthscales, order=order)
+        except sgp.SGPError as e:
+            assert e.code == -2
+            continue
+        finally:
+            a.refuse = lambda k, nbytes: False
+        without += 1
+        assert _blur_launches(sgp, lat, V) == ((d + 2) // 2 if order == 1 else d + 1)
+        np.testing.assert_array_equal(sgp.lattice_mvm(lat, V).cpu().numpy(), ref)
+        lat.free()
+    assert without == 2  # the groups' rows, and their counts
+    lat = sgp.lattice_build(X, w.lengthscales, order=order)
+    np.testing.assert_array_equal(sgp.lattice_mvm(lat, V).cpu().numpy(), ref)
+    lat.free()
