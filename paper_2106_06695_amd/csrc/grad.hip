@@ -181,25 +181,52 @@ extern "C" int lattice_mvm_grad(const sgp_lattice* L, const float* X, const floa
   } guard{bufs, s};
   const int kb = std::max(1, std::min((int)C, 128 / CH));  // columns per batch
   // channels per MVM: all of a batch's, unless the lattice arrays of m x W
-  // fp32 would be large. The blur by groups reads and writes each row once a
+  // fp32 would be large. The fused pairs of the blur want two arrays near the
+  // 256 MiB Infinity Cache. The blur by groups reads and writes each row once a
   // group, so that rows of at least 64 bytes (W = 16) pay, whatever the arrays'
   // size: m = 4.2M, d = 16, 8 columns: blur and gather of a pass 31 and
-  // 6.7 ms with W = 16, 30 and 10 ms with W = 32. Without groups the fused pairs
-  // want the two arrays near the 256 MiB Infinity Cache.
+  // 6.7 ms with W = 16, 30 and 10 ms with W = 32. These arrays are up to four
+  // times as large, so where there is no memory for them the blocks are halved,
+  // down to the width that the pairs would have.
+  const int all = kb * CH;
   int W = 64;
-  while (W > (L->ngroups ? 16 : 4) && 2.0 * (double)L->m * W * sizeof(float) > 320.0 * (1 << 20)) W >>= 1;
-  if (W >= kb * CH) W = kb * CH;
-  const int nblk_max = (kb * CH + W - 1) / W;
-  const size_t hbytes = sizeof(float) * (size_t)n * nblk_max * W;
-  const size_t sizes[4] = {hbytes, hbytes, sizeof(double) * n * d, sizeof(double) * kColBlocks * d};
-  for (int k = 0; k < 4; ++k) {
-    hipError_t e = pool_alloc(&bufs[k], sizes[k], s);
-    if (e != hipSuccess) {
-      bufs[k] = nullptr;
-      (void)hipGetLastError();
-      set_error("lattice_mvm_grad: device allocation of %zu bytes failed", sizes[k]);
+  while (W > 4 && 2.0 * (double)L->m * W * sizeof(float) > 320.0 * (1 << 20)) W >>= 1;
+  const int narrowest = W;
+  if (L->ngroups && W < 16) W = 16;
+  sgp_lattice* Lm = const_cast<sgp_lattice*>(L);
+  for (;; W >>= 1) {
+    const int Wm = std::min(W, all);
+    const size_t hbytes = sizeof(float) * (size_t)n * ((all + Wm - 1) / Wm) * Wm;
+    const size_t sizes[4] = {hbytes, hbytes, sizeof(double) * n * d, sizeof(double) * kColBlocks * d};
+    const size_t work = mvm_f32_work_bytes(L, Wm);
+    size_t bytes = 0;
+    hipError_t e = hipSuccess;
+    for (int k = 0; k < 4 && e == hipSuccess; ++k) {
+      bytes = sizes[k];
+      e = pool_alloc(&bufs[k], bytes, s);
+      if (e != hipSuccess) bufs[k] = nullptr;
+    }
+    if (e == hipSuccess && L->ubuf.bytes < work) {
+      if (const int rc = wait_last_use(L)) return rc;
+      dev_free(Lm->ubuf);
+      bytes = work;
+      e = dev_try_alloc(Lm->ubuf, work, s);
+    }
+    if (e == hipSuccess) {
+      W = Wm;
+      break;
+    }
+    (void)hipGetLastError();
+    if (e != hipErrorOutOfMemory || W <= narrowest) {
+      set_error("lattice_mvm_grad: device allocation of %zu bytes failed", bytes);
       return e == hipErrorOutOfMemory ? SGP_ENOMEM : SGP_EHIP;
     }
+    for (void*& b : bufs) {
+      dev_release(b, s);
+      b = nullptr;
+    }
+    if (const int rc = wait_last_use(L)) return rc;
+    dev_free(Lm->ubuf);
   }
   float* H = (float*)bufs[0];
   float* O = (float*)bufs[1];

@@ -1845,6 +1845,8 @@ int mvm_f64(const sgp_lattice* L, const double* V, int C, double* out, hipStream
   return mvm_dispatch<double>(L, V, nullptr, C, out, s, 0.0, nullptr);
 }
 
+size_t mvm_f32_work_bytes(const sgp_lattice* L, int C) { return sizeof(float) * mvm_work_elems(L, C, false); }
+
 int mvm_f32(const sgp_lattice* L, const float* V, int C, float* out, hipStream_t s) {
   return mvm_dispatch<float>(L, V, nullptr, C, out, s, 0.f, nullptr);
 }

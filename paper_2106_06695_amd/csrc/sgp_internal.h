@@ -301,6 +301,7 @@ int cg_lat_iter(const sgp_lattice* L, int C, const CgLat& cl, bool first, hipStr
 int cg_lat_out(const sgp_lattice* L, int C, const CgLat& cl, hipStream_t s);
 // fp64 values and accumulation, internal point order, no epilogue
 int mvm_f64(const sgp_lattice* L, const double* V, int C, double* out, hipStream_t s);
-// fp32 values and accumulation, internal point order
+// fp32 values and accumulation, internal point order, and its work memory
+size_t mvm_f32_work_bytes(const sgp_lattice* L, int C);
 int mvm_f32(const sgp_lattice* L, const float* V, int C, float* out, hipStream_t s);
 }  // namespace sgp

@@ -1,6 +1,6 @@
 """Allocations that fail. A lattice that has no memory for its blur groups is
-built without them; any other failure is reported and leaves the library
-usable."""
+built without them, and an adjoint without memory for its wide blocks filters
+narrower ones; any other failure is reported and leaves the library usable."""
 import gc
 
 import numpy as np
@@ -92,4 +92,40 @@ def test_build_with_an_allocation_refused(mem, order):
     assert without == 2  # the groups' rows, and their counts
     lat = sgp.lattice_build(X, w.lengthscales, order=order)
     np.testing.assert_array_equal(sgp.lattice_mvm(lat, V).cpu().numpy(), ref)
+    lat.free()
+
+
+def test_adjoint_narrows_its_blocks(mem):
+    """A lattice with groups whose work arrays for 16 channels find no memory:
+    the adjoint filters narrower blocks, with the same bits; with no memory for
+    those either, an error, and the next call is served."""
+    sgp, a = mem
+    n, d = 200000, 16
+    rng = np.random.default_rng(d)
+    X = _cuda(rng.standard_normal((n, d)))
+    V, G = _cuda(rng.standard_normal((n, 2))), _cuda(rng.standard_normal((n, 2)))
+    lat = sgp.lattice_build(X, np.full(d, 0.5))
+    print(f"adjoint blocks: m={lat.m}", flush=True)
+    assert 2 * lat.m * 16 * 4 > 320 << 20  # the fused pairs would take 8 channels
+    a.sizes.clear()
+    dX, dl = sgp.lattice_mvm_grad(lat, X, V, G)
+    ref, wide = dX.cpu().numpy(), max(a.sizes)
+    assert wide >= 4 * 16 * 4 * lat.m  # a block of 16
+    lat.free()
+    lat = sgp.lattice_build(X, np.full(d, 0.5))
+    a.refuse = lambda i, nbytes: nbytes >= wide
+    dX2, dl2 = sgp.lattice_mvm_grad(lat, X, V, G)
+    np.testing.assert_array_equal(dX2.cpu().numpy(), ref)
+    np.testing.assert_array_equal(np.asarray(dl2), np.asarray(dl))
+    a.refuse = lambda i, nbytes: False
+    lat.free()
+    lat = sgp.lattice_build(X, np.full(d, 0.5))
+    m = lat.m
+    a.refuse = lambda i, nbytes: nbytes >= 4 * 8 * 4 * m  # a block of 8
+    with pytest.raises(sgp.SGPError) as e:
+        sgp.lattice_mvm_grad(lat, X, V, G)
+    assert e.value.code == -2
+    a.refuse = lambda i, nbytes: False
+    dX2, _ = sgp.lattice_mvm_grad(lat, X, V, G)
+    np.testing.assert_array_equal(dX2.cpu().numpy(), ref)
     lat.free()
