@@ -264,19 +264,22 @@ int sgp_cg_fuse_enable(int on);
 
 /* Autotuning of the MVM's launch shape (the multi-column lattice filter of
  * Section 3.2, batched as in the mBCG solver of Section 2). Times every
- * candidate on lattice L for C columns, fp64 (the CG path, C <= 64) or
- * fp32 (lattice_mvm), with reps timed MVMs each after one warm-up: the
- * channel chunk width (the widest that fits the LDS budget, half, quarter)
- * times the resident blocks per CU of the persistent splat and slice (as
- * many as fit, or one). The fastest is kept process-wide for lattices of
- * the same d, column width class (C rounded up to a power of two), element
- * size and size class (m rounded up to a power of two) and is used by later
+ * candidate on lattice L for C columns, fp64 (iterations of cg_solve, C <= 64)
+ * or fp32 (lattice_mvm), with reps timed MVMs or iterations each after a
+ * warm-up: the channel chunk width (the widest that fits the LDS budget, half,
+ * quarter) times the resident blocks per CU of the persistent splat and slice
+ * (as many as fit, or one). On a lattice whose solves keep their vectors per
+ * lattice point (cg_solve) one tile kernel stands for both and takes the
+ * splat's. The fastest is kept process-wide for lattices of the same d, column
+ * width class (C rounded up to a power of two), element size, size class (m
+ * rounded up to a power of two) and form of the solve, and is used by later
  * lattice_mvm and cg_solve calls; no choice changes any result bit.
- * Allocates two n x C work arrays for the duration of the call and
- * synchronises the stream. choice (may be NULL) receives {chunk width,
- * splat blocks per CU, slice blocks per CU} (0: as many as fit);
- * ms_per_mvm (may be NULL) the fastest time. Returns SGP_EINVAL for a NULL
- * lattice, C < 1, C > 64 in fp64 or reps < 1. */
+ * Allocates two n x C fp32 work arrays for the duration of the call, grows the
+ * lattice's work buffers as one such call would, and synchronises the stream.
+ * choice (may be NULL) receives {chunk width, splat blocks per CU, slice blocks
+ * per CU} (0: as many as fit, or no slice); ms_per_mvm (may be NULL) the
+ * fastest time of one MVM or iteration. Returns SGP_EINVAL for a NULL lattice,
+ * C < 1, C > 64 in fp64 or reps < 1. */
 int sgp_autotune(const sgp_lattice* L, int32_t C, int32_t fp64, int32_t reps, void* stream,
                  int32_t* choice, float* ms_per_mvm);
 

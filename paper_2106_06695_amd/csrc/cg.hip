@@ -297,8 +297,23 @@ void defer_graph(hipGraph_t g, hipGraphExec_t e) {
   t_idle_exec = e;
 }
 
-int cg_run(const sgp_lattice* L, const float* b, int C, float noise, float tol, int max_iter,
-           float* x, int32_t* iters, float* rel, hipStream_t s) {
+// The buffers and hooks of a solve. Work buffers are grown here; those of the
+// point form's MVM by its first iteration.
+struct CgSetup {
+  bool lat;
+  double *r, *p;
+  float* x32;
+  CgState* st;
+  double* rr_parts;
+  unsigned* counter;
+  int64_t iparts;
+  CgHook start;
+  CgMvm mvm;
+  CgLat cl;
+};
+
+int cg_setup(const sgp_lattice* L, const float* b, int C, float noise, float tol, float* x, hipStream_t s,
+             CgSetup* o) {
   sgp_lattice* Lm = const_cast<sgp_lattice*>(L);
   const int64_t n = L->n, nC = n * C;
   int rc;
@@ -320,74 +335,86 @@ int cg_run(const sgp_lattice* L, const float* b, int C, float noise, float tol, 
   const size_t st_bytes = ((sizeof(CgState) + 255) / 256) * 256;
   const size_t red_bytes = rr_bytes + al_bytes + pp_bytes + st_bytes + 256;
   if ((rc = dev_reserve(L, Lm->cgred, red_bytes, s))) return rc;
-  double* r = (double*)Lm->cgvec.ptr;
-  double* p = r + nC;
-  float* x32 = (float*)(p + nC);
   char* red = (char*)Lm->cgred.ptr;
-  double* rr_parts = (double*)red;
   double* al_parts = (double*)(red + rr_bytes);
-  double* pp_parts = (double*)(red + rr_bytes + al_bytes);
   CgState* st = (CgState*)(red + rr_bytes + al_bytes + pp_bytes);
   unsigned* counter = (unsigned*)(red + rr_bytes + al_bytes + pp_bytes + st_bytes);
-
-  int32_t* host = (int32_t*)pinned_scratch(sizeof(int32_t) * 3 * kMaxCgCols);
-  if (!host) {
-    set_error("cg_solve: pinned host scratch unavailable");
-    return SGP_ENOMEM;
-  }
-
-  const dim3 block(kBlock);
-  const dim3 igrid((unsigned)std::min<int64_t>(iparts, 65536));
-  const size_t vlds = cg_vec_lds(C);
-  const CgHook h_start{rr_parts, iparts, st, counter, (int)SM_START, (double)tol, 0.0, 0};
-  CgMvm cgm;
+  o->lat = lat;
+  o->r = (double*)Lm->cgvec.ptr;
+  o->p = o->r + nC;
+  o->x32 = (float*)(o->p + nC);
+  o->rr_parts = (double*)red;
+  o->st = st;
+  o->counter = counter;
+  o->iparts = iparts;
+  o->start = CgHook{o->rr_parts, iparts, st, counter, (int)SM_START, (double)tol, 0.0, 0};
+  CgMvm& cgm = o->mvm;
   cgm.alpha = CgHook{al_parts, lparts + groups, st, counter, (int)SM_ALPHA, (double)tol, 0.0, 0};
   cgm.lat_parts = lparts;
-  cgm.pp = pp_parts;
+  cgm.pp = (double*)(red + rr_bytes + al_bytes);
   cgm.ntiles = L->ntiles;
-  cgm.beta = CgHook{rr_parts, L->ntiles, st, counter, (int)SM_BETA, (double)tol, 0.0, 0};
-  cgm.r = r;
+  cgm.beta = CgHook{o->rr_parts, L->ntiles, st, counter, (int)SM_BETA, (double)tol, 0.0, 0};
+  cgm.r = o->r;
   // The same solve with its vectors on the lattice: the first tile pass
   // starts it, the last one forms x.
-  CgLat cl;
+  CgLat& cl = o->cl;
   cl.rhs = b;
   cl.x = x;
   cl.bs = (float*)Lm->cgvec.ptr;
   cl.work = (double*)Lm->ubuf.ptr;
   cl.noise = (double)noise;
   cl.lat_parts = lparts;
-  cl.start = CgHook{rr_parts, L->ntiles, st, counter, (int)SM_START, (double)tol, 0.0, 0};
+  cl.start = CgHook{o->rr_parts, L->ntiles, st, counter, (int)SM_START, (double)tol, 0.0, 0};
   cl.alpha = CgHook{al_parts, lparts, st, counter, (int)SM_ALPHA_LAT, (double)tol, (double)noise, 0};
   cl.beta = cgm.beta;
-  if ((rc = launch_fill_u32(counter, 1, 0u, s))) return rc;
-  if (lat) {
-    if ((rc = cg_lat_start(L, C, cl, s))) return rc;
-  } else {
+  return SGP_OK;
+}
+
+// x = 0, r = p = b and the starting r.r.
+int cg_begin(const sgp_lattice* L, const CgSetup& cs, int C, hipStream_t s) {
+  int rc;
+  if ((rc = launch_fill_u32(cs.counter, 1, 0u, s))) return rc;
+  if (cs.lat) return cg_lat_start(L, C, cs.cl, s);
+  {
     ProfScope ps(KK_CG_INIT, s);
-    hipLaunchKernelGGL(k_cg_init, igrid, block, vlds, s, b, (const uint32_t*)L->perm.ptr, x32, r, p, n, C,
-                       L->solve_rows, rr_parts);
+    const dim3 grid((unsigned)std::min<int64_t>(cs.iparts, 65536));
+    hipLaunchKernelGGL(k_cg_init, grid, dim3(kBlock), cg_vec_lds(C), s, cs.cl.rhs, (const uint32_t*)L->perm.ptr,
+                       cs.x32, cs.r, cs.p, L->n, C, L->solve_rows, cs.rr_parts);
     SGP_LAUNCH_CHECK("k_cg_init");
   }
-  if (!lat && (rc = launch_cg_scalar(h_start, C, s))) return rc;
-  // One iteration: one MVM of p that also yields alpha, r -= alpha A p,
-  // convergence and beta (CgMvm); x and p move in the next iteration's
-  // splat. Nothing here talks to the host, so a block of iterations can be
-  // recorded as a graph.
-  // The direction update x += alpha p, p = r + beta p of an iteration runs
-  // in the next iteration's splat (CgDirUpdate), or as a pass of its own
-  // when that fusion is switched off; both give the same values bit for bit.
+  return launch_cg_scalar(cs.start, C, s);
+}
+
+// One iteration: one MVM of p that also yields alpha, r -= alpha A p,
+// convergence and beta (CgMvm); x and p move in the next iteration's
+// splat. Nothing here talks to the host, so a block of iterations can be
+// recorded as a graph.
+// The direction update x += alpha p, p = r + beta p of an iteration runs
+// in the next iteration's splat (CgDirUpdate) if fused, or as a pass of its
+// own; both give the same values bit for bit.
+int cg_iterate(const sgp_lattice* L, const CgSetup& cs, int C, bool fused, bool first, hipStream_t s) {
+  if (cs.lat) return cg_lat_iter(L, C, cs.cl, first, s);
+  const CgDirUpdate up{cs.p, cs.r, cs.x32, cs.st};
+  const int rc = mvm_cg(L, cs.p, C, s, cs.cl.noise, cs.mvm, (fused && !first) ? &up : nullptr);
+  if (rc || fused) return rc;
+  return launch_cg_dir(up, L->n * C, C, s);
+}
+
+int cg_run(const sgp_lattice* L, const float* b, int C, float noise, float tol, int max_iter,
+           float* x, int32_t* iters, float* rel, hipStream_t s) {
+  const int64_t n = L->n;
+  int rc;
+  CgSetup cs;
+  if ((rc = cg_setup(L, b, C, noise, tol, x, s, &cs))) return rc;
+  CgState* st = cs.st;
+  int32_t* host = (int32_t*)pinned_scratch(sizeof(int32_t) * 3 * kMaxCgCols);
+  if (!host) {
+    set_error("cg_solve: pinned host scratch unavailable");
+    return SGP_ENOMEM;
+  }
+  if ((rc = cg_begin(L, cs, C, s))) return rc;
   const bool fused = cg_fuse_enabled();
-  const CgDirUpdate dirup{p, r, x32, st};
-  auto iterate = [&](hipStream_t st_, bool first) -> int {
-    if (lat) return cg_lat_iter(L, C, cl, first, st_);
-    int rc_ = mvm_cg(L, p, C, st_, (double)noise, cgm, (fused && !first) ? &dirup : nullptr);
-    if (rc_) return rc_;
-    if (!fused) {
-      const int rc2 = launch_cg_dir(dirup, nC, C, st_);
-      if (rc2) return rc2;
-    }
-    return SGP_OK;
-  };
+  auto iterate = [&](hipStream_t st_, bool first) { return cg_iterate(L, cs, C, fused, first, st_); };
   // Polls read the per-column active flags; each one drains the queue, so
   // none are made when the caller asked for a fixed iteration count.
   auto all_done = [&](bool* done) -> int {
@@ -441,15 +468,15 @@ int cg_run(const sgp_lattice* L, const float* b, int C, float noise, float tol, 
     }
   } guard{&graph, &exec, s};
   if (!done && max_iter - it >= 2 * blk && cg_graphs_enabled() && !profiling()) {
-    hipStream_t cs = capture_stream();
-    if (!cs) {
+    hipStream_t cap = capture_stream();
+    if (!cap) {
       set_error("cg_solve: could not create a capture stream");
       return SGP_EHIP;
     }
-    SGP_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
+    SGP_HIP(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
     int crc = SGP_OK;
-    for (int b = 0; b < blk && !crc; ++b) crc = iterate(cs, false);
-    hipError_t ce = hipStreamEndCapture(cs, &graph);
+    for (int b = 0; b < blk && !crc; ++b) crc = iterate(cap, false);
+    hipError_t ce = hipStreamEndCapture(cap, &graph);
     if (crc) return crc;
     SGP_HIP(ce);
     SGP_HIP(hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
@@ -465,15 +492,15 @@ int cg_run(const sgp_lattice* L, const float* b, int C, float noise, float tol, 
     if (polling && (it + 1) % blk == 0 && it + 1 < max_iter)
       if ((rc = all_done(&done))) return rc;
   }
-  if (lat) {
-    if ((rc = cg_lat_out(L, C, cl, s))) return rc;
+  if (cs.lat) {
+    if ((rc = cg_lat_out(L, C, cs.cl, s))) return rc;
   } else {
     ProfScope ps(KK_CG_OUT, s);
     const int vec = (C % 4 == 0 && ((uintptr_t)x & 15u) == 0) ? 1 : 0;
     const int64_t work = n * ((C + 3) / 4);
-    hipLaunchKernelGGL(k_cg_out, dim3((unsigned)std::min<int64_t>((work + kBlock - 1) / kBlock, 65536)), block, 0, s,
-                       (const float*)x32, (const uint32_t*)L->perm.ptr, x, n, C, vec,
-                       fused ? (const double*)p : (const double*)nullptr, (const CgState*)st);
+    hipLaunchKernelGGL(k_cg_out, dim3((unsigned)std::min<int64_t>((work + kBlock - 1) / kBlock, 65536)), dim3(kBlock), 0, s,
+                       (const float*)cs.x32, (const uint32_t*)L->perm.ptr, x, n, C, vec,
+                       fused ? (const double*)cs.p : (const double*)nullptr, (const CgState*)st);
     SGP_LAUNCH_CHECK("k_cg_out");
   }
   SGP_HIP(hipMemcpyAsync(host, st->iters, sizeof(int32_t) * C, hipMemcpyDeviceToHost, s));
@@ -493,6 +520,25 @@ int cg_run(const sgp_lattice* L, const float* b, int C, float noise, float tol, 
 }
 
 }  // namespace
+
+int cg_time(const sgp_lattice* L, const float* b, float* x, int C, int reps, hipEvent_t e0, hipEvent_t e1, float* ms,
+            hipStream_t s) {
+  int rc;
+  CgSetup cs;
+  if ((rc = cg_setup(L, b, C, 1.f, 0.f, x, s, &cs))) return rc;
+  if ((rc = cg_begin(L, cs, C, s))) return rc;
+  const bool fused = cg_fuse_enabled();
+  for (int i = 0; i < reps + 2; ++i) {
+    if (i == 2) SGP_HIP(hipEventRecord(e0, s));
+    if ((rc = cg_iterate(L, cs, C, fused, i == 0, s))) return rc;
+  }
+  SGP_HIP(hipEventRecord(e1, s));
+  SGP_HIP(hipEventSynchronize(e1));
+  SGP_HIP(hipEventElapsedTime(ms, e0, e1));
+  *ms /= (float)reps;
+  return SGP_OK;
+}
+
 }  // namespace sgp
 
 using namespace sgp;

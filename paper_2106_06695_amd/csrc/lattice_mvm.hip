@@ -1157,14 +1157,17 @@ int cu_count() {
 // allowed to.
 // Launch choices an autotuning run can set: the channel chunk width and the
 // resident blocks per CU of the persistent splat and slice (0: as many as
-// the occupancy allows). None of them changes a result: every sum is formed
-// in an order that depends on neither the chunk width nor the grid.
+// the occupancy allows; splat_bpc is k_cg_tile's in CG on the lattice). None of
+// them changes a result: every sum is formed in an order that depends on
+// neither the chunk width nor the grid.
 struct LaunchChoice {
   int g;
   int splat_bpc;
   int slice_bpc;
 };
+enum TuneForm { TF_MVM = 0, TF_LAT = 1 };  // MVMs, also inside CG; CG on the lattice
 struct TuneEntry {
+  TuneForm form;
   int d, elem, g0, mlog;
   LaunchChoice c;
   float ms;
@@ -1179,10 +1182,10 @@ int mlog_of(int64_t m) {
   return b;
 }
 
-bool tune_find(const sgp_lattice* L, int C, int elem, LaunchChoice* out) {
+bool tune_find(const sgp_lattice* L, int C, int elem, TuneForm form, LaunchChoice* out) {
   std::lock_guard<std::mutex> lk(g_tune_mu);
   for (const TuneEntry& e : g_tune)
-    if (e.d == L->d && e.elem == elem && e.g0 == lanes_for(C) && e.mlog == mlog_of(L->m)) {
+    if (e.form == form && e.d == L->d && e.elem == elem && e.g0 == lanes_for(C) && e.mlog == mlog_of(L->m)) {
       *out = e.c;
       return true;
     }
@@ -1663,7 +1666,7 @@ int mvm_dispatch(const sgp_lattice* L, const TU* V, const uint32_t* perm, int C,
   if (g_force)
     lc = *g_force;
   else
-    (void)tune_find(L, C, (int)sizeof(TU), &lc);
+    (void)tune_find(L, C, (int)sizeof(TU), TF_MVM, &lc);
   if (lc.g < 1 || lc.g > gmax || (lc.g & (lc.g - 1))) lc.g = gmax;  // never wider than the LDS allows
   switch (lc.g) {
     case 1: return mvm_g<TU, 1>(L, V, perm, C, out, s, noise, cgm, lc, work, up);
@@ -1783,12 +1786,21 @@ size_t cg_tile_lds_g(const sgp_lattice* L, int C, int g) {
   }
 }
 
-int lat_cg(const sgp_lattice* L, int C, const CgLat& cl, LatStep step, hipStream_t s) {
+// The widest channel chunk of k_cg_tile.
+int lat_lanes(const sgp_lattice* L, int C) {
   int g = lanes_for(C);
   if (g > kMaxChunk) g = kMaxChunk;
   while (g > 1 && cg_tile_lds_g(L, C, g) > kCgTileLds) g >>= 1;
+  return g;
+}
+
+int lat_cg(const sgp_lattice* L, int C, const CgLat& cl, LatStep step, hipStream_t s) {
+  const int g = lat_lanes(L, C);
   LaunchChoice lc{g, 0, 0};
-  (void)tune_find(L, C, (int)sizeof(double), &lc);
+  if (g_force)
+    lc = *g_force;
+  else
+    (void)tune_find(L, C, (int)sizeof(double), TF_LAT, &lc);
   if (lc.g < 1 || lc.g > g || (lc.g & (lc.g - 1))) lc.g = g;
   switch (lc.g) {
     case 1: return lat_cg_g<1>(L, C, cl, step, lc, s);
@@ -1841,10 +1853,6 @@ int mvm_cg(const sgp_lattice* L, double* p, int C, hipStream_t s, double noise, 
   return mvm_dispatch<double>(L, p, nullptr, C, cg.r, s, noise, &cg, nullptr, up);
 }
 
-int mvm_f64(const sgp_lattice* L, const double* V, int C, double* out, hipStream_t s) {
-  return mvm_dispatch<double>(L, V, nullptr, C, out, s, 0.0, nullptr);
-}
-
 size_t mvm_f32_work_bytes(const sgp_lattice* L, int C) { return sizeof(float) * mvm_work_elems(L, C, false); }
 
 int mvm_f32(const sgp_lattice* L, const float* V, int C, float* out, hipStream_t s) {
@@ -1852,13 +1860,17 @@ int mvm_f32(const sgp_lattice* L, const float* V, int C, float* out, hipStream_t
 }
 
 // Times every candidate launch choice on this lattice and keeps the fastest
-// for lattices of the same shape.
+// for lattices of the same shape. What is timed is what runs: an fp32 MVM, or
+// an iteration of a solve in the form that this lattice's take (whose MVM
+// carries the direction update where the chunk covers all columns, or which
+// has one tile kernel and no slice to choose for).
 int autotune(const sgp_lattice* L, int C, bool fp64, int reps, hipStream_t s, int32_t* choice,
              float* best_ms) {
   const int elem = fp64 ? 8 : 4;
-  const int gmax = chunk_lanes(L, C, elem);
+  const bool lat = fp64 && cg_on_lattice(L);
+  const int gmax = lat ? lat_lanes(L, C) : chunk_lanes(L, C, elem);
   DevBuf buf;
-  const size_t bytes = (size_t)elem * (size_t)L->n * (size_t)C;
+  const size_t bytes = sizeof(float) * (size_t)L->n * (size_t)C;
   int rc = dev_alloc(buf, 2 * bytes, s);
   if (rc) return rc;
   struct Cleanup {
@@ -1873,46 +1885,47 @@ int autotune(const sgp_lattice* L, int C, bool fp64, int reps, hipStream_t s, in
       dev_free(*b);
     }
   } cleanup{&buf, s};
-  // values near 1 (every 32-bit word 0x3F800000 for fp32, 0x3FF00000 for fp64)
-  if ((rc = launch_fill_u32((uint32_t*)buf.ptr, bytes / 4, fp64 ? 0x3FF00000u : 0x3F800000u, s))) return rc;
+  if ((rc = launch_fill_u32((uint32_t*)buf.ptr, bytes / 4, 0x3F800000u, s))) return rc;  // ones
   SGP_HIP(hipEventCreate(&cleanup.e0));
   SGP_HIP(hipEventCreate(&cleanup.e1));
-  void* V = buf.ptr;
-  void* out = (char*)buf.ptr + bytes;
-  auto run = [&]() {
-    return fp64 ? mvm_f64(L, (const double*)V, C, (double*)out, s)
-                : mvm_into(L, (const float*)V, C, (float*)out, s);
+  const float* V = (const float*)buf.ptr;
+  float* out = (float*)((char*)buf.ptr + bytes);
+  auto time_mvm = [&](float* ms) -> int {
+    int rc_ = mvm_into(L, V, C, out, s);  // warm-up (sizes buffers, sets LDS limits)
+    if (rc_) return rc_;
+    SGP_HIP(hipEventRecord(cleanup.e0, s));
+    for (int r = 0; r < reps; ++r)
+      if ((rc_ = mvm_into(L, V, C, out, s))) return rc_;
+    SGP_HIP(hipEventRecord(cleanup.e1, s));
+    SGP_HIP(hipEventSynchronize(cleanup.e1));
+    SGP_HIP(hipEventElapsedTime(ms, cleanup.e0, cleanup.e1));
+    *ms /= (float)reps;
+    return SGP_OK;
   };
   LaunchChoice best{gmax, 0, 0};
   float best_t = -1.f;
   for (int g = gmax; g >= 1 && g >= gmax / 4; g >>= 1) {
     for (int sb = 0; sb <= 1; ++sb) {
-      for (int lb = 0; lb <= 1; ++lb) {
+      for (int lb = 0; lb <= (lat ? 0 : 1); ++lb) {
         const LaunchChoice cand{g, sb, lb};
-        g_force = &cand;
-        if ((rc = run())) return rc;  // warm-up (sizes buffers, sets LDS limits)
-        SGP_HIP(hipEventRecord(cleanup.e0, s));
-        for (int r = 0; r < reps; ++r)
-          if ((rc = run())) return rc;
-        SGP_HIP(hipEventRecord(cleanup.e1, s));
-        SGP_HIP(hipEventSynchronize(cleanup.e1));
         float ms = 0.f;
-        SGP_HIP(hipEventElapsedTime(&ms, cleanup.e0, cleanup.e1));
-        ms /= (float)reps;
+        g_force = &cand;
+        rc = fp64 ? cg_time(L, V, out, C, reps, cleanup.e0, cleanup.e1, &ms, s) : time_mvm(&ms);
+        g_force = nullptr;
+        if (rc) return rc;
         if (best_t < 0.f || ms < best_t) {
           best_t = ms;
           best = cand;
         }
-        g_force = nullptr;
       }
     }
   }
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
-    const TuneEntry e{L->d, elem, lanes_for(C), mlog_of(L->m), best, best_t};
+    const TuneEntry e{lat ? TF_LAT : TF_MVM, L->d, elem, lanes_for(C), mlog_of(L->m), best, best_t};
     bool found = false;
     for (TuneEntry& x : g_tune)
-      if (x.d == e.d && x.elem == e.elem && x.g0 == e.g0 && x.mlog == e.mlog) {
+      if (x.form == e.form && x.d == e.d && x.elem == e.elem && x.g0 == e.g0 && x.mlog == e.mlog) {
         x = e;
         found = true;
       }

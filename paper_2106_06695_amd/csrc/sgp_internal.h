@@ -299,8 +299,10 @@ size_t cg_lat_work_elems(const sgp_lattice* L, int C);
 int cg_lat_start(const sgp_lattice* L, int C, const CgLat& cl, hipStream_t s);
 int cg_lat_iter(const sgp_lattice* L, int C, const CgLat& cl, bool first, hipStream_t s);
 int cg_lat_out(const sgp_lattice* L, int C, const CgLat& cl, hipStream_t s);
-// fp64 values and accumulation, internal point order, no epilogue
-int mvm_f64(const sgp_lattice* L, const double* V, int C, double* out, hipStream_t s);
+// Time of one CG iteration in the form that L's solves take (b, x: n x C
+// fp32), from reps of them after two
+int cg_time(const sgp_lattice* L, const float* b, float* x, int C, int reps, hipEvent_t e0, hipEvent_t e1, float* ms,
+            hipStream_t s);
 // fp32 values and accumulation, internal point order, and its work memory
 size_t mvm_f32_work_bytes(const sgp_lattice* L, int C);
 int mvm_f32(const sgp_lattice* L, const float* V, int C, float* out, hipStream_t s);
