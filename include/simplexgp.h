@@ -236,11 +236,15 @@ int sgp_debug_inject_oom(int32_t count);
  * Returns the previous setting. */
 int sgp_cg_graph_enable(int on);
 
-/* Fused blur steps (process-wide switch, default on). With a three-tap
- * stencil (order 1), two consecutive direction steps of the blur (Section
- * 3.2, Blur) run as one launch that forms the first step's values at the
- * three neighbours it needs in the same order as a separate step would, so
- * results are bitwise identical with the switch off. Returns the previous
+/* Fused blur steps (process-wide switch, default on). Several direction steps
+ * of the blur (Section 3.2, Blur) then run as one launch: the whole lattice
+ * part of an MVM, one block per column, on lattices of at most 2,048 points
+ * (order 1); groups of up to four directions, on lattices of d >= 5 and 8,192
+ * points or more whose points connected along such a group fit a tile of 255
+ * (orders 1 and 2); else two consecutive steps (order 1), the first step's
+ * values formed at the three neighbours that the second needs. Every value is
+ * formed in the same order as by separate steps, one launch each, which run
+ * with the switch off, so results are bitwise identical. Returns the previous
  * setting. */
 int sgp_blur_fuse_enable(int on);
 
@@ -251,7 +255,9 @@ int sgp_blur_fuse_enable(int on);
  * chains in one launch, so that a launch's arrays share the Infinity Cache.
  * Every row is computed as before, so results are bitwise identical for any
  * setting. bytes < 0: never. The default is SGP_BLUR_SEQ_MIB MiB from the
- * environment, else 128 MiB. Returns the previous threshold. */
+ * environment, else 128 MiB; at 128 MiB, launches of groups of directions
+ * (sgp_blur_fuse_enable) only do so from 768 MiB. Returns the previous
+ * threshold. */
 int64_t sgp_blur_seq_bytes(int64_t bytes);
 
 /* CG direction update fused into the splat (process-wide switch, default

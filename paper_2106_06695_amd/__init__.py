@@ -300,16 +300,17 @@ def cg_fuse_enable(on: bool) -> bool:
 
 
 def blur_fuse_enable(on: bool) -> bool:
-    """Turn fused two-step blur launches on or off (process-wide); returns
-    the previous setting. Results do not depend on it."""
+    """Turn blur launches of several direction steps on or off (process-wide;
+    sgp_blur_fuse_enable); returns the previous setting. Results do not depend
+    on it."""
     return bool(_lib.load().sgp_blur_fuse_enable(1 if on else 0))
 
 
 def blur_seq_bytes(nbytes: int) -> int:
     """Set the size of the four lattice value arrays above which the
     symmetric blur runs its two chains one after the other (process-wide;
-    negative: never); returns the previous threshold. Results do not depend
-    on it."""
+    negative: never; sgp_blur_seq_bytes); returns the previous threshold.
+    Results do not depend on it."""
     return int(_lib.load().sgp_blur_seq_bytes(int(nbytes)))
 
 

@@ -36,7 +36,7 @@ const Tuning& tuning() {
     if (k.slice_lds_budget > 163840) k.slice_lds_budget = 163840;
     k.blocks_per_cu = env_int("SGP_TILE_BLOCKS_PER_CU", 0);
     if (k.blocks_per_cu < 0) k.blocks_per_cu = 0;
-    k.blur_seq_mib = env_int("SGP_BLUR_SEQ_MIB", 128);
+    k.blur_seq_mib = env_int("SGP_BLUR_SEQ_MIB", kBlurSeqMib);
     if (k.blur_seq_mib < 0) k.blur_seq_mib = 0;
     return k;
   }();
@@ -489,8 +489,9 @@ std::atomic<int64_t>& blur_seq_threshold() {
   static std::atomic<int64_t> t{tuning().blur_seq_mib > 0 ? (int64_t)tuning().blur_seq_mib << 20 : -1};
   return t;
 }
-bool blur_seq_for(double bytes) {
-  const int64_t t = blur_seq_threshold().load();
+bool blur_seq_for(double bytes, bool groups) {
+  int64_t t = blur_seq_threshold().load();
+  if (groups && t == (int64_t)kBlurSeqMib << 20) t = (int64_t)kGroupSeqMib << 20;
   return t >= 0 && bytes > (double)t;
 }
 bool cg_fuse_enabled() { return g_cg_fuse.load() != 0; }

@@ -1360,11 +1360,10 @@ int blur_g(const sgp_lattice* L, TU* U0, TU* B1, TU* B2, TU* B3, TU* B4, int C, 
   };
   const bool fuse = L->order == 1 && blur_fuse_enabled();
   const bool groups = L->ngroups && blur_fuse_enabled();
-  // Large lattices (the four value arrays over 128 MiB by default, half the
-  // Infinity Cache): the chains' split launches run one chain after the
-  // other (all of chain 0's, then chain 1's), so that a launch's input and
-  // output arrays sit in the cache together.
-  bool seq = (fuse || groups) && sym && blur_seq_for(4.0 * (double)mC * sizeof(TU));
+  // Large lattices: the chains' launches run one chain after the other (all of
+  // chain 0's, then chain 1's), so that a launch's arrays sit in the Infinity
+  // Cache together.
+  const bool seq = (fuse || groups) && sym && blur_seq_for(4.0 * (double)mC * sizeof(TU), groups);
   std::vector<Blur2Args<TU>> later;  // chain 1's split launches, in order
   auto launch2 = [&](const Blur2Args<TU>& b, unsigned grid) -> int {
     ProfScope ps(KK_BLUR, s);
@@ -1385,11 +1384,6 @@ int blur_g(const sgp_lattice* L, TU* U0, TU* B1, TU* B2, TU* B3, TU* B4, int C, 
   };
   if (groups) {
     const int ng = L->ngroups;
-    // A launch only touches its chains' own arrays, and one chain after the
-    // other pays late: adjoint of m = 4.2M, d = 16 (254 MiB an array) 54.3
-    // against 57.3 ms for both in one launch; at half that (C = 8) 2.47
-    // against 2.43 ms an MVM, at 44 MB (m = 681,000, fp64) 529 against 492 us.
-    seq = seq && 2.0 * (double)mC * sizeof(TU) > 384.0 * (1 << 20);
     GroupArgs<TU> b;
     b.C = C;
     b.chunks = (C + G - 1) / G;

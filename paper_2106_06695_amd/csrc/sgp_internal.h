@@ -114,8 +114,15 @@ bool profiling();
 bool cg_graphs_enabled();
 bool blur_fuse_enabled();
 // True when the symmetric blur should run its chains one after the other
-// for lattice value arrays of `bytes` in all (four arrays).
-bool blur_seq_for(double bytes);
+// for lattice value arrays of `bytes` in all (four arrays). The defaults: half
+// the Infinity Cache for the fused pairs, so that a launch's input and output
+// arrays sit in it together. A launch of the blur by groups only touches its
+// chains' own arrays, and one chain after the other pays late: adjoint of
+// m = 4.2M, d = 16 (254 MiB an array) 54.3 against 57.3 ms for both in one
+// launch; at half that (C = 8) 2.47 against 2.43 ms an MVM, at 44 MB
+// (m = 681,000, fp64) 529 against 492 us.
+constexpr int kBlurSeqMib = 128, kGroupSeqMib = 768;
+bool blur_seq_for(double bytes, bool groups);
 bool cg_fuse_enabled();
 // A per-thread, per-device stream used only to record graphs.
 hipStream_t capture_stream();
