@@ -19,8 +19,12 @@ enum ColMode {
   CM_CG = 1    // and alpha of the CG iteration (CgMvm)
 };
 
+// Columns of one launch: 2^30 threads (a grid has less than 2^32).
+constexpr int kColGrid = 1 << 20;
+
 struct ColArgs {
   int m, C, D;
+  int c0;          // first column
   int rshift;      // log2 of the rows per gather range
   int first, rev;  // chains to run: directions 0 .. d, and d .. 0
   int lat_parts, ntiles;
@@ -38,7 +42,7 @@ size_t col_lds(const ColArgs& a) {
   return sizeof(double) * (size_t)(2 * (col_at(a.m) + 1) + a.m / 8 + 1 + a.lat_parts + (a.ntiles + 15) / 16 + kFold);
 }
 
-// Block c filters column c. Thread t holds rows t + i * 1024 in registers; a
+// A block filters a column. Thread t holds rows t + i * 1024 in registers; a
 // blur step reads the neighbours' rows from LDS, and the next step's neighbour
 // indices are in flight meanwhile. Every sum is formed as by the kernels that
 // larger lattices use (k_gather_fix, the blur, k_cg_alpha, the fold), in the
@@ -58,7 +62,7 @@ __global__ __launch_bounds__(kColThreads) void k_lattice_col(TU* __restrict__ U,
   double* gs = (double*)(us + rows);       // CG: sums of 8 rows, then partial sums and their fold
   double* parts = gs + a.m / 8 + 1;
   double* fold = parts + (a.lat_parts + (a.ntiles + 15) / 16);
-  const int tid = threadIdx.x, c = blockIdx.x;
+  const int tid = threadIdx.x, c = a.c0 + (int)blockIdx.x;
   const int m = a.m;
   TU st[3];
 #pragma unroll

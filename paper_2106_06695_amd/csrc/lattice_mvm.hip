@@ -682,7 +682,7 @@ struct GroupArgs {
   int64_t tile0[2];         // the group's first tile and tiles
   int32_t tiles[2];
   int dirs[2], rev[2];      // directions, from the last one down if rev
-  int C, chunks;
+  int C, chunk0, chunks;    // channel chunks of this launch
   unsigned blocks;          // of one chain
   int vec;
   TU st[5];
@@ -728,7 +728,7 @@ __global__ __launch_bounds__((group_threads<G, TU>())) void k_blur_group(
   const int tile = b / a.chunks;
   if (tile >= a.tiles[ch]) return;  // the other chain's group has more
   const int r0 = (int)threadIdx.x / LPR, cl = (int)(threadIdx.x % LPR) * VW;
-  const int c = (b - tile * a.chunks) * G + cl;
+  const int c = (a.chunk0 + b - tile * a.chunks) * G + cl;
   const bool vec = a.vec && c + VW <= a.C;
   const int64_t p0 = (a.tile0[ch] + tile) * kGroupRows + r0;
   const int nd = a.dirs[ch];
@@ -1318,11 +1318,13 @@ int col_launch(const sgp_lattice* L, TU* U, const TU* frag, TU* Bu, int C, doubl
   for (int t = 0; t < 3; ++t) a.st[t] = L->stencil64[t];
   const size_t lds = col_lds<TU, MODE>(a);
   auto launch = [&](auto nr_tag) -> int {
-    ProfScope ps(KK_BLUR, s);
-    hipLaunchKernelGGL((k_lattice_col<TU, decltype(nr_tag)::value, MODE>), dim3((unsigned)C), dim3(kColThreads), lds,
-                       s, U, frag, (const int32_t*)L->occ_ptr.ptr, (const int32_t*)L->nbr.ptr, Bu, cgm.pp, cgm.alpha,
-                       a);
-    SGP_LAUNCH_CHECK("k_lattice_col");
+    for (a.c0 = 0; a.c0 < C; a.c0 += kColGrid) {
+      ProfScope ps(KK_BLUR, s);
+      hipLaunchKernelGGL((k_lattice_col<TU, decltype(nr_tag)::value, MODE>),
+                         dim3((unsigned)std::min(C - a.c0, kColGrid)), dim3(kColThreads), lds, s, U, frag,
+                         (const int32_t*)L->occ_ptr.ptr, (const int32_t*)L->nbr.ptr, Bu, cgm.pp, cgm.alpha, a);
+      SGP_LAUNCH_CHECK("k_lattice_col");
+    }
     return SGP_OK;
   };
   return a.m <= kColThreads ? launch(std::integral_constant<int, 1>{}) : launch(std::integral_constant<int, 2>{});
@@ -1386,7 +1388,6 @@ int blur_g(const sgp_lattice* L, TU* U0, TU* B1, TU* B2, TU* B3, TU* B4, int C, 
     const int ng = L->ngroups;
     GroupArgs<TU> b;
     b.C = C;
-    b.chunks = (C + G - 1) / G;
     b.vec = (C % group_vw<G, TU>() == 0 && aligned16(U0) && aligned16(B1) && aligned16(B2)) ? 1 : 0;
     for (int t = 0; t < 2 * L->order + 1; ++t) b.st[t] = a.st[t];
     // one group of chain 0 (i0 >= 0) and one of chain 1 (i1 >= 0)
@@ -1408,14 +1409,21 @@ int blur_g(const sgp_lattice* L, TU* U0, TU* B1, TU* B2, TU* B3, TU* B4, int C, 
         ++n;
       }
       b.add = sum ? B1 : nullptr;
-      b.blocks = (unsigned)(most * b.chunks);
-      ProfScope ps(KK_BLUR, s);
-      const dim3 grid(b.blocks * n), block(group_threads<G, TU>());
-      if (L->order == 1)
-        hipLaunchKernelGGL((k_blur_group<TU, G, 1>), grid, block, 0, s, (const GroupRow<1>*)L->group_rows.ptr, b);
-      else
-        hipLaunchKernelGGL((k_blur_group<TU, G, 2>), grid, block, 0, s, (const GroupRow<2>*)L->group_rows.ptr, b);
-      SGP_LAUNCH_CHECK("k_blur_group");
+      // a launch takes all channel chunks, unless they are so many that its
+      // grid would come near 2^32 threads
+      const int chunks = (C + G - 1) / G;
+      const int most_chunks = (int)std::max<int64_t>(1, ((int64_t)1 << 31) / (most * n * group_threads<G, TU>()));
+      for (b.chunk0 = 0; b.chunk0 < chunks; b.chunk0 += b.chunks) {
+        b.chunks = std::min(chunks - b.chunk0, most_chunks);
+        b.blocks = (unsigned)(most * b.chunks);
+        ProfScope ps(KK_BLUR, s);
+        const dim3 grid(b.blocks * n), block(group_threads<G, TU>());
+        if (L->order == 1)
+          hipLaunchKernelGGL((k_blur_group<TU, G, 1>), grid, block, 0, s, (const GroupRow<1>*)L->group_rows.ptr, b);
+        else
+          hipLaunchKernelGGL((k_blur_group<TU, G, 2>), grid, block, 0, s, (const GroupRow<2>*)L->group_rows.ptr, b);
+        SGP_LAUNCH_CHECK("k_blur_group");
+      }
       return SGP_OK;
     };
     int rc = SGP_OK;
