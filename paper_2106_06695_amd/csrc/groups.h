@@ -7,7 +7,15 @@
 // m = 874,000 (d = 11), 166 at m = 4.2M (d = 16). To find and place them takes
 // 0.1 ms of a build at m = 141,000 (d = 11), 0.4 ms at 681,000 (d = 20), 3.0 ms
 // at 4.2M (d = 16), random accesses to the roots; a blur there gains 0.1, 0.3
-// and 2 ms.
+// and 2 ms. On dense lattices of few dimensions the first cut does not fit and is
+// divided. Builds without any search, with every cut joined and counted, and
+// with those left out that a sampled part tells not to fit (k_group_init), which
+// adds some 8 us where the first cut fits: m = 62,000 (d = 6) 0.56, 0.94, 0.73 ms;
+// 245,000 (d = 6) 1.06, 1.98, 1.32; 673,000 (d = 8) 2.25, 3.12, 2.55; 1.13M
+// (d = 5, no groups in the end) 3.05, 4.70, 2.95 (its neighbour look-ups are
+// faster now, too). Groups of at most two directions do not pay there: an MVM of
+// 8 columns without and with them 64 and 73 us (m = 62,000), 157 and 171
+// (245,000), 405 and 387 (673,000).
 #ifndef SGP_GROUPS_H
 #define SGP_GROUPS_H
 #include <hip/hip_runtime.h>
@@ -61,17 +69,79 @@ __device__ __forceinline__ void group_nbrs(const int32_t* nbr, int64_t k, int64_
   }
 }
 
-// parent = the smallest of a point and its neighbours along the group;
-// also clears the sizes and the class counts.
+// Whether the part of `start` has more than kGroupPart points: its points are
+// visited breadth first by one block, a thread per neighbour, for at most
+// kGroupSteps steps. False may also mean that they did not suffice. A step adds
+// at most a point a thread to the 255 there are, so the table is never full.
+constexpr int kGroupSteps = 16;
+template <int R>
+__device__ inline bool group_outgrows(const int32_t* __restrict__ nbr, int64_t m, int first, int dirs,
+                                      int32_t start) {
+  constexpr int E = 2 * R * kGroupDirs, T = 1024;
+  __shared__ int32_t list[kGroupRows], table[T];
+  __shared__ int count;
+  const int tid = threadIdx.x;
+  auto slot_of = [](int32_t x) { return (int)((uint32_t)x * 0x9E3779B1u >> 22); };
+  for (int i = tid; i < T; i += 256) table[i] = -1;
+  __syncthreads();
+  if (tid == 0) {
+    list[0] = start;
+    table[slot_of(start)] = start;
+    count = 1;
+  }
+  __syncthreads();
+  int done = 0, known = 1;  // points visited, and found
+  for (int step = 0; step < kGroupSteps && done < known && known <= kGroupPart; ++step) {
+    const int i = done + tid / E, e = tid % E;
+    if (i < known && e / (2 * R) < dirs) {
+      const int32_t x = nbr[((first + e / (2 * R)) * m + list[i]) * (2 * R) + e % (2 * R)];
+      for (int s = x >= 0 ? slot_of(x) : -1; s >= 0; s = (s + 1) % T) {
+        const int32_t old = (int32_t)atomicCAS((uint32_t*)table + s, ~0u, (uint32_t)x);
+        if (old == x) break;
+        if (old < 0) {
+          const int at = atomicAdd(&count, 1);
+          if (at < kGroupRows) list[at] = x;
+          break;
+        }
+      }
+    }
+    __syncthreads();
+    done = done + 256 / E < known ? done + 256 / E : known;
+    known = count;
+    __syncthreads();
+  }
+  return known > kGroupPart;
+}
+
+// Whether a group's parts are known already, or one of its samples outgrows a
+// tile (k_group_init): every thread of a block gets the same answer.
+__device__ __forceinline__ bool group_over(const uint8_t* __restrict__ over, int g) {
+  static_assert(kGroupSamples == 4 * 64, "four answers a lane");
+  return __ballot(((const uint32_t*)(over + g * kGroupSamples))[threadIdx.x & 63] != 0) != 0;
+}
+
+// parent = the smallest of a point and its neighbours along the group; also
+// clears the sizes and the class counts. The first kGroupSamples blocks look at
+// the part of a point each: a group whose parts outgrow a tile mostly has many
+// points in such parts (17 to 95% on dense lattices of d = 5 to 7, 1% at d = 8),
+// and to join and count them takes many steps to few roots (m = 245,000, d = 6,
+// groups of four and three directions: 530 us), so it is then left out.
 template <int R>
 __global__ __launch_bounds__(256) void k_group_init(const int32_t* __restrict__ nbr, int64_t m, GroupSpec sp,
                                                     int32_t* __restrict__ parent, int32_t* __restrict__ info,
-                                                    uint32_t* __restrict__ cnt) {
+                                                    uint32_t* __restrict__ cnt, uint8_t* __restrict__ over) {
   const int g = (int)blockIdx.y;
   if (sp.skip[g]) return;
-  if (blockIdx.x == 0 && threadIdx.x < kGroupWords) cnt[g * kGroupWords + threadIdx.x] = 0;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < m; j += stride) {
+  if (blockIdx.x < kGroupSamples) {
+    const int64_t at = (2 * (int64_t)blockIdx.x + 1) * m / (2 * kGroupSamples);
+    const bool big = group_outgrows<R>(nbr, m, sp.first[g], sp.dirs[g], (int32_t)at);
+    if (threadIdx.x == 0) over[g * kGroupSamples + blockIdx.x] = big ? 1 : 0;
+    return;
+  }
+  const int64_t block = (int64_t)blockIdx.x - kGroupSamples;
+  if (block == 0 && threadIdx.x < kGroupWords) cnt[g * kGroupWords + threadIdx.x] = 0;
+  const int64_t stride = (int64_t)(gridDim.x - kGroupSamples) * blockDim.x;
+  for (int64_t j = block * blockDim.x + threadIdx.x; j < m; j += stride) {
     int32_t p = (int32_t)j;
 #pragma unroll
     for (int t = 0; t < kGroupDirs; ++t)
@@ -92,9 +162,10 @@ __global__ __launch_bounds__(256) void k_group_init(const int32_t* __restrict__ 
 // and ends.
 template <int R>
 __global__ __launch_bounds__(256) void k_group_join(const int32_t* __restrict__ nbr, int64_t m, GroupSpec sp,
-                                                    int32_t* __restrict__ parents) {
+                                                    int32_t* __restrict__ parents,
+                                                    const uint8_t* __restrict__ over) {
   const int g = (int)blockIdx.y;
-  if (sp.skip[g]) return;
+  if (sp.skip[g] || group_over(over, g)) return;
   int32_t* parent = parents + g * m;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < m; j += stride) {
@@ -127,8 +198,9 @@ __global__ __launch_bounds__(256) void k_group_join(const int32_t* __restrict__ 
 // (in info, at the root). Points of a wave with its first lane's root are
 // counted together: a part of a lattice without gaps may hold every point.
 __global__ __launch_bounds__(256) void k_group_count(int64_t m, GroupSpec sp, int32_t* __restrict__ parents,
-                                                     int32_t* __restrict__ infos, int32_t* __restrict__ place) {
-  if (sp.skip[blockIdx.y]) return;
+                                                     int32_t* __restrict__ infos, int32_t* __restrict__ place,
+                                                     const uint8_t* __restrict__ over) {
+  if (sp.skip[blockIdx.y] || group_over(over, (int)blockIdx.y)) return;
   const int64_t at = blockIdx.y * m;
   int32_t* parent = parents + at;
   int32_t* info = infos + at;
@@ -151,16 +223,22 @@ __global__ __launch_bounds__(256) void k_group_count(int64_t m, GroupSpec sp, in
 }
 
 // Number the parts within their size classes: at a root, info becomes
-// (number << 5) | class. cnt: a group's parts by class, then the largest.
+// (number << 5) | class. cnt: a group's parts by class, then the largest (of a
+// group that was left out, a size past a tile's).
 constexpr int kGroupSpan = 8;
 __global__ __launch_bounds__(256) void k_group_class(int64_t m, GroupSpec sp, const int32_t* __restrict__ parents,
-                                                     int32_t* __restrict__ infos, uint32_t* __restrict__ cnts) {
+                                                     int32_t* __restrict__ infos, uint32_t* __restrict__ cnts,
+                                                     const uint8_t* __restrict__ over) {
   __shared__ uint32_t hist[kGroupClasses], first[kGroupClasses];
   __shared__ int largest;
   if (sp.skip[blockIdx.y]) return;
   const int64_t at = blockIdx.y * m;
   uint32_t* cnt = cnts + blockIdx.y * kGroupWords;
   const int tid = threadIdx.x;
+  if (group_over(over, (int)blockIdx.y)) {
+    if (blockIdx.x == 0 && tid == 0) cnt[kGroupClasses] = kGroupRows;
+    return;
+  }
   if (tid < kGroupClasses) hist[tid] = 0;
   if (tid == 0) largest = 0;
   __syncthreads();

@@ -30,6 +30,7 @@
 #include <cmath>
 #include <cstring>
 #include <mutex>
+#include <utility>
 #include <vector>
 
 #include "groups.h"
@@ -1150,11 +1151,13 @@ int bits_for(uint64_t range) {  // bits to hold values 0..range
 }
 
 // Groups of blur directions in the making: device arrays of `room` x m words
-// (the points' roots, then info and place behind them), the class counts and
-// their copy on the host.
+// (the points' roots, then info and place behind them), the class counts,
+// the samples behind them, and the counts' copy on the host.
 struct GroupBuild {
   int n = 0, room = 0;
-  GroupSpec sp = {}, div = {};  // and a division in the making
+  GroupSpec sp = {};
+  bool large[kMaxGroups] = {};  // known to have a part that outgrows a tile
+  std::vector<std::pair<int, int>> bad;  // ranges of directions that have one: first, one past the last
   int32_t* parent = nullptr;
   uint32_t* cnt = nullptr;
   uint32_t* host = nullptr;
@@ -1168,17 +1171,20 @@ int group_parts(sgp_lattice* L, const GroupBuild& gb, hipStream_t st) {
   int32_t* info = gb.parent + gb.room * m;
   int32_t* place = info + gb.room * m;
   const int32_t* nbr = (const int32_t*)L->nbr.ptr;
+  uint8_t* over = (uint8_t*)(gb.cnt + kMaxGroups * kGroupWords);
   const dim3 grid((unsigned)grid_for(m, kBlock, 4096), (unsigned)gb.n);
   ProfScope ps(KK_NEIGHBORS, st);
-  hipLaunchKernelGGL(k_group_init<R>, grid, dim3(kBlock), 0, st, nbr, m, gb.sp, gb.parent, info, gb.cnt);
+  hipLaunchKernelGGL(k_group_init<R>, dim3(grid.x + kGroupSamples, grid.y), dim3(kBlock), 0, st, nbr, m, gb.sp,
+                     gb.parent, info, gb.cnt, over);
   SGP_LAUNCH_CHECK("k_group_init");
-  hipLaunchKernelGGL(k_group_join<R>, grid, dim3(kBlock), 0, st, nbr, m, gb.sp, gb.parent);
+  hipLaunchKernelGGL(k_group_join<R>, grid, dim3(kBlock), 0, st, nbr, m, gb.sp, gb.parent, (const uint8_t*)over);
   SGP_LAUNCH_CHECK("k_group_join");
-  hipLaunchKernelGGL(k_group_count, grid, dim3(kBlock), 0, st, m, gb.sp, gb.parent, info, place);
+  hipLaunchKernelGGL(k_group_count, grid, dim3(kBlock), 0, st, m, gb.sp, gb.parent, info, place,
+                     (const uint8_t*)over);
   SGP_LAUNCH_CHECK("k_group_count");
   const int64_t span = (int64_t)kGroupSpan * kBlock;
   hipLaunchKernelGGL(k_group_class, dim3((unsigned)((m + span - 1) / span), (unsigned)gb.n), dim3(kBlock), 0, st, m,
-                     gb.sp, (const int32_t*)gb.parent, info, gb.cnt);
+                     gb.sp, (const int32_t*)gb.parent, info, gb.cnt, (const uint8_t*)over);
   SGP_LAUNCH_CHECK("k_group_class");
   SGP_HIP(hipMemcpyAsync(gb.host, gb.cnt, sizeof(uint32_t) * gb.n * kGroupWords, hipMemcpyDeviceToHost, st));
   return SGP_OK;
@@ -1201,58 +1207,88 @@ int group_start(sgp_lattice* L, GroupBuild& gb, int32_t* words, uint32_t* cnt, u
   return group_parts<R>(L, gb, st);
 }
 
+// The verdict on the groups whose parts were counted.
+void group_judge(GroupBuild& gb) {
+  for (int g = 0; g < gb.n; ++g) {
+    if (gb.sp.skip[g]) continue;
+    gb.sp.skip[g] = 1;
+    gb.large[g] = gb.host[g * kGroupWords + kGroupClasses] > (uint32_t)kGroupPart;
+    if (gb.large[g]) gb.bad.emplace_back(gb.sp.first[g], gb.sp.first[g] + gb.sp.dirs[g]);
+  }
+}
+
 // Divide each run of neighbouring groups that have a part too large for a tile
-// into more groups, of at most `most` directions. True if there were any.
+// into more groups, of at most `most` directions. The new ones are to be
+// counted, unless one holds a range that was too large before. False if there
+// is no room for so many.
 bool group_divide(GroupBuild& gb, int D, int most) {
   std::vector<int> at(D, -1), bad;  // group by first direction; groups to do again
   for (int g = 0; g < gb.n; ++g) {
-    gb.sp.skip[g] = gb.host[g * kGroupWords + kGroupClasses] <= (uint32_t)kGroupPart;
     at[gb.sp.first[g]] = g;
-    if (!gb.sp.skip[g]) bad.push_back(g);
+    if (gb.large[g]) bad.push_back(g);
   }
-  if (bad.empty()) return false;
+  const GroupSpec old = gb.sp;
   size_t used = 0;
   for (int k = 0; k < D;) {
-    if (gb.sp.skip[at[k]]) {
-      k += gb.sp.dirs[at[k]];
+    const int g0 = at[k];
+    if (g0 < 0) return false;  // (not reached: groups cover every direction)
+    if (std::find(bad.begin(), bad.end(), g0) == bad.end()) {
+      k += old.dirs[g0];
       continue;
     }
     const int k0 = k;
     int had = 0;
-    for (; k < D && !gb.sp.skip[at[k]]; k += gb.sp.dirs[at[k]]) ++had;
+    for (; k < D && std::find(bad.begin(), bad.end(), at[k]) != bad.end(); k += old.dirs[at[k]]) ++had;
     const int nd = k - k0, want = std::min(nd, std::max((nd + most - 1) / most, had + 1));
     int first = k0;
     for (int i = 0; i < want; ++i) {
       const int g = used < bad.size() ? bad[used++] : gb.n++;
-      if (g >= gb.room) return true;
-      gb.div.first[g] = first;
-      gb.div.dirs[g] = nd / want + (i < nd % want ? 1 : 0);
-      first += gb.div.dirs[g];
+      if (g >= gb.room) return false;
+      const int end = first + nd / want + (i < nd % want ? 1 : 0);
+      gb.large[g] = false;
+      for (const auto& b : gb.bad) gb.large[g] |= first <= b.first && b.second <= end;
+      gb.sp.skip[g] = gb.large[g] ? 1 : 0;
+      gb.sp.first[g] = first;
+      gb.sp.dirs[g] = end - first;
+      first = end;
     }
   }
-  for (int g = 0; g < gb.n; ++g)
-    if (!gb.sp.skip[g]) {
-      gb.sp.first[g] = gb.div.first[g];
-      gb.sp.dirs[g] = gb.div.dirs[g];
-    }
   return true;
 }
 
+// Whether the groups are more passes over the lattice than the fused pairs of
+// order 1 and none of them is a longer one: m = 607,000, d = 5, groups of 2, 2, 1
+// and 1 directions 146 us a blur of 8 fp32 columns, three pairs 115 us.
+bool group_passes_lose(const GroupBuild& gb, int D) {
+  for (int g = 0; g < gb.n; ++g)
+    if (gb.sp.dirs[g] > 2) return false;
+  return gb.n > (D + 1) / 2;
+}
+
 // Place the parts in tiles. Groups whose parts outgrow a tile are divided, to
-// three and then to two directions; a lattice on which that does not help, or
-// whose tiles would be more than a fifth empty, keeps no groups.
+// three and then to two directions; a lattice on which that does not help, whose
+// tiles would be more than a fifth empty, or whose pairs are fewer keeps no
+// groups.
 template <int R>
 int group_place(sgp_lattice* L, GroupBuild& gb, hipStream_t st) {
   const int64_t m = L->m;
-  for (int most = kGroupDirs - 1; most >= 2 && group_divide(gb, L->d + 1, most); --most) {
-    if (gb.n > gb.room) return SGP_OK;
+  group_judge(gb);
+  auto large = [&]() {
+    for (int g = 0; g < gb.n; ++g)
+      if (gb.large[g]) return true;
+    return false;
+  };
+  for (int most = kGroupDirs - 1; most >= 2 && large(); --most) {
+    if (!group_divide(gb, L->d + 1, most) || (R == 1 && group_passes_lose(gb, L->d + 1))) return SGP_OK;
+    if (large()) continue;
     if (const int rc = group_parts<R>(L, gb, st)) return rc;
     SGP_HIP(hipStreamSynchronize(st));
+    group_judge(gb);
   }
+  if (large()) return SGP_OK;
   int64_t tiles = 0;
   for (int g = 0; g < gb.n; ++g) {
     const uint32_t* cnt = gb.host + g * kGroupWords;
-    if (cnt[kGroupClasses] > (uint32_t)kGroupPart) return SGP_OK;
     gb.sp.tile0[g] = tiles;
     tiles += group_tiles(cnt, kGroupClasses);
   }
@@ -1569,7 +1605,7 @@ int build_attempt(sgp_lattice* L, const float* X, const double* f, double load_f
   GroupBuild gb;
   L->ngroups = 0;
   if (L->order <= 2 && d >= 5 && m >= kGroupMin && m <= kGroupMax &&
-      tr.try_alloc(T_GROUP, sizeof(uint32_t) * kMaxGroups * kGroupWords) == hipSuccess) {
+      tr.try_alloc(T_GROUP, kMaxGroups * (sizeof(uint32_t) * kGroupWords + kGroupSamples)) == hipSuccess) {
     // T_NBRC has been read: at least 2 (d + 1) words a point, three a group
     const auto start = L->order == 1 ? group_start<1> : group_start<2>;
     if ((rc = start(L, gb, nbr_can, (uint32_t*)tr.ptr[T_GROUP], host_word + 4 + 2 * kMaxD, st))) return rc;

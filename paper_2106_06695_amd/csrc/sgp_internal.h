@@ -52,6 +52,7 @@ constexpr int kGroupPart = kGroupRows - 1;
 constexpr int kMaxGroups = 2 * (kMaxD + 1) / 3;
 constexpr int kGroupClasses = 30;
 constexpr int kGroupWords = kGroupClasses + 1;
+constexpr int kGroupSamples = 256;  // points whose parts are looked at first, a byte each
 template <int R>
 struct GroupRow {
   int32_t point;
