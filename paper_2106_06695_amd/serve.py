@@ -74,11 +74,13 @@ def build_peak_bytes(N: int, d: int, order: int = 1) -> int:
     every vertex distinct. Per splat entry (N(d+1) of them): 48 bytes of hash
     table, 12 of slots and unsorted entries, about 40 of sort and order
     buffers, 35 of the kept structure, 4 d of keys, 8 order (d+1) of
-    neighbour table and, for orders 1 and 2, (3 + 7 order) (d+1) of blur
-    groups."""
+    neighbour table and, for orders 1 and 2, d >= 5 and 8,192 entries or more,
+    which lattices without blur groups fall short of, (3 + 7 order) (d+1) of
+    those."""
     D = d + 1
     L = N * D
-    return int((136 + 4 * d + (8 * order + (3 + 7 * order if order <= 2 else 0)) * D) * L + 8 * N * d + (64 << 20))
+    groups = 3 + 7 * order if order <= 2 and d >= 5 and L >= 8192 else 0
+    return int((136 + 4 * d + (8 * order + groups) * D) * L + 8 * N * d + (64 << 20))
 
 
 def solve_bytes(N: int, C: int, d: int, m: int) -> int:
