@@ -5,8 +5,8 @@
 // direction update and emits p.p per tile; after the blur a lattice kernel
 // forms p.Ap = scale * u.(B u) + noise * p.p (u = W^T p: the quadratic
 // form of W B W^T taken on the m lattice rows instead of the n points) and
-// a one-block kernel turns it into alpha; the slice then moves the residual
-// (r -= alpha A p, never storing A p) and its last block decides
+// a fold of its partial sums turns it into alpha; the slice then moves the
+// residual (r -= alpha A p, never storing A p) and the fold of its r.r decides
 // convergence and beta. The host only polls the per-column "active" flags
 // every few iterations. Where lattice points are few against the points, the
 // vectors live on the lattice instead (cg_tile.h).

@@ -1,8 +1,8 @@
 // Scalar steps of the conjugate-gradient recurrence (Section 2, Krylov
 // methods): fold per-chunk partial sums in a fixed order and apply one step.
-// The solver's one-block scalar kernel runs it after a vector kernel; the
-// slice's CG variant runs it in its last block to finish, which saves a
-// launch where the kernel has few (persistent) blocks.
+// The solver's one-block scalar kernel runs it after a vector or tile kernel, or
+// the last block of that kernel to finish, which saves a launch where the kernel
+// has few blocks (kFoldBlocks).
 #ifndef SGP_CG_STEP_H
 #define SGP_CG_STEP_H
 #include "sgp_internal.h"
@@ -62,9 +62,10 @@ constexpr int64_t kFoldBlocks = 100;
 //   pp:    row t gets noise * p.p of tile t (from the splat).
 //   alpha: rows [0, lat_parts) of its partials get scale * u.Bu of a
 //          block of lattice rows, the rows after them the sums of 16
-//          consecutive pp rows; a one-block launch folds them into alpha.
+//          consecutive pp rows, which are folded into alpha.
 //   beta:  row t of its partials gets the new r.r of tile t (from the
-//          slice, which updates r in place); its last block folds beta.
+//          slice, which updates r in place), folded into beta.
+// Either fold is the last block's, or a one-block launch (kFoldBlocks).
 struct CgMvm {
   CgHook alpha;
   int64_t lat_parts;

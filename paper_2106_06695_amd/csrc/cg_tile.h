@@ -103,6 +103,10 @@ __device__ __forceinline__ void slice_step(const double* rows, const uint16_t* s
 // Bound by LDS reads and the barriers between its phases: at n = 2M, d = 11,
 // C = 16 a tile takes about 9.5 us, of which its 0.83 MB of LDS row reads take
 // 3.5 us at the rate of random padded rows (233 of a CU's 300 B/ns, measured).
+// What the iteration keeps in flight does not fit the 128 registers of four
+// waves a SIMD: 11 of a lane's spill at G = 16 (48 bytes), 19 to 21 at G = 8 and
+// 2, 3 at G = 1, and 70 to 80 scalar ones into vector lanes; a spilled value that
+// is read back waits behind the tile's loads. G = 4, at two waves, has none.
 // 299 us an iteration, where the splat with the direction update (244 us) and
 // the slice with the residual update (260 us) moved the same vectors per point.
 template <int G, int MODE, bool CV>
@@ -263,7 +267,6 @@ __global__ __launch_bounds__(cg_tile_threads<G>()) __attribute__((amdgpu_waves_p
     const int ne = cur.np * a.D;
     const int cg = cur.ch * G + cl;
     const bool live = cg < a.C;
-    const bool full = cg + S::VW <= a.C;
     __syncthreads();  // the previous tile is done with the LDS
     if constexpr (kSlice) {
 #pragma unroll

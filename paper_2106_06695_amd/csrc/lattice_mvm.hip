@@ -809,7 +809,7 @@ struct SliceLds {
   int zrow;  // an all-zero lattice row past the staged rows and the reduction area
 };
 template <typename TU, int G, int NT = 1024>
-__host__ __device__ inline SliceLds slice_lds(int P, int D, int maxq) {
+__host__ __device__ inline SliceLds slice_lds(int P, int D) {
   using S = TileShape<TU, G, NT>;
   SliceLds o;
   const size_t row = sizeof(TU) * (size_t)S::RS;
@@ -1121,19 +1121,19 @@ __global__ __launch_bounds__(NT) void k_slice_tile(
       }
     }
   }
-  // CG: the last block to finish folds the tiles' r . r into beta
+  // CG: the tiles' r . r folded into beta, where this grid is small (kFoldBlocks)
   if constexpr (CG) cg_finish(hook, a.C, (double*)smem);
 }
 
 
 template <typename TU>
-size_t slice_lds_g(int P, int D, int maxq, int g) {
+size_t slice_lds_g(int P, int D, int g) {
   switch (g) {
-    case 1: return slice_lds<TU, 1>(P, D, maxq).total;
-    case 2: return slice_lds<TU, 2>(P, D, maxq).total;
-    case 4: return slice_lds<TU, 4>(P, D, maxq).total;
-    case 8: return slice_lds<TU, 8>(P, D, maxq).total;
-    default: return slice_lds<TU, 16>(P, D, maxq).total;
+    case 1: return slice_lds<TU, 1>(P, D).total;
+    case 2: return slice_lds<TU, 2>(P, D).total;
+    case 4: return slice_lds<TU, 4>(P, D).total;
+    case 8: return slice_lds<TU, 8>(P, D).total;
+    default: return slice_lds<TU, 16>(P, D).total;
   }
 }
 
@@ -1521,8 +1521,6 @@ int mvm_g(const sgp_lattice* L, const TU* V, const uint32_t* perm, int C, TU* ou
   TU* frag = part + L->npiece * C;  // 2 rows per gather range
   const int chunks = (C + G - 1) / G;
   const int P = L->tile_points;
-  const dim3 tgrid((unsigned)L->ntiles, (unsigned)chunks);
-  const int maxq = L->max_tile_runs;
   SplatArgs<TU> sa;
   sa.n = L->n;
   sa.items = L->ntiles * chunks;
@@ -1604,7 +1602,7 @@ int mvm_g(const sgp_lattice* L, const TU* V, const uint32_t* perm, int C, TU* ou
   auto launch = [&](auto nt_tag) {
     ProfScope ps(KK_SLICE, s);
     constexpr int NT = decltype(nt_tag)::value;
-    la.lds = slice_lds<TU, G, NT>(P, D, maxq);
+    la.lds = slice_lds<TU, G, NT>(P, D);
     if (cgm) {
       const unsigned grid = persistent_grid((const void*)&k_slice_tile<TU, G, true, NT>, NT, la.lds.total,
                                             la.items, lc.slice_bpc);
@@ -1639,12 +1637,12 @@ constexpr size_t kCgTileLds = 163840 - 2048;
 int chunk_lanes(const sgp_lattice* L, int C, size_t elem) {
   int g = lanes_for(C);
   if (g > kMaxChunk) g = kMaxChunk;
-  const int D = L->d + 1, P = L->tile_points, maxq = L->max_tile_runs;
+  const int D = L->d + 1, P = L->tile_points;
   const size_t budget = (size_t)tuning().lds_budget;
   const size_t slice_budget = (size_t)tuning().slice_lds_budget;
   while (g > 1) {
     const size_t splat = elem == 8 ? splat_lds<double>(L, g).end : splat_lds<float>(L, g).end;
-    const size_t slice = elem == 8 ? slice_lds_g<double>(P, D, maxq, g) : slice_lds_g<float>(P, D, maxq, g);
+    const size_t slice = elem == 8 ? slice_lds_g<double>(P, D, g) : slice_lds_g<float>(P, D, g);
     if (splat <= budget && slice <= slice_budget) break;
     g >>= 1;
   }
@@ -1822,11 +1820,17 @@ int lat_cg(const sgp_lattice* L, int C, const CgLat& cl, LatStep step, hipStream
 // bytes, hence 2/3). Measured, point form against lattice form: m / n = 0.07
 // (n = 2M, d = 11, C = 16) 18.36 -> 14.9 ms for a build and 20 iterations;
 // 0.022 (n = 500,000, d = 8, C = 1) 1.79 -> 1.31 ms for 16; 0.44 (n = 2M)
-// equal. Below 4096 lattice points a solve is bound by its launches either
-// way, and its iterates depend on the rounding after about 12 iterations (the
-// Krylov basis loses its orthogonality once the largest eigenvalue has
-// converged), so those keep the point form's arithmetic. The rule depends on
-// the lattice alone, so a column is solved the same way in any batch.
+// equal.
+// The bound below is for the iterates, not for speed: on smaller lattices they
+// depend on the rounding after about 12 iterations (the Krylov basis loses its
+// orthogonality once the largest eigenvalue has converged), so those keep the
+// point form's arithmetic. In time the lattice form would lose there on few
+// points, where the point form has fewer launches, and gain on many (16
+// iterations, point | lattice form): n = 20,000, d = 3, m = 715, C = 8 0.58 |
+// 0.70 ms; n = 30,011, d = 7, m = 3,132, C = 8 0.85 | 0.89; n = 200,000, d = 6,
+// m = 1,410, C = 8 1.40 | 1.15; n = 2M, d = 6, m = 2,048, C = 16 8.08 | 5.03.
+// The rule depends on the lattice alone, so a column is solved the same way in
+// any batch; point sets of one shape may fall on either side of it.
 constexpr int64_t kLatticeCgMin = 4096;
 bool cg_on_lattice(const sgp_lattice* L) {
   return L->m >= kLatticeCgMin && 3 * L->m <= 2 * L->n && cg_tile_lds_g(L, kMaxCgCols, 1) <= kCgTileLds;

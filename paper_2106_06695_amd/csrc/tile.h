@@ -159,7 +159,6 @@ struct TileShape {
   static constexpr int NT = NT_;
   static constexpr int kPts = 256;
   static constexpr int EPT = kMaxTileEntries / NT;  // entries per thread
-  static constexpr int RPT = 2;                      // runs prefetched per thread (splat)
   static constexpr int VPT = (kPts * G) / NT > 0 ? (kPts * G) / NT : 1;  // point values
   static constexpr int VW = G < 4 ? G : 4;  // channels per lane
   static constexpr int LPR = G / VW;        // lanes per run (splat) or point (slice)
