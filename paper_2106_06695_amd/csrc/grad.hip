@@ -206,7 +206,10 @@ extern "C" int lattice_mvm_grad(const sgp_lattice* L, const float* X, const floa
       e = pool_alloc(&bufs[k], bytes, s);
       if (e != hipSuccess) bufs[k] = nullptr;
     }
-    if (e == hipSuccess && L->ubuf.bytes < work) {
+    // (the narrowest block's are left to its first MVM, whose wait for the
+    // lattice's last use then overlaps with k_grad_channels: n = 100,003, d = 6,
+    // forward and backward 0.96 against 1.02 ms)
+    if (e == hipSuccess && W > narrowest && L->ubuf.bytes < work) {
       if (const int rc = wait_last_use(L)) return rc;
       dev_free(Lm->ubuf);
       bytes = work;
