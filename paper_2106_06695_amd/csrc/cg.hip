@@ -321,7 +321,8 @@ int cg_setup(const sgp_lattice* L, const float* b, int C, float noise, float tol
   // r, p in fp64, then x in fp32; on the lattice, b in sorted order
   const size_t vec_bytes = lat ? sizeof(float) * nC : (sizeof(double) * 2 + sizeof(float)) * nC;
   if ((rc = dev_reserve(L, Lm->cgvec, vec_bytes, s))) return rc;
-  if (lat && (rc = dev_reserve(L, Lm->ubuf, sizeof(double) * cg_lat_work_elems(L, C), s))) return rc;
+  const bool fuse = blur_fuse_enabled();
+  if (lat && (rc = dev_reserve(L, Lm->ubuf, sizeof(double) * cg_lat_work_elems(L, C, fuse), s))) return rc;
   // partial sums: one row per superchunk from the init kernel or per tile
   // from the slice (r.r); one per superchunk of lattice rows and per 16
   // tiles (alpha); one per tile from the splat (p.p); then the scalar
@@ -355,6 +356,7 @@ int cg_setup(const sgp_lattice* L, const float* b, int C, float noise, float tol
   cgm.ntiles = L->ntiles;
   cgm.beta = CgHook{o->rr_parts, L->ntiles, st, counter, (int)SM_BETA, (double)tol, 0.0, 0};
   cgm.r = o->r;
+  cgm.fuse = fuse;
   // The same solve with its vectors on the lattice: the first tile pass
   // starts it, the last one forms x.
   CgLat& cl = o->cl;
@@ -367,6 +369,7 @@ int cg_setup(const sgp_lattice* L, const float* b, int C, float noise, float tol
   cl.start = CgHook{o->rr_parts, L->ntiles, st, counter, (int)SM_START, (double)tol, 0.0, 0};
   cl.alpha = CgHook{al_parts, lparts, st, counter, (int)SM_ALPHA_LAT, (double)tol, (double)noise, 0};
   cl.beta = cgm.beta;
+  cl.fuse = fuse;
   return SGP_OK;
 }
 

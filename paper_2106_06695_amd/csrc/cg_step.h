@@ -73,6 +73,7 @@ struct CgMvm {
   int64_t ntiles;
   CgHook beta;
   double* r;
+  bool fuse;  // blur_fuse_enabled when the solve began
 };
 
 // A solve whose vectors live on the lattice (cg_tile.h): the caller's rhs
@@ -86,6 +87,7 @@ struct CgLat {
   double noise;
   int64_t lat_parts;  // partial rows of u.(B u)
   CgHook start, alpha, beta;
+  bool fuse;          // blur_fuse_enabled when the solve began
 };
 
 constexpr int kFold = 64;  // fixed fold width: the order depends on nparts only

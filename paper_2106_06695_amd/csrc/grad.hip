@@ -185,7 +185,7 @@ extern "C" int lattice_mvm_grad(const sgp_lattice* L, const float* X, const floa
   // 256 MiB Infinity Cache. The blur by groups reads and writes each row once a
   // group, so that rows of at least 64 bytes (W = 16) pay, whatever the arrays'
   // size: m = 4.2M, d = 16, 8 columns: blur and gather of a pass 31 and
-  // 6.7 ms with W = 16, 30 and 10 ms with W = 32. These arrays are up to four
+  // 6.7 ms with W = 16, 30 and 10 ms with W = 32. These arrays are up to three
   // times as large, so where there is no memory for them the blocks are halved,
   // down to the width that the pairs would have.
   const int all = kb * CH;

@@ -1241,12 +1241,17 @@ void split_rows(int64_t rows, int R, int64_t cap, unsigned* blocks, int64_t* row
   *blocks = (unsigned)((rows + *rows_per_block - 1) / *rows_per_block);
 }
 
-// Work memory of one MVM in elements of its accumulator type: four m x C
-// lattice value arrays (the splat's result and the blur's ping-pong; a
-// fifth inside CG, where the splat's result must outlive the blur), one
-// partial row per run piece, two fragment rows per gather range.
-size_t mvm_work_elems(const sgp_lattice* L, int C, bool cg) {
-  return (size_t)((cg ? 5 : 4) * L->m + L->npiece + 2 * gather_ranges(L)) * (size_t)C;
+// m x C lattice value arrays that the blur works in beside the one it reads: its
+// ping-pong between two a chain (the second chain's other one may be the input,
+// where that need not outlive the blur: not inside CG), or one a chain, in place,
+// by groups of directions.
+int blur_arrays(const sgp_lattice* L, bool cg, bool fuse) { return L->ngroups && fuse ? 2 : cg ? 4 : 3; }
+
+// Work memory of one MVM in elements of its accumulator type: m x C lattice
+// value arrays (the splat's result and the blur's), one partial row per run
+// piece, two fragment rows per gather range.
+size_t mvm_work_elems(const sgp_lattice* L, int C, bool cg, bool fuse) {
+  return (size_t)((1 + blur_arrays(L, cg, fuse)) * L->m + L->npiece + 2 * gather_ranges(L)) * (size_t)C;
 }
 
 // U0 = the partial rows summed per lattice point (+ beta U0 per column when
@@ -1298,8 +1303,8 @@ int gather_g(const sgp_lattice* L, const TU* part, TU* U0, TU* frag, int C, cons
 // saves: with four rows a thread, m = 4,453 (d = 6) 55, 571; 63, 651 |
 // 66, 503; 68, 571. As good on many columns: m = 1,460, one MVM of 256 columns
 // 87 | 175 us.
-bool col_path(const sgp_lattice* L, int64_t parts) {
-  return L->order == 1 && L->m <= kColRows && parts <= kColParts && blur_fuse_enabled();
+bool col_path(const sgp_lattice* L, int64_t parts, bool fuse) {
+  return L->order == 1 && L->m <= kColRows && parts <= kColParts && fuse;
 }
 
 template <typename TU, int MODE>
@@ -1331,10 +1336,11 @@ int col_launch(const sgp_lattice* L, TU* U, const TU* frag, TU* Bu, int C, doubl
 }
 
 // The blur of U0 (m x C): B1 .. B4 are work arrays (B4 may be U0 where it need
-// not outlive the blur); *result is the array that holds the blurred values
+// not outlive the blur; of blur_arrays 2 only B1 and B2 are there); *result is the array that holds the blurred values
 // (forward + reverse in SYMMETRIC order).
 template <typename TU, int G>
-int blur_g(const sgp_lattice* L, TU* U0, TU* B1, TU* B2, TU* B3, TU* B4, int C, hipStream_t s, const TU** result) {
+int blur_g(const sgp_lattice* L, TU* U0, TU* B1, TU* B2, TU* B3, TU* B4, int C, bool fused, hipStream_t s,
+           const TU** result) {
   const int d = L->d, T = 2 * L->order;
   const int64_t m = L->m, mC = m * C;
   const bool sym = L->blur == SGP_BLUR_SYMMETRIC;
@@ -1360,8 +1366,8 @@ int blur_g(const sgp_lattice* L, TU* U0, TU* B1, TU* B2, TU* B3, TU* B4, int C, 
   auto kdir = [&](int step, int chain) {
     return chain == 0 ? ((L->blur == SGP_BLUR_REVERSE) ? d - step : step) : d - step;
   };
-  const bool fuse = L->order == 1 && blur_fuse_enabled();
-  const bool groups = L->ngroups && blur_fuse_enabled();
+  const bool fuse = L->order == 1 && fused;
+  const bool groups = L->ngroups && fused;
   // Large lattices: the chains' launches run one chain after the other (all of
   // chain 0's, then chain 1's), so that a launch's arrays sit in the Infinity
   // Cache together.
@@ -1508,16 +1514,17 @@ SplatLists splat_lds(const sgp_lattice* L, int G) {
 // internal order), and the MVM finishes the CG step (CgMvm).
 template <typename TU, int G>
 int mvm_g(const sgp_lattice* L, const TU* V, const uint32_t* perm, int C, TU* out, hipStream_t s,
-          TU noise, const CgMvm* cgm, const LaunchChoice& lc, void* work, const CgDirUpdate* up) {
+          TU noise, const CgMvm* cgm, const LaunchChoice& lc, void* work, const CgDirUpdate* up, bool fuse) {
   const int D = L->d + 1;
   const int64_t m = L->m, mC = m * C;
   const TU* p = cgm ? V : nullptr;
   TU* U0 = (TU*)work;
   TU* B1 = U0 + mC;
   TU* B2 = B1 + mC;
-  TU* B3 = B2 + mC;
-  TU* B4 = cgm ? B3 + mC : U0;  // chain 1's second array (U0 itself outside CG)
-  TU* part = (cgm ? B4 : B3) + mC;
+  const int arrays = blur_arrays(L, cgm != nullptr, fuse);
+  TU* B3 = arrays > 2 ? B2 + mC : nullptr;
+  TU* B4 = arrays > 3 ? B3 + mC : U0;  // chain 1's second array (U0 itself outside CG)
+  TU* part = U0 + (1 + arrays) * mC;
   TU* frag = part + L->npiece * C;  // 2 rows per gather range
   const int chunks = (C + G - 1) / G;
   const int P = L->tile_points;
@@ -1560,7 +1567,7 @@ int mvm_g(const sgp_lattice* L, const TU* V, const uint32_t* perm, int C, TU* ou
                          (const float*)L->ent_w.ptr, V, perm, part, pp, sa, CgDirUpdate{});
     SGP_LAUNCH_CHECK("k_splat_tile");
   }
-  const bool col = col_path(L, cgm ? cgm->alpha.nparts : 0);
+  const bool col = col_path(L, cgm ? cgm->alpha.nparts : 0, fuse);
   if (const int rc = gather_g<TU, G>(L, part, U0, frag, C, nullptr, !col, s)) return rc;
   const TU* blurred = B1;
   const bool sym = L->blur == SGP_BLUR_SYMMETRIC;
@@ -1573,7 +1580,7 @@ int mvm_g(const sgp_lattice* L, const TU* V, const uint32_t* perm, int C, TU* ou
     else
       rc = col_launch<TU, CM_MVM>(L, U0, frag, B1, C, 0.0, CgMvm{}, s);
     if (rc) return rc;
-  } else if (const int rc = blur_g<TU, G>(L, U0, B1, B2, B3, B4, C, s, &blurred)) {
+  } else if (const int rc = blur_g<TU, G>(L, U0, B1, B2, B3, B4, C, fuse, s, &blurred)) {
     return rc;
   }
   if (cgm && !col) {
@@ -1649,15 +1656,16 @@ int chunk_lanes(const sgp_lattice* L, int C, size_t elem) {
   return g;
 }
 
-// work: the MVM's work memory (mvm_work_elems(L, C, cgm) elements of TU),
-// or null for the lattice's own buffer, grown on demand.
+// work: the MVM's work memory (mvm_work_elems elements of TU), or null for the
+// lattice's own buffer, grown on demand.
 template <typename TU>
 int mvm_dispatch(const sgp_lattice* L, const TU* V, const uint32_t* perm, int C, TU* out,
                  hipStream_t s, TU noise, const CgMvm* cgm, void* work = nullptr,
                  const CgDirUpdate* up = nullptr) {
+  const bool fuse = cgm ? cgm->fuse : blur_fuse_enabled();
   if (!work) {
     int rc = dev_reserve(L, const_cast<sgp_lattice*>(L)->ubuf,
-                         sizeof(TU) * mvm_work_elems(L, C, cgm != nullptr), s);
+                         sizeof(TU) * mvm_work_elems(L, C, cgm != nullptr, fuse), s);
     if (rc) return rc;
     work = L->ubuf.ptr;
   }
@@ -1669,11 +1677,11 @@ int mvm_dispatch(const sgp_lattice* L, const TU* V, const uint32_t* perm, int C,
     (void)tune_find(L, C, (int)sizeof(TU), TF_MVM, &lc);
   if (lc.g < 1 || lc.g > gmax || (lc.g & (lc.g - 1))) lc.g = gmax;  // never wider than the LDS allows
   switch (lc.g) {
-    case 1: return mvm_g<TU, 1>(L, V, perm, C, out, s, noise, cgm, lc, work, up);
-    case 2: return mvm_g<TU, 2>(L, V, perm, C, out, s, noise, cgm, lc, work, up);
-    case 4: return mvm_g<TU, 4>(L, V, perm, C, out, s, noise, cgm, lc, work, up);
-    case 8: return mvm_g<TU, 8>(L, V, perm, C, out, s, noise, cgm, lc, work, up);
-    default: return mvm_g<TU, 16>(L, V, perm, C, out, s, noise, cgm, lc, work, up);
+    case 1: return mvm_g<TU, 1>(L, V, perm, C, out, s, noise, cgm, lc, work, up, fuse);
+    case 2: return mvm_g<TU, 2>(L, V, perm, C, out, s, noise, cgm, lc, work, up, fuse);
+    case 4: return mvm_g<TU, 4>(L, V, perm, C, out, s, noise, cgm, lc, work, up, fuse);
+    case 8: return mvm_g<TU, 8>(L, V, perm, C, out, s, noise, cgm, lc, work, up, fuse);
+    default: return mvm_g<TU, 16>(L, V, perm, C, out, s, noise, cgm, lc, work, up, fuse);
   }
 }
 
@@ -1684,11 +1692,12 @@ int mvm_dispatch(const sgp_lattice* L, const TU* V, const uint32_t* perm, int C,
 struct LatWork {
   double *yr, *yp, *yx, *u, *b1, *b2, *b3, *b4, *part, *frag;
 };
-LatWork lat_work(const sgp_lattice* L, int C, double* work) {
+LatWork lat_work(const sgp_lattice* L, int C, const CgLat& cl) {
   const int64_t mC = L->m * C;
-  LatWork w;
-  double* p = work;
+  LatWork w = {};
+  double* p = cl.work;
   for (double** a : {&w.yr, &w.yp, &w.yx, &w.u, &w.b1, &w.b2, &w.b3, &w.b4}) {
+    if (a == &w.b3 && blur_arrays(L, true, cl.fuse) == 2) break;
     *a = p;
     p += mC;
   }
@@ -1700,7 +1709,7 @@ LatWork lat_work(const sgp_lattice* L, int C, double* work) {
 template <int G, int MODE>
 int cg_tile_launch(const sgp_lattice* L, int C, const CgLat& cl, const CgHook& hook, const double* Y,
                    const LaunchChoice& lc, hipStream_t s) {
-  const LatWork w = lat_work(L, C, cl.work);
+  const LatWork w = lat_work(L, C, cl);
   CgTileArgs a;
   a.n = L->n;
   a.chunks = (C + G - 1) / G;
@@ -1744,7 +1753,7 @@ enum LatStep { LS_START, LS_FIRST, LS_ITER, LS_OUT };
 
 template <int G>
 int lat_cg_g(const sgp_lattice* L, int C, const CgLat& cl, LatStep step, const LaunchChoice& lc, hipStream_t s) {
-  const LatWork w = lat_work(L, C, cl.work);
+  const LatWork w = lat_work(L, C, cl);
   const double* beta = cl.beta.st->beta;
   int rc;
   if (step == LS_OUT) return cg_tile_launch<G, CT_OUT>(L, C, cl, cl.beta, w.yx, lc, s);
@@ -1753,7 +1762,7 @@ int lat_cg_g(const sgp_lattice* L, int C, const CgLat& cl, LatStep step, const L
     return gather_g<double, G>(L, w.part, w.u, w.frag, C, nullptr, true, s);
   }
   const double* bu = nullptr;
-  if ((rc = blur_g<double, G>(L, w.u, w.b1, w.b2, w.b3, w.b4, C, s, &bu))) return rc;
+  if ((rc = blur_g<double, G>(L, w.u, w.b1, w.b2, w.b3, w.b4, C, cl.fuse, s, &bu))) return rc;
   const double scale = (L->blur == SGP_BLUR_SYMMETRIC ? 0.5 : 1.0) * (double)L->outputscale;
   CgMvm am = {};
   am.alpha = cl.alpha;
@@ -1836,8 +1845,8 @@ bool cg_on_lattice(const sgp_lattice* L) {
   return L->m >= kLatticeCgMin && 3 * L->m <= 2 * L->n && cg_tile_lds_g(L, kMaxCgCols, 1) <= kCgTileLds;
 }
 
-size_t cg_lat_work_elems(const sgp_lattice* L, int C) {
-  return (size_t)(8 * L->m + L->npiece + 2 * gather_ranges(L)) * (size_t)C;
+size_t cg_lat_work_elems(const sgp_lattice* L, int C, bool fuse) {
+  return (size_t)((4 + blur_arrays(L, true, fuse)) * L->m + L->npiece + 2 * gather_ranges(L)) * (size_t)C;
 }
 
 int cg_lat_start(const sgp_lattice* L, int C, const CgLat& cl, hipStream_t s) {
@@ -1859,7 +1868,9 @@ int mvm_cg(const sgp_lattice* L, double* p, int C, hipStream_t s, double noise, 
   return mvm_dispatch<double>(L, p, nullptr, C, cg.r, s, noise, &cg, nullptr, up);
 }
 
-size_t mvm_f32_work_bytes(const sgp_lattice* L, int C) { return sizeof(float) * mvm_work_elems(L, C, false); }
+size_t mvm_f32_work_bytes(const sgp_lattice* L, int C) {
+  return sizeof(float) * mvm_work_elems(L, C, false, blur_fuse_enabled());
+}
 
 int mvm_f32(const sgp_lattice* L, const float* V, int C, float* out, hipStream_t s) {
   return mvm_dispatch<float>(L, V, nullptr, C, out, s, 0.f, nullptr);
@@ -2025,7 +2036,7 @@ extern "C" int lattice_mvm_noalloc(const sgp_lattice* L, const float* values, in
     set_error("lattice_mvm_noalloc: out overlaps values");
     return SGP_EINVAL;
   }
-  const size_t need = sizeof(float) * mvm_work_elems(L, C, false);
+  const size_t need = sizeof(float) * mvm_work_elems(L, C, false, false);  // the same whatever the switch says
   if (need > kScratchBytes) {
     set_error("lattice_mvm_noalloc: this lattice and C = %d need %zu bytes of work memory; the "
               "no-allocation entry point has %zu (use lattice_mvm)", (int)C, need, kScratchBytes);

@@ -113,6 +113,8 @@ enum KernelKind {
 bool profiling();
 // Process-wide switch for graph replay of CG iterations.
 bool cg_graphs_enabled();
+// Process-wide switch for blur launches of several steps: read once per MVM or
+// solve, as the work memory depends on it.
 bool blur_fuse_enabled();
 // True when the symmetric blur should run its chains one after the other
 // for lattice value arrays of `bytes` in all (four arrays). The defaults: half
@@ -247,7 +249,7 @@ struct sgp_lattice {
   hipEvent_t last_use = nullptr;  // recorded at the end of every call on the lattice
 
   // work buffers, grown on demand
-  sgp::DevBuf ubuf;   // lattice values 4 x m x C (5 inside CG), piece partial sums npiece x C, gather fragments
+  sgp::DevBuf ubuf;   // lattice values (mvm_work_elems, cg_lat_work_elems), piece partial sums, gather fragments
   sgp::DevBuf cgvec;  // CG vectors: r and p (n x C fp64 each), then x (n x C fp32)
   sgp::DevBuf cgred;  // CG partial sums and per-column scalars
 };
@@ -303,7 +305,7 @@ int mvm_cg(const sgp_lattice* L, double* p, int C, hipStream_t s, double noise, 
 // its work memory in doubles, and its steps (start; one iteration; x out)
 struct CgLat;
 bool cg_on_lattice(const sgp_lattice* L);
-size_t cg_lat_work_elems(const sgp_lattice* L, int C);
+size_t cg_lat_work_elems(const sgp_lattice* L, int C, bool fuse);
 int cg_lat_start(const sgp_lattice* L, int C, const CgLat& cl, hipStream_t s);
 int cg_lat_iter(const sgp_lattice* L, int C, const CgLat& cl, bool first, hipStream_t s);
 int cg_lat_out(const sgp_lattice* L, int C, const CgLat& cl, hipStream_t s);

@@ -129,3 +129,49 @@ def test_adjoint_narrows_its_blocks(mem):
     dX2, _ = sgp.lattice_mvm_grad(lat, X, V, G)
     np.testing.assert_array_equal(dX2.cpu().numpy(), ref)
     lat.free()
+
+
+# seed, n, d, ell: m = 16,474 (CG's vectors per point); m = 9,992 of 50,001 points (on the lattice)
+@pytest.mark.parametrize("seed,n,d,ell,on_lattice", [(500, 17000, 11, (0.5, 2.0), False),
+                                                      (205, 50001, 11, (0.7, 2.0), True)])
+def test_work_memory_of_the_blur(mem, seed, n, d, ell, on_lattice):
+    """The blur by groups works in two lattice arrays in place; steps and pairs
+    take three (four inside CG), and the buffer grows when the switch turns to
+    them. Results do not depend on it."""
+    sgp, a = mem
+    C = 3
+    w = workloads.small_case(seed, n, d, channels=C, kind="mixture", ell_range=ell)
+    X, V = _cuda(w.X), _cuda(w.values)
+
+    def largest(call):
+        a.sizes.clear()
+        out = call().cpu().numpy()
+        return out, max(a.sizes, default=0)
+
+    def solve(lat):
+        return lambda: sgp.cg_solve(lat, V, 0.1, 0.0, max_iter=11)[0]
+
+    got = {}
+    for fuse in (True, False):
+        prev = sgp.blur_fuse_enable(fuse)
+        try:
+            for name in ("mvm", "cg"):
+                lat = sgp.lattice_build(X, w.lengthscales)
+                m = lat.m
+                assert m >= 8192 and (3 * m <= 2 * n) == on_lattice
+                got[name, fuse] = largest((lambda: sgp.lattice_mvm(lat, V)) if name == "mvm" else solve(lat))
+                if fuse:  # the same lattice, then without groups and with them again
+                    sgp.blur_fuse_enable(False)
+                    again, _ = largest((lambda: sgp.lattice_mvm(lat, V)) if name == "mvm" else solve(lat))
+                    sgp.blur_fuse_enable(True)
+                    back, grown = largest((lambda: sgp.lattice_mvm(lat, V)) if name == "mvm" else solve(lat))
+                    np.testing.assert_array_equal(again, got[name, True][0])
+                    np.testing.assert_array_equal(back, got[name, True][0])
+                    assert grown == 0
+                lat.free()
+        finally:
+            sgp.blur_fuse_enable(prev)
+    print(f"work memory m={m} on_lattice={on_lattice} {[(k, v[1]) for k, v in got.items()]}", flush=True)
+    for name, extra in (("mvm", 1 * 4), ("cg", 2 * 8)):
+        np.testing.assert_array_equal(got[name, True][0], got[name, False][0])
+        assert got[name, False][1] - got[name, True][1] == extra * m * C
