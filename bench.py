@@ -29,11 +29,11 @@ HBM_PEAK_GBS = 8000.0  # MI355X HBM3E
 
 
 def kernel_bytes(kind: str, n: int, d: int, m: int, C: int, r: int, sym: bool, cg: bool,
-                 dir_frac: float = 0.0) -> float:
+                 dir_frac: float = 0.0, blur=None) -> float:
     """Algorithmic HBM bytes of ONE launch of a kernel kind: int32 indices,
     fp32 weights, every array touched once per launch. Inside CG (cg=True)
     the values and lattice accumulators are fp64, in lattice_mvm fp32.
-    dir_frac: the share of the splat launches that also apply the CG
+    blur: blur_shape of the lattice. dir_frac: the share of the splat launches that also apply the CG
     direction update (r and x in, p and x out: 24 bytes per element)."""
     D = d + 1
     chains = 2 if sym else 1
@@ -47,7 +47,7 @@ def kernel_bytes(kind: str, n: int, d: int, m: int, C: int, r: int, sym: bool, c
     if kind == "cg_lattice":  # B u, y_r, y_p, y_x in, the last three out (fp64)
         return 7 * m * C * 8
     if kind == "blur":       # average per launch: per chain U in, U out, neighbour lists
-        return blur_bytes_per_mvm(d, m, C, r, sym, cg) / blur_launches(d, m, r, sym)
+        return blur_bytes_per_mvm(d, m, C, r, sym, cg, blur[0]) / blur[1]
     if kind == "cg_alpha":   # u and B u in (fp64)
         return 2 * m * C * 8
     if kind == "cg_dir":     # p, r in (fp64), x in (fp32); p out (fp64), x out (fp32)
@@ -62,7 +62,7 @@ def kernel_bytes(kind: str, n: int, d: int, m: int, C: int, r: int, sym: bool, c
 
 
 def survey_bytes(kind: str, n: int, d: int, m: int, C: int, r: int, sym: bool,
-                 dir_frac: float = 0.0) -> float:
+                 dir_frac: float = 0.0, blur=None) -> float:
     """Algorithmic HBM bytes of ONE launch under the survey's byte model:
     fp32 values, int32 indices and fp32 weights whatever precision a kernel
     computes in, neighbour lists counted once per sweep. The splat stage is
@@ -77,7 +77,7 @@ def survey_bytes(kind: str, n: int, d: int, m: int, C: int, r: int, sym: bool,
     if kind == "splat":      # k_splat_tile alone: W and V in (U is the gather's)
         return n * D * 8 + n * C * 4 + dir_frac * 16 * n * C
     if kind == "blur":
-        return blur_bytes_per_mvm(d, m, C, r, sym, False) / blur_launches(d, m, r, sym)
+        return blur_bytes_per_mvm(d, m, C, r, sym, False, blur[0]) / blur[1]
     if kind == "slice":      # CG variant: idx + w, U, p and r in, r out
         return n * D * 8 + chains * m * C * 4 + 3 * n * C * 4
     if kind == "cg_tile":    # lattice CG: W, the rhs and the lattice residual in (U is the gather's)
@@ -89,30 +89,39 @@ def survey_bytes(kind: str, n: int, d: int, m: int, C: int, r: int, sym: bool,
     return 0.0
 
 
-def blur_passes(d, m, r):
-    """Passes over a chain's lattice values per blur: one per group of up to
-    four directions where the lattice keeps groups, else one per two
-    directions (three-tap stencil) or per direction."""
-    if r <= 2 and d >= 5 and m >= 8192:
-        return (d + 4) // 4
-    return (d + 2) // 2 if r == 1 else d + 1
+def blur_shape(sgp, lat, C, sym):
+    """Passes over a chain's lattice values and launches per blur of a lattice
+    of order 1, counted: one pass per group of directions where the lattice
+    keeps groups (then, with the chains one after the other, every launch moves
+    one chain and their number is even), else one per two directions, or one
+    block per column for all."""
+    import torch
+    V = torch.zeros((lat.n, C), dtype=torch.float32, device="cuda")
+
+    def launches():
+        with sgp.profile() as prof:
+            sgp.lattice_mvm(lat, V)
+            torch.cuda.synchronize()
+        return prof.results["blur"][0]
+    run = launches()
+    prev = sgp.blur_seq_bytes(0)
+    try:
+        apart = launches()
+    finally:
+        sgp.blur_seq_bytes(prev)
+    if not sym or run == 1:
+        return run, run
+    return (apart // 2 if apart % 2 == 0 else (lat.d + 2) // 2), run
 
 
-def blur_launches(d, m, r, sym):
-    """Launches per blur: with groups, the chains' last passes do not share
-    one."""
-    grouped = r <= 2 and d >= 5 and m >= 8192
-    return blur_passes(d, m, r) + (1 if grouped and sym else 0)
-
-
-def blur_bytes_per_mvm(d, m, C, r, sym, cg):
+def blur_bytes_per_mvm(d, m, C, r, sym, cg, passes):
     ub = 8 if cg else 4
     chains = 2 if sym else 1
-    return chains * (blur_passes(d, m, r) * 2 * m * C * ub + (d + 1) * 2 * r * m * 4)
+    return chains * (passes * 2 * m * C * ub + (d + 1) * 2 * r * m * 4)
 
 
-def mvm_bytes(n, d, m, C, r, sym, cg=False):
-    return (kernel_bytes("splat", n, d, m, C, r, sym, cg) + blur_bytes_per_mvm(d, m, C, r, sym, cg)
+def mvm_bytes(n, d, m, C, r, sym, passes, cg=False):
+    return (kernel_bytes("splat", n, d, m, C, r, sym, cg) + blur_bytes_per_mvm(d, m, C, r, sym, cg, passes)
             + kernel_bytes("slice", n, d, m, C, r, sym, cg))
 
 
@@ -342,7 +351,7 @@ def configs_bench(sgp):
         sgp.lattice_mvm(lat, V, y)
     torch.cuda.synchronize()
     mvm_s = (time.perf_counter() - t0) / reps
-    B = mvm_bytes(w.n, w.d, lat.m, 1, 1, True)
+    B = mvm_bytes(w.n, w.d, lat.m, 1, 1, True, blur_shape(sgp, lat, 1, True)[0])
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     x, its, rel = sgp.cg_solve(lat, V, w.noise, w.tol, max_iter=w.max_iter)
@@ -368,7 +377,7 @@ def configs_bench(sgp):
     mvm_ms = _median_ms(lambda: sgp.lattice_mvm(lat, V, y), 10)
     sgp.lattice_mvm_grad(lat, X, V, G)
     adj_ms = _median_ms(lambda: sgp.lattice_mvm_grad(lat, X, V, G), 3)
-    B = mvm_bytes(w.n, w.d, lat.m, w.C, 1, True)
+    B = mvm_bytes(w.n, w.d, lat.m, w.C, 1, True, blur_shape(sgp, lat, w.C, True)[0])
     out["ws4"] = {"workload": "n=1,000,000 d=16 X~U[-1,1]^16, l~logU[0.3,3], C=8; forward MVM "
                               "and adjoint (dX, dlog l) of sum(G * K V)",
                   "m": lat.m, "build_ms": build_ms, "mvm_ms": mvm_ms,
@@ -449,9 +458,10 @@ def paper_sparsity_bench(sgp, X, V, w, x, args):
         sgp.lattice_mvm(lat, V, out)
     torch.cuda.synchronize()
     mvm_s = (time.perf_counter() - t0) / reps
-    lat.free()
     n, d, C = w.n, w.d, w.C
-    B = mvm_bytes(n, d, m, C, 1, args.blur == "symmetric")
+    sym = args.blur == "symmetric"
+    B = mvm_bytes(n, d, m, C, 1, sym, blur_shape(sgp, lat, C, sym)[0])
+    lat.free()
     return {"workload": "ws3p: ws3 with lengthscales x %.4f (the paper's Houseelectric sparsity)" % scale,
             "m": m, "m_over_L": m / (n * (d + 1)), "steps": args.paper_steps, "ms_per_step": ms,
             "value": n * C * iters / (ms / 1e3), "unit": "points*ch/s",
@@ -541,11 +551,13 @@ def main(argv=None):
     # where the solve's vectors live on the lattice one kernel (timed as the
     # splat) slices the residual, sums r.r and splats it
     lattice_cg = not prof.results["slice"][0]
+    lat = sgp.lattice_build(X, w.lengthscales, blur=args.blur)
+    blur = blur_shape(sgp, lat, C, sym)
     kernels = {}
     for kind, (launches, ms) in prof.results.items():
         if launches:
             model = {"splat": "cg_tile", "cg_dir": "cg_lattice"}.get(kind, kind) if lattice_cg else kind
-            b = kernel_bytes(model, n, d, m, C, 1, sym, cg=True, dir_frac=dir_frac)
+            b = kernel_bytes(model, n, d, m, C, 1, sym, cg=True, dir_frac=dir_frac, blur=blur)
             avg = ms / launches
             kernels[kind] = {"launches": launches, "total_ms": round(ms, 3), "avg_us": round(avg * 1e3, 2),
                              "algo_GBps": round(b / (avg / 1e3) / 1e9, 1) if b else None}
@@ -574,8 +586,8 @@ def main(argv=None):
     single = {k: kernels[k]["total_ms"] for k in names if k in kernels}
     dom = max(single, key=single.get)
     splat_native = kernel_bytes("splat", n, d, m, C, 1, sym, cg=True, dir_frac=dir_frac)
-    dom_survey = survey_bytes(dom, n, d, m, C, 1, sym, dir_frac=dir_frac)
-    dom_native = kernel_bytes(dom, n, d, m, C, 1, sym, cg=True, dir_frac=dir_frac)
+    dom_survey = survey_bytes(dom, n, d, m, C, 1, sym, dir_frac=dir_frac, blur=blur)
+    dom_native = kernel_bytes(dom, n, d, m, C, 1, sym, cg=True, dir_frac=dir_frac, blur=blur)
     if lattice_cg:
         tile_s, tile_n = (f("cg_tile", n, d, m, C, 1, sym) for f in
                           (survey_bytes, lambda *a: kernel_bytes(*a, cg=True)))
@@ -595,7 +607,6 @@ def main(argv=None):
     splat_stage = roof(stage[0], ["splat", "splat_gather"], stage[1], stage[2], "splat_stage")
 
     # standalone MVMs on a resident lattice (outside the timed steps)
-    lat = sgp.lattice_build(X, w.lengthscales, blur=args.blur)
     out = torch.empty_like(V)
     for _ in range(3):
         sgp.lattice_mvm(lat, V, out)
@@ -605,7 +616,7 @@ def main(argv=None):
         sgp.lattice_mvm(lat, V, out)
     torch.cuda.synchronize()
     mvm_s = (time.perf_counter() - t0) / args.mvm_reps
-    B = mvm_bytes(n, d, lat.m, C, 1, sym)
+    B = mvm_bytes(n, d, lat.m, C, 1, sym, blur[0])
 
     # the same 20 iterations as C separate single-column solves
     sep_x = torch.empty((n, 1), dtype=torch.float32, device=V.device)
