@@ -13,9 +13,8 @@
 // adds some 8 us where the first cut fits: m = 62,000 (d = 6) 0.56, 0.94, 0.73 ms;
 // 245,000 (d = 6) 1.06, 1.98, 1.32; 673,000 (d = 8) 2.25, 3.12, 2.55; 1.13M
 // (d = 5, no groups in the end) 3.05, 4.70, 2.95 (its neighbour look-ups are
-// faster now, too). Groups of at most two directions do not pay there: an MVM of
-// 8 columns without and with them 64 and 73 us (m = 62,000), 157 and 171
-// (245,000), 405 and 387 (673,000).
+// faster now, too). Groups that are no fewer passes than the fused pairs only
+// pay there with wide rows (blur_by_groups).
 #ifndef SGP_GROUPS_H
 #define SGP_GROUPS_H
 #include <hip/hip_runtime.h>

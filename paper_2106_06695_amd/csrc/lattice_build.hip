@@ -1256,19 +1256,9 @@ bool group_divide(GroupBuild& gb, int D, int most) {
   return true;
 }
 
-// Whether the groups are more passes over the lattice than the fused pairs of
-// order 1 and none of them is a longer one: m = 607,000, d = 5, groups of 2, 2, 1
-// and 1 directions 146 us a blur of 8 fp32 columns, three pairs 115 us.
-bool group_passes_lose(const GroupBuild& gb, int D) {
-  for (int g = 0; g < gb.n; ++g)
-    if (gb.sp.dirs[g] > 2) return false;
-  return gb.n > (D + 1) / 2;
-}
-
 // Place the parts in tiles. Groups whose parts outgrow a tile are divided, to
-// three and then to two directions; a lattice on which that does not help, whose
-// tiles would be more than a fifth empty, or whose pairs are fewer keeps no
-// groups.
+// three and then to two directions; a lattice on which that does not help, or
+// whose tiles would be more than a fifth empty, keeps no groups.
 template <int R>
 int group_place(sgp_lattice* L, GroupBuild& gb, hipStream_t st) {
   const int64_t m = L->m;
@@ -1279,7 +1269,7 @@ int group_place(sgp_lattice* L, GroupBuild& gb, hipStream_t st) {
     return false;
   };
   for (int most = kGroupDirs - 1; most >= 2 && large(); --most) {
-    if (!group_divide(gb, L->d + 1, most) || (R == 1 && group_passes_lose(gb, L->d + 1))) return SGP_OK;
+    if (!group_divide(gb, L->d + 1, most)) return SGP_OK;
     if (large()) continue;
     if (const int rc = group_parts<R>(L, gb, st)) return rc;
     SGP_HIP(hipStreamSynchronize(st));
@@ -1313,6 +1303,7 @@ int group_place(sgp_lattice* L, GroupBuild& gb, hipStream_t st) {
     for (int g = 0; g < gb.n; ++g)
       if (gb.sp.first[g] == k) {
         L->group_dirs[L->ngroups] = gb.sp.dirs[g];
+        L->group_most = std::max(L->group_most, gb.sp.dirs[g]);
         L->group_tile[L->ngroups] = gb.sp.tile0[g];
         L->group_tiles[L->ngroups++] = (int32_t)group_tiles(gb.host + g * kGroupWords, kGroupClasses);
       }
@@ -1603,7 +1594,7 @@ int build_attempt(sgp_lattice* L, const float* X, const double* f, double load_f
   // ---- groups of blur directions: parts and their counts (the placing waits
   // for the counts, further on)
   GroupBuild gb;
-  L->ngroups = 0;
+  L->ngroups = L->group_most = 0;
   if (L->order <= 2 && d >= 5 && m >= kGroupMin && m <= kGroupMax &&
       tr.try_alloc(T_GROUP, kMaxGroups * (sizeof(uint32_t) * kGroupWords + kGroupSamples)) == hipSuccess) {
     // T_NBRC has been read: at least 2 (d + 1) words a point, three a group

@@ -1241,17 +1241,44 @@ void split_rows(int64_t rows, int R, int64_t cap, unsigned* blocks, int64_t* row
   *blocks = (unsigned)((rows + *rows_per_block - 1) / *rows_per_block);
 }
 
+// Whether the blur of C columns (fp64 inside CG) runs by the groups of directions
+// that the lattice keeps. Of order 1 they may be as many passes as the fused
+// pairs (dense lattices of few dimensions, mostly groups of two). A pair reads
+// nearby rows, coalesced, a group each row once, in no order, so groups then win
+// with wide rows on lattices that outgrow the L2s, and where a pair's lanes read
+// their four columns element by element. Pairs | groups, MVMs (fp32) and CG
+// iterations (fp64), microseconds: m = 62,000 (d = 6) C = 1 48 | 55, 4 62 | 68,
+// 8 66 | 73, 16 71 | 77, 32 119 | 107, fp64 2 76 | 80, 6 110 | 100, 8 85 | 90;
+// m = 245,000 (d = 6) C = 1 96 | 101, 3 152 | 144, 8 162 | 174, 11 346 | 261,
+// 16 200 | 188, fp64 1 131 | 139, 8 230 | 208; m = 673,000 (d = 8) C = 1
+// 205 | 220, 4 319 | 353, 8 410 | 392, 16 564 | 466, fp64 1 258 | 303, 2 339 |
+// 369, 4 455 | 396. Groups of two and one that are one pass more, m = 607,000
+// (d = 5): C = 1 112 | 141, 3 202 | 237, 6 312 | 268, 8 188 | 214, 12 238 | 287,
+// 16 257 | 257, 32 662 | 478, fp64 4 223 | 235, 6 437 | 311, 8 306 | 286.
+bool blur_by_groups(const sgp_lattice* L, int C, bool cg, bool fuse) {
+  if (!L->ngroups || !fuse) return false;
+  const int pairs = (L->d + 2) / 2;
+  if (L->order != 1 || L->ngroups < pairs) return true;
+  const int64_t row = (int64_t)C * (cg ? sizeof(double) : sizeof(float));
+  const bool whole = C == 1 || C % 4 == 0 || (cg && C == 2);  // lanes read an element, or 16-byte vectors
+  const bool more = L->ngroups > pairs && L->group_most <= 2;
+  if (!whole) return row >= 20 || !more;
+  return row >= 128 || (row >= (more ? 64 : 32) && L->m * row >= (8 << 20));
+}
+
 // m x C lattice value arrays that the blur works in beside the one it reads: its
 // ping-pong between two a chain (the second chain's other one may be the input,
 // where that need not outlive the blur: not inside CG), or one a chain, in place,
 // by groups of directions.
-int blur_arrays(const sgp_lattice* L, bool cg, bool fuse) { return L->ngroups && fuse ? 2 : cg ? 4 : 3; }
+int blur_arrays(const sgp_lattice* L, int C, bool cg, bool fuse) {
+  return blur_by_groups(L, C, cg, fuse) ? 2 : cg ? 4 : 3;
+}
 
 // Work memory of one MVM in elements of its accumulator type: m x C lattice
 // value arrays (the splat's result and the blur's), one partial row per run
 // piece, two fragment rows per gather range.
 size_t mvm_work_elems(const sgp_lattice* L, int C, bool cg, bool fuse) {
-  return (size_t)((1 + blur_arrays(L, cg, fuse)) * L->m + L->npiece + 2 * gather_ranges(L)) * (size_t)C;
+  return (size_t)((1 + blur_arrays(L, C, cg, fuse)) * L->m + L->npiece + 2 * gather_ranges(L)) * (size_t)C;
 }
 
 // U0 = the partial rows summed per lattice point (+ beta U0 per column when
@@ -1367,7 +1394,7 @@ int blur_g(const sgp_lattice* L, TU* U0, TU* B1, TU* B2, TU* B3, TU* B4, int C, 
     return chain == 0 ? ((L->blur == SGP_BLUR_REVERSE) ? d - step : step) : d - step;
   };
   const bool fuse = L->order == 1 && fused;
-  const bool groups = L->ngroups && fused;
+  const bool groups = blur_by_groups(L, C, sizeof(TU) == 8, fused);  // (fp64 is CG's)
   // Large lattices: the chains' launches run one chain after the other (all of
   // chain 0's, then chain 1's), so that a launch's arrays sit in the Infinity
   // Cache together.
@@ -1521,7 +1548,7 @@ int mvm_g(const sgp_lattice* L, const TU* V, const uint32_t* perm, int C, TU* ou
   TU* U0 = (TU*)work;
   TU* B1 = U0 + mC;
   TU* B2 = B1 + mC;
-  const int arrays = blur_arrays(L, cgm != nullptr, fuse);
+  const int arrays = blur_arrays(L, C, cgm != nullptr, fuse);
   TU* B3 = arrays > 2 ? B2 + mC : nullptr;
   TU* B4 = arrays > 3 ? B3 + mC : U0;  // chain 1's second array (U0 itself outside CG)
   TU* part = U0 + (1 + arrays) * mC;
@@ -1697,7 +1724,7 @@ LatWork lat_work(const sgp_lattice* L, int C, const CgLat& cl) {
   LatWork w = {};
   double* p = cl.work;
   for (double** a : {&w.yr, &w.yp, &w.yx, &w.u, &w.b1, &w.b2, &w.b3, &w.b4}) {
-    if (a == &w.b3 && blur_arrays(L, true, cl.fuse) == 2) break;
+    if (a == &w.b3 && blur_arrays(L, C, true, cl.fuse) == 2) break;
     *a = p;
     p += mC;
   }
@@ -1846,7 +1873,7 @@ bool cg_on_lattice(const sgp_lattice* L) {
 }
 
 size_t cg_lat_work_elems(const sgp_lattice* L, int C, bool fuse) {
-  return (size_t)((4 + blur_arrays(L, true, fuse)) * L->m + L->npiece + 2 * gather_ranges(L)) * (size_t)C;
+  return (size_t)((4 + blur_arrays(L, C, true, fuse)) * L->m + L->npiece + 2 * gather_ranges(L)) * (size_t)C;
 }
 
 int cg_lat_start(const sgp_lattice* L, int C, const CgLat& cl, hipStream_t s) {

@@ -239,6 +239,7 @@ struct sgp_lattice {
   // where there is no memory for them), each one's directions and tiles, the
   // tiles' rows
   int ngroups = 0;
+  int group_most = 0;  // directions of the longest
   int group_dirs[sgp::kMaxGroups] = {};
   int64_t group_tile[sgp::kMaxGroups] = {};   // first tile
   int32_t group_tiles[sgp::kMaxGroups] = {};
