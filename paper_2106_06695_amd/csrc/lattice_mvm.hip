@@ -269,17 +269,18 @@ __global__ __launch_bounds__(kSplatBlock) __attribute__((amdgpu_waves_per_eu(4))
 // k_gather_fix. The work per group is fixed, whatever the list lengths.
 // VW channels per lane (16-byte loads when the rows allow), G / VW lanes per
 // group; every channel's rows are added in the same order for any VW.
-// BETA (lattice CG): U = sum + beta U per column; a batch's old U rows are
-// requested with its partial rows, and the next batch's lattice points too, so
-// that no load waits for another: m = 141,000, 16 fp64 columns 76 -> 67 us
-// (2.2M rows, 4.1 TB/s), m = 80,000, 8 columns 32 -> 26 us; without BETA
-// m = 4.2M, 16 fp32 channels 350 -> 326 us.
-template <typename TU, int G, int VW, bool BETA>
+// AHEAD: a batch's lattice points are requested with the batch before it.
+// BETA (lattice CG, AHEAD): U = sum + beta U per column; a batch's old U rows are
+// then requested with its partial rows, so that no load waits for another:
+// m = 141,000, 16 fp64 columns 76 -> 67 us (2.2M rows, 4.1 TB/s), m = 80,000,
+// 8 columns 32 -> 26 us.
+template <typename TU, int G, int VW, bool AHEAD, bool BETA>
 __global__ __launch_bounds__(kBlock) void k_splat_gather(const int32_t* __restrict__ row_vert,
                                                          const TU* __restrict__ part,
                                                          TU* U, TU* __restrict__ frag,
                                                          int64_t nrows, int C, int64_t ngroups, int R,
                                                          const double* __restrict__ beta) {
+  static_assert(AHEAD || !BETA, "the old rows are found by the points requested ahead");
   constexpr int LG = G / VW;       // lanes per group
   constexpr int GPB = kBlock / LG;  // groups per block
   constexpr int B = 8;              // rows loaded together
@@ -292,55 +293,97 @@ __global__ __launch_bounds__(kBlock) void k_splat_gather(const int32_t* __restri
   // its lattice point continues across
   const int32_t before = o0 > 0 ? row_vert[o0 - 1] : -1;
   const int32_t after = o1 < nrows ? row_vert[o1] : -1;
-  for (int c = lane * VW; c < C; c += G) {
-    int64_t seg = o0;
-    TU acc[VW], bt[VW];
+  if constexpr (!AHEAD) {
+    for (int c = lane * VW; c < C; c += G) {
+      int32_t cur = row_vert[o0];
+      int64_t seg = o0;
+      TU acc[VW];
 #pragma unroll
-    for (int i = 0; i < VW; ++i) {
-      acc[i] = 0;
-      bt[i] = BETA ? (TU)beta[c + i] : (TU)0;
-    }
-    int32_t rv[B + 1];  // a batch's lattice points, and the next row's
-#pragma unroll
-    for (int u = 0; u < B; ++u) rv[u] = row_vert[o0 + u < o1 ? o0 + u : o1 - 1];
-    for (int64_t k0 = o0; k0 < o1; k0 += B) {
-      TU v[B][VW], old[BETA ? B : 1][VW];
-      int32_t rn[B];
-#pragma unroll
-      for (int u = 0; u < B; ++u) {
-        const int64_t k = k0 + u < o1 ? k0 + u : o1 - 1;
-        // partial rows are read once: non-temporal, which keeps the
-        // lattice values the blur reads next in the caches
-        read_row_nt<TU, VW>(part + k * C + c, v[u]);
-      }
-      if constexpr (BETA) {
-#pragma unroll
-        for (int u = 0; u < B; ++u) read_row<TU, VW>(U + (int64_t)rv[u] * C + c, old[u]);
-      }
-#pragma unroll
-      for (int u = 0; u < B; ++u) rn[u] = row_vert[k0 + B + u < o1 ? k0 + B + u : o1 - 1];
-      rv[B] = rn[0];
-#pragma unroll
-      for (int u = 0; u < B; ++u) {
-        const int64_t k = k0 + u;
-        if (k < o1) {
-#pragma unroll
-          for (int i = 0; i < VW; ++i) acc[i] += v[u][i];
-        }
-        if (k >= o1 || (k + 1 < o1 && rv[u + 1] == rv[u])) continue;
-        const bool whole = (seg > o0 || before != rv[u]) && (k + 1 < o1 || after != rv[u]);
-        TU* dst = whole ? U + (int64_t)rv[u] * C + c : frag + (gi * 2 + (seg == o0 ? 0 : 1)) * C + c;
-        if (BETA && whole) {
-#pragma unroll
-          for (int i = 0; i < VW; ++i) acc[i] = fma_t(bt[i], old[BETA ? u : 0][i], acc[i]);
-        }
+      for (int i = 0; i < VW; ++i) acc[i] = 0;
+      auto flush = [&](int64_t end) {
+        const bool whole = (seg > o0 || before != cur) && (end < o1 || after != cur);
+        TU* dst = whole ? U + (int64_t)cur * C + c : frag + (gi * 2 + (seg == o0 ? 0 : 1)) * C + c;
         write_row<TU, VW>(dst, acc);
-        seg = k + 1;
+      };
+      for (int64_t k0 = o0; k0 < o1; k0 += B) {
+        TU v[B][VW];
+        int32_t rv[B];
 #pragma unroll
-        for (int i = 0; i < VW; ++i) acc[i] = 0;
+        for (int u = 0; u < B; ++u) {
+          const int64_t k = k0 + u < o1 ? k0 + u : o1 - 1;
+          // partial rows are read once: non-temporal, which keeps the
+          // lattice values the blur reads next in the caches
+          read_row_nt<TU, VW>(part + k * C + c, v[u]);
+          rv[u] = row_vert[k];
+        }
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+          if (k0 + u < o1) {
+            if (rv[u] != cur) {
+              flush(k0 + u);
+              cur = rv[u];
+              seg = k0 + u;
+#pragma unroll
+              for (int i = 0; i < VW; ++i) acc[i] = 0;
+            }
+#pragma unroll
+            for (int i = 0; i < VW; ++i) acc[i] += v[u][i];
+          }
+        }
       }
+      flush(o1);
+    }
+  } else {
+    for (int c = lane * VW; c < C; c += G) {
+      int64_t seg = o0;
+      TU acc[VW], bt[VW];
 #pragma unroll
-      for (int u = 0; u < B; ++u) rv[u] = rn[u];
+      for (int i = 0; i < VW; ++i) {
+        acc[i] = 0;
+        bt[i] = BETA ? (TU)beta[c + i] : (TU)0;
+      }
+      int32_t rv[B + 1];  // a batch's lattice points, and the next row's
+#pragma unroll
+      for (int u = 0; u < B; ++u) rv[u] = row_vert[o0 + u < o1 ? o0 + u : o1 - 1];
+      for (int64_t k0 = o0; k0 < o1; k0 += B) {
+        TU v[B][VW], old[BETA ? B : 1][VW];
+        int32_t rn[B];
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+          const int64_t k = k0 + u < o1 ? k0 + u : o1 - 1;
+          // partial rows are read once: non-temporal, which keeps the
+          // lattice values the blur reads next in the caches
+          read_row_nt<TU, VW>(part + k * C + c, v[u]);
+        }
+        if constexpr (BETA) {
+#pragma unroll
+          for (int u = 0; u < B; ++u) read_row<TU, VW>(U + (int64_t)rv[u] * C + c, old[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < B; ++u) rn[u] = row_vert[k0 + B + u < o1 ? k0 + B + u : o1 - 1];
+        rv[B] = rn[0];
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+          const int64_t k = k0 + u;
+          if (k < o1) {
+#pragma unroll
+            for (int i = 0; i < VW; ++i) acc[i] += v[u][i];
+          }
+          if (k >= o1 || (k + 1 < o1 && rv[u + 1] == rv[u])) continue;
+          const bool whole = (seg > o0 || before != rv[u]) && (k + 1 < o1 || after != rv[u]);
+          TU* dst = whole ? U + (int64_t)rv[u] * C + c : frag + (gi * 2 + (seg == o0 ? 0 : 1)) * C + c;
+          if (BETA && whole) {
+#pragma unroll
+            for (int i = 0; i < VW; ++i) acc[i] = fma_t(bt[i], old[BETA ? u : 0][i], acc[i]);
+          }
+          write_row<TU, VW>(dst, acc);
+          seg = k + 1;
+#pragma unroll
+          for (int i = 0; i < VW; ++i) acc[i] = 0;
+        }
+#pragma unroll
+        for (int u = 0; u < B; ++u) rv[u] = rn[u];
+      }
     }
   }
 }
@@ -1291,11 +1334,24 @@ int gather_g(const sgp_lattice* L, const TU* part, TU* U0, TU* frag, int C, cons
   const int R = gather_rows(L);
   const int64_t ngroups = gather_ranges(L);
   constexpr int VWG = 16 / (int)sizeof(TU);  // channels per lane with 16-byte loads
+  // Lattice points requested ahead pay where the rows outgrow the caches and the
+  // waves are too few to hide their latency, first with one lane a range; below,
+  // the loads past a range's end and the registers cost more. In the batch | ahead,
+  // microseconds: 0.38M rows, C = 1 fp32 37 | 35, 8 31 | 33, 16 24 | 28, fp64 8
+  // 23 | 28; 0.95M rows 1 42 | 39, 8 37 | 39, 16 30 | 36, fp64 8 29 | 35; 1.7M rows
+  // 1 44 | 40, 3 34 | 33, 8 46 | 46, 16 58 | 59, fp64 3 45 | 42; 3.1M rows 1 52 | 45,
+  // 8 92 | 85, 16 90 | 84, fp64 2 72 | 64, 16 108 | 108; 4.0M rows 8 106 | 96.
   auto launch = [&](auto vw_tag, auto beta_tag) {
     constexpr int VW = decltype(vw_tag)::value;
-    const int64_t blocks = (ngroups + kBlock / (G / VW) - 1) / (kBlock / (G / VW));
-    hipLaunchKernelGGL((k_splat_gather<TU, G, VW, decltype(beta_tag)::value>), dim3((unsigned)blocks), dim3(kBlock), 0,
-                       s, (const int32_t*)L->row_vert.ptr, part, U0, frag, L->npiece, C, ngroups, R, beta);
+    constexpr bool BETA = decltype(beta_tag)::value;
+    const unsigned blocks = (unsigned)((ngroups + kBlock / (G / VW) - 1) / (kBlock / (G / VW)));
+    const bool ahead = BETA || L->npiece >= (G == VW ? (int64_t)1 << 18 : (int64_t)3 << 19);
+    if (ahead)
+      hipLaunchKernelGGL((k_splat_gather<TU, G, VW, true, BETA>), dim3(blocks), dim3(kBlock), 0, s,
+                         (const int32_t*)L->row_vert.ptr, part, U0, frag, L->npiece, C, ngroups, R, beta);
+    else if constexpr (!BETA)
+      hipLaunchKernelGGL((k_splat_gather<TU, G, VW, false, false>), dim3(blocks), dim3(kBlock), 0, s,
+                         (const int32_t*)L->row_vert.ptr, part, U0, frag, L->npiece, C, ngroups, R, beta);
   };
   auto widths = [&](auto beta_tag) {
     if (G % VWG == 0 && C % VWG == 0 && aligned16(part) && aligned16(U0) && aligned16(frag))
